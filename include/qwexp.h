@@ -20,15 +20,17 @@
  *   - stream is a hipStream_t passed as void* (NULL = the null stream).  Calls
  *     enqueue their kernels on it.  Host synchronisation of an action call:
  *       * the spectral bound (plain calls, qw_spectral_bound_*) is read back
- *         once, 16 bytes; this one wait also covers the upload of (h, J);
- *       * calls given (c, r) with the diagonal from (h, J) wait once for that
- *         upload unless the norm monitor's read-back follows;
- *       * the one-workgroup path (n <= 13, complex64 or complex128, no norm
- *         monitor) waits once more, at its end, for its coefficient upload;
+ *         once, 16 bytes, except where an action call of n <= 13 with the
+ *         diagonal from (h, J) and no norm monitor finds it on the host;
  *       * the norm monitor reads back its K + 2 norms at the end (one wait);
  *       * timing != 0 waits for the call's last event.
- *     So a plain call of n >= 14 synchronises exactly once, at the read-back,
- *     before its Clenshaw passes are enqueued; they run asynchronously.
+ *     So a plain call synchronises at most once, at the read-back, before its
+ *     recurrence is enqueued; that runs asynchronously.  Host arrays may be
+ *     freed when a call returns.
+ *   - The recurrence of n <= 20 qubits (complex128: 19) without norm monitor is
+ *     one launch whose workgroups exchange data; workgroups that cannot all
+ *     start together (the device shared with many waiting kernels) make one of
+ *     them run it alone, slowly, with results that differ by rounding.
  *   - Errors: every call returns a qw_status; nothing is thrown across the ABI.
  *     qw_last_error() returns a thread-local message for the last failure.
  *   - Calls on distinct workspaces may run concurrently from different threads.
@@ -428,6 +430,12 @@ int qw_debug_check_plan(int n, int precision);
  * term k, final flag) written to out (4*cap ints).  Returns the number of
  * passes; nothing is written when it exceeds cap.  Launches nothing. */
 int qw_debug_schedule(int K, int P, int *out, int cap);
+
+/* For tests: how often the workgroups of a one-launch recurrence look at their
+ * common start before one of them runs the recurrence alone (calls of this host
+ * thread from now on; negative: the default, some 0.1 s).  The results differ
+ * only by rounding.  Returns the value before. */
+int qw_debug_start_patience(int looks);
 
 /* Library version string. */
 const char *qw_version(void);

@@ -21,6 +21,7 @@
 // whole recurrence inside one workgroup with the vector resident in LDS.
 #include "qw_kernels.h"
 #include "qw_prepared.h"
+#include "qw_resident.h"
 
 #include <hip/hip_runtime.h>
 
@@ -33,6 +34,7 @@
 
 namespace qw {
 
+static thread_local int t_patience = RES_PATIENCE;   // qw_debug_start_patience
 static thread_local std::string g_err;
 void set_error(const std::string &msg) { g_err = msg; }
 
@@ -112,47 +114,120 @@ static WsLayout ws_layout(int n, int prec, bool otf)
 }
 
 
-// Host copy of (h, J) for the upload of setup_tables.  The asynchronous copy
-// reads it when the stream reaches it, so it must outlive that point: calls
-// whose bound read-back follows the upload (which synchronises the stream)
-// need nothing more; otherwise the destructor synchronises once.
-struct HostTables {
-    hipStream_t s = nullptr;
-    std::vector<double> hj;
-    bool pending = false;
-    ~HostTables()
-    {
-        if (pending) (void)hipStreamSynchronize(s);
-    }
+// Small host arrays travel as kernel arguments (a launch keeps its own copy, so
+// nothing on the host has to outlive the call and no copy engine is involved).
+struct PutBlob {
+    static constexpr int WORDS = 440;   // arguments stay below 4 KB
+    uint64_t v[WORDS];
 };
 
-// Upload h, J (staged in `keep`), build the Q table; returns the tables view.
-static qw_status setup_tables(int n, const double *h, const double *J, char *ws, const WsLayout &L,
-                              hipStream_t s, EnergyTables *T, HostTables &keep)
+template <int D = 0>
+__global__ void __launch_bounds__(256) k_put(PutBlob b, int count, uint64_t *dst, int *lines, int nlines,
+                                             int *two)
+{
+    for (int i = threadIdx.x; i < count; i += 256) dst[i] = b.v[i];
+    for (int i = threadIdx.x; i < nlines; i += 256) lines[i * RES_LINE] = 0;
+    if (nlines > 0 && threadIdx.x < 2) two[threadIdx.x * RES_LINE] = 0;
+}
+
+// Copies `count` 8-byte words to dst; the last launch also clears the first
+// word of nlines lines and of the two lines at `two`.
+static qw_status put(const void *src, size_t count, void *dst, hipStream_t s, int *lines = nullptr, int nlines = 0,
+                     int *two = nullptr)
+{
+    PutBlob b;
+    for (size_t off = 0; off < count; off += PutBlob::WORDS) {
+        const size_t m = std::min<size_t>(PutBlob::WORDS, count - off);
+        std::memcpy(b.v, static_cast<const uint64_t *>(src) + off, m * sizeof(uint64_t));
+        hipLaunchKernelGGL(k_put<0>, dim3(1), dim3(256), 0, s, b, (int)m, static_cast<uint64_t *>(dst) + off, lines,
+                           off + m == count ? nlines : 0, two);
+    }
+    QW_HIP(hipGetLastError());
+    return QW_OK;
+}
+
+// Puts (h, J) into the workspace; returns the tables view, whose pair table is
+// built by build_qtable.
+static qw_status upload_couplings(int n, const double *h, const double *J, char *ws, const WsLayout &L, hipStream_t s,
+                                  EnergyTables *T)
 {
     const int np = n * (n - 1) / 2;
-    keep.s = s;
-    keep.hj.assign(n + np, 0.0);
-    std::memcpy(keep.hj.data(), h, n * sizeof(double));
-    if (np) std::memcpy(keep.hj.data() + n, J, np * sizeof(double));
+    std::vector<double> hj(n + np);
+    std::memcpy(hj.data(), h, n * sizeof(double));
+    if (np) std::memcpy(hj.data() + n, J, np * sizeof(double));
     double *dhj = reinterpret_cast<double *>(ws + L.hj);
-    QW_HIP(hipMemcpyAsync(dhj, keep.hj.data(), keep.hj.size() * sizeof(double), hipMemcpyHostToDevice, s));
-    keep.pending = true;
     T->h = dhj;
     T->J = dhj + n;
     T->Q = reinterpret_cast<double *>(ws + L.q);
     T->n = n;
     T->LB = std::min(n, LB_TAB);
-    const int nq = 1 << T->LB;
-    hipLaunchKernelGGL(k_qtable<0>, dim3((nq + 255) / 256), dim3(256), 0, s, *T, const_cast<double *>(T->Q));
+    return put(hj.data(), hj.size(), dhj, s);
+}
+
+static qw_status build_qtable(const EnergyTables &T, hipStream_t s)
+{
+    const int nq = 1 << T.LB;
+    hipLaunchKernelGGL(k_qtable<0>, dim3((nq + 255) / 256), dim3(256), 0, s, T, const_cast<double *>(T.Q));
     QW_HIP(hipGetLastError());
     return QW_OK;
+}
+
+// Min / max of E over all z by direct sums, for the sizes that run in one
+// launch and build no pair table.  256 threads.
+template <int D = 0>
+__global__ void __launch_bounds__(256) k_minmax_direct(const double *hJ, int n, double *part)
+{
+    __shared__ double c[32 + 32 * 31 / 2];
+    for (int i = threadIdx.x; i < n + n * (n - 1) / 2; i += 256) c[i] = hJ[i];
+    __syncthreads();
+    double mn = INFINITY, mx = -INFINITY;
+    for (uint32_t z = blockIdx.x * 256 + threadIdx.x; z < (1u << n); z += gridDim.x * 256) {
+        const double e = energy_direct(c, n, z);
+        mn = fmin(mn, e);
+        mx = fmax(mx, e);
+    }
+    block_minmax(mn, mx, part);
+}
+
+// The same on the host for small instances (n <= HOST_RANGE_NMAX, 2^n 16 adds
+// by doubling): no read-back, so the call need not wait.  At 13 qubits 12 us
+// against 60 us for the kernels, the copy and the wait.
+static constexpr int HOST_RANGE_NMAX = 13;
+static void host_energy_range(int n, const double *h, const double *J, double *emin, double *emax)
+{
+    std::vector<double> E(size_t(1) << n), f(size_t(1) << n);
+    E[0] = 0.0;
+    for (int j = 0; j < n; ++j) {
+        // f: field of bits 0..j-1 on spin j; then both signs of spin j
+        f[0] = h[j];
+        for (int k = 0; k < j; ++k) {
+            const double x = J[pair_off(n, k, j)];
+            const size_t m = size_t(1) << k;
+            for (size_t z = 0; z < m; ++z) {
+                f[z + m] = f[z] - x;
+                f[z] += x;
+            }
+        }
+        const size_t m = size_t(1) << j;
+        for (size_t z = 0; z < m; ++z) {
+            E[z + m] = E[z] - f[z];
+            E[z] += f[z];
+        }
+    }
+    double mn = INFINITY, mx = -INFINITY;
+    for (double e : E) {
+        if (e != e) mn = -INFINITY;   // overflowed sums: a non-finite range
+        mn = std::min(mn, e);
+        mx = std::max(mx, e);
+    }
+    *emin = mn;
+    *emax = mx;
 }
 
 // Min / max of the energies: the one synchronising read-back of a call.
 template <typename R>
 static qw_status minmax(int n, const R *diag, const EnergyTables *T, char *ws, const WsLayout &L,
-                        hipStream_t s, double *emin, double *emax, HostTables *keep = nullptr)
+                        hipStream_t s, double *emin, double *emax, bool direct = false)
 {
     double *part = reinterpret_cast<double *>(ws + L.part);
     double *red = reinterpret_cast<double *>(ws + L.red);
@@ -161,6 +236,9 @@ static qw_status minmax(int n, const R *diag, const EnergyTables *T, char *ws, c
         const uint64_t N = uint64_t(1) << n;
         np = grid_for(N, 256 * 16, MAXPART);
         hipLaunchKernelGGL(k_minmax_diag<R>, dim3(np), dim3(256), 0, s, diag, N, part);
+    } else if (direct) {
+        np = grid_for(uint64_t(1) << n, 256 * 4, MAXPART);
+        hipLaunchKernelGGL(k_minmax_direct<0>, dim3(np), dim3(256), 0, s, T->h, n, part);
     } else {
         const uint64_t ntiles = uint64_t(1) << (n - T->LB);
         np = grid_for(ntiles, 1, MAXPART);
@@ -172,7 +250,6 @@ static qw_status minmax(int n, const R *diag, const EnergyTables *T, char *ws, c
     double h2[2];
     QW_HIP(hipMemcpyAsync(h2, red, sizeof(h2), hipMemcpyDeviceToHost, s));
     QW_HIP(hipStreamSynchronize(s));
-    if (keep) keep->pending = false;   // the upload of (h, J) has been read
     *emin = h2[0];
     *emax = h2[1];
     return QW_OK;
@@ -204,20 +281,32 @@ static qw_status validate(int n, const R *diag, const double *h, const double *J
     return QW_OK;
 }
 
-// Spectral shift / bound, optionally uploading tables.  Leaves T valid when
-// diag == NULL.
+// Couplings on the device and the range of E.  `resident`: for a call that runs
+// in one launch, without the pair table.
 template <typename R>
-static qw_status bound_impl(int n, const R *diag, const double *h, const double *J, double gamma,
+static qw_status energy_range(int n, const R *diag, const double *h, const double *J, bool resident, char *ws,
+                              const WsLayout &L, hipStream_t s, EnergyTables *T, double *emin, double *emax)
+{
+    if (diag) return minmax<R>(n, diag, T, ws, L, s, emin, emax);
+    qw_status st = upload_couplings(n, h, J, ws, L, s, T);
+    if (st != QW_OK) return st;
+    if (resident && n <= HOST_RANGE_NMAX) {
+        host_energy_range(n, h, J, emin, emax);
+        return QW_OK;
+    }
+    if (!resident && (st = build_qtable(*T, s)) != QW_OK) return st;
+    return minmax<R>(n, nullptr, T, ws, L, s, emin, emax, resident);
+}
+
+// Spectral shift / bound, optionally uploading the couplings.  Leaves T valid
+// when diag == NULL (without its pair table if `resident`).
+template <typename R>
+static qw_status bound_impl(int n, const R *diag, const double *h, const double *J, double gamma, bool resident,
                             char *ws, const WsLayout &L, hipStream_t s, EnergyTables *T,
                             double *c, double *r)
 {
-    HostTables keep;
-    if (!diag) {
-        qw_status st = setup_tables(n, h, J, ws, L, s, T, keep);
-        if (st != QW_OK) return st;
-    }
     double emin, emax;
-    qw_status st = minmax<R>(n, diag, T, ws, L, s, &emin, &emax, &keep);
+    qw_status st = energy_range<R>(n, diag, h, J, resident, ws, L, s, T, &emin, &emax);
     if (st != QW_OK) return st;
     if (!finite(emin) || !finite(emax)) { set_error("diagonal has non-finite entries"); return QW_EINVAL; }
     *c = 0.5 * (emax + emin);
@@ -430,10 +519,18 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     timer.mark(0);
 
     EnergyTables T{};
-    HostTables keep;   // (h, J) staged for an upload with no read-back after it
     double c = 0.0, r = 0.0;
     if (poly && info && info->monitor) { set_error("the norm monitor applies to exp(-itH) only"); return QW_EINVAL; }
     const bool monitor = !poly && ((info && info->monitor) || (given_cr && !prep));
+    // one launch for the whole recurrence (unless the degree turns out too large
+    // for the coefficients' place); a cooperative launch is not recorded into graphs
+    bool resident = !monitor && n <= resident_nmax<R>();
+    if (resident && resident_coop<R>(n)) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        QW_HIP(hipStreamIsCapturing(s, &cap));
+        resident = cap == hipStreamCaptureStatusNone;
+    }
+    bool have_q = !resident;   // pair table built
     if (given_cr) {
         c = given_cr[0];
         r = given_cr[1];
@@ -441,13 +538,15 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         if (!diag) {
             if (prep) {
                 T = prep->T;
+                have_q = prep->have_q;
             } else {
-                st = setup_tables(n, h, J, ws, L, s, &T, keep);
+                st = upload_couplings(n, h, J, ws, L, s, &T);
+                if (st == QW_OK && have_q) st = build_qtable(T, s);
                 if (st != QW_OK) return st;
             }
         }
     } else {
-        st = bound_impl<R>(n, diag, h, J, gamma, ws, L, s, &T, &c, &r);
+        st = bound_impl<R>(n, diag, h, J, gamma, resident, ws, L, s, &T, &c, &r);
         if (st != QW_OK) return st;
     }
 
@@ -509,17 +608,6 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     if (any_otf && !(L.ft != size_t(-1))) { set_error("internal: no per-tile field table for this size"); return QW_EINVAL; }
     double *ft = any_otf ? reinterpret_cast<double *>(ws + L.ft) : nullptr;
     const uint64_t ft_stride = (N >> TB_NARROW) * TILE_FIELDS;   // doubles per orientation
-    if (!otf && plan_reads_diag(plan)) {
-        if (diag) {
-            hipLaunchKernelGGL(k_normalize_diag<R>, dim3(grid_for(N, 256 * 8, 1 << 16)), dim3(256), 0, s,
-                               diag, N, c, inv_r, dn);
-        } else {
-            hipLaunchKernelGGL(k_normalize_energy<R>, dim3(grid_for(N >> T.LB, 1, 1 << 16)), dim3(256), 0, s,
-                               T, norm_c, norm_inv_r, dn);
-        }
-    }
-    QW_HIP(hipGetLastError());
-
     // coefficients (host, double): c_k = (-i)^k alpha_k, or the caller's
     const double a = poly ? 0.0 : t * r;
     std::vector<double> alpha;
@@ -550,32 +638,6 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
             if (plan[o].otf) info->otf_mask |= 1 << o;
     }
 
-    if (n <= Cfg<R>::TB && !monitor) {
-        // on-chip: whole recurrence in one workgroup
-        if (K > KMAX_ONCHIP) { set_error("degree too large for the on-chip path"); return QW_ENOMEM; }
-        std::vector<C> ch(K + 1);
-        for (int k = 0; k <= K; ++k) {
-            ch[k].x = (R)cre[k];
-            ch[k].y = (R)cim[k];
-        }
-        C *dcoef = reinterpret_cast<C *>(ws + L.coef);
-        OnchipItem<R> item{psi, out, dn, dcoef, (R)g, (R)ph_r, (R)ph_i, n, K};
-        if (horner) {
-            item.two = R(1);
-            item.sub = R(0);
-        }
-        OnchipItem<R> *ditem = reinterpret_cast<OnchipItem<R> *>(ws + L.items);
-        QW_HIP(hipMemcpyAsync(dcoef, ch.data(), ch.size() * sizeof(C), hipMemcpyHostToDevice, s));
-        QW_HIP(hipMemcpyAsync(ditem, &item, sizeof(item), hipMemcpyHostToDevice, s));
-        timer.mark(1);
-        hipLaunchKernelGGL((k_onchip<R, Cfg<R>::TB, ONCHIP_NT>), dim3(1), dim3(ONCHIP_NT), 0, s,
-                           (const OnchipItem<R> *)ditem, (const int *)nullptr, 1);
-        QW_HIP(hipGetLastError());
-        QW_HIP(hipStreamSynchronize(s));  // host copies of ch/item go out of scope
-        keep.pending = false;
-        return timer.finish(info);
-    }
-
     if (K == 0) {
         const double cr = cre[0], ci = cim[0];
         const double pr = cr * ph_r - ci * ph_i, pi = cr * ph_i + ci * ph_r;
@@ -589,6 +651,62 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     C *X = reinterpret_cast<C *>(ws + L.b1);
     C *Y = reinterpret_cast<C *>(ws + L.b2);
     double *norms = reinterpret_cast<double *>(ws + L.norms);
+
+    // up to 13 qubits the coefficients have a place of their own, above it they
+    // take that of the split pair tables; the flags take that of the norms
+    const bool own_coef = L.coef != size_t(-1);
+    if (resident && own_coef && K > KMAX_ONCHIP) {
+        if (n <= Cfg<R>::TB) { set_error("degree too large for the on-chip path"); return QW_ENOMEM; }
+        resident = false;
+    }
+    if (resident && !own_coef && (size_t)(K + 1) * sizeof(C) > 4 * (size_t(1) << TB_WIDE) * sizeof(double)) resident = false;
+    if (resident) {
+        std::vector<C> ch(K + 1);
+        for (int k = 0; k <= K; ++k) {
+            ch[k].x = (R)cre[k];
+            ch[k].y = (R)cim[k];
+        }
+        ResArgs<R> ra{};
+        ra.psi = psi;
+        ra.out = out;
+        ra.diag = diag;
+        ra.hJ = T.h;
+        ra.c = norm_c;
+        ra.inv_r = norm_inv_r;
+        ra.X0 = X;
+        ra.X1 = Y;
+        ra.d = dn;
+        ra.start = reinterpret_cast<int *>(ws + L.items);
+        ra.flags = reinterpret_cast<int *>(norms);
+        ra.g = (R)g;
+        ra.two = horner ? R(1) : R(2);
+        ra.sub = horner ? R(0) : R(1);
+        ra.pr = (R)ph_r;
+        ra.pi = (R)ph_i;
+        ra.n = n;
+        ra.K = K;
+        ra.patience = t_patience;
+        C *dcoef = reinterpret_cast<C *>(ws + (own_coef ? L.coef : L.qt));
+        ra.coef = dcoef;
+        st = put(ch.data(), ch.size() * sizeof(C) / sizeof(uint64_t), dcoef, s, ra.flags, RES_MAXFLAGS, ra.start);
+        if (st != QW_OK) return st;
+        timer.mark(1);
+        QW_HIP(launch_resident<R>(ra, s));
+        return timer.finish(info);
+    }
+
+    if (!otf && plan_reads_diag(plan)) {
+        if (diag) {
+            hipLaunchKernelGGL(k_normalize_diag<R>, dim3(grid_for(N, 256 * 8, 1 << 16)), dim3(256), 0, s,
+                               diag, N, c, inv_r, dn);
+        } else {
+            if (!have_q && (st = build_qtable(T, s)) != QW_OK) return st;
+            hipLaunchKernelGGL(k_normalize_energy<R>, dim3(grid_for(N >> T.LB, 1, 1 << 16)), dim3(256), 0, s,
+                               T, norm_c, norm_inv_r, dn);
+        }
+    }
+    QW_HIP(hipGetLastError());
+
     if (monitor) {
         if (K + 2 > KMAX_MON) { set_error("degree too large for the norm monitor"); return QW_ENOMEM; }
         // cleared by a kernel, not a memset node, so that the call can be captured
@@ -705,7 +823,6 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     if (tst != QW_OK || !monitor) return tst;
     tst = check_growth(n, K, alpha, tol, sizeof(R) == 4 ? std::ldexp(1.0, -24) : std::ldexp(1.0, -53), norms, s,
                        info);
-    keep.pending = false;   // check_growth synchronised the stream
     return tst;
 }
 
@@ -718,7 +835,7 @@ static qw_status bound_entry(int n, const R *diag, const double *h, const double
     const WsLayout L = ws_layout(n, prec_of<R>(), diag == nullptr && n >= OTF_NMIN && sizeof(R) == 4);
     if (ws_bytes < L.total) { set_error("workspace too small"); return QW_ENOMEM; }
     EnergyTables T{};
-    return bound_impl<R>(n, diag, h, J, gamma, static_cast<char *>(workspace), L,
+    return bound_impl<R>(n, diag, h, J, gamma, false, static_cast<char *>(workspace), L,
                          reinterpret_cast<hipStream_t>(stream), &T, c, r);
 }
 
@@ -774,7 +891,7 @@ static qw_status poly_entry(int n, const R *diag, const double *h, const double 
 
 template <typename R>
 qw_status prepare_energy(int n, const double *h, const double *J, void *workspace, size_t ws_bytes, void *stream,
-                         EnergyTables *T, double *emin, double *emax)
+                         EnergyTables *T, bool *have_q, double *emin, double *emax)
 {
     if (n < 1 || n > 32 || !h || (n > 1 && !J) || !workspace) { set_error("bad arguments"); return QW_EINVAL; }
     const WsLayout L = ws_layout(n, prec_of<R>(), n >= OTF_NMIN && sizeof(R) == 4);
@@ -784,20 +901,18 @@ qw_status prepare_energy(int n, const double *h, const double *J, void *workspac
     }
     char *ws = static_cast<char *>(workspace);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    HostTables keep;
-    qw_status st = setup_tables(n, h, J, ws, L, s, T, keep);
-    if (st != QW_OK) return st;
-    return minmax<R>(n, nullptr, T, ws, L, s, emin, emax, &keep);
+    *have_q = n > resident_nmax<R>();
+    return energy_range<R>(n, (const R *)nullptr, h, J, !*have_q, ws, L, s, T, emin, emax);
 }
 
 template <typename R>
-qw_status scaled_action(int n, const double *h, const double *J, const EnergyTables &T, double alpha, double emin,
-                        double emax, double beta, double t, const void *psi_in, void *psi_out, double tol,
+qw_status scaled_action(int n, const double *h, const double *J, const EnergyTables &T, bool have_q, double alpha,
+                        double emin, double emax, double beta, double t, const void *psi_in, void *psi_out, double tol,
                         void *workspace, size_t ws_bytes, void *stream, qw_info *info)
 {
     const double c = alpha * 0.5 * (emax + emin);
     const double r = std::fabs(alpha) * 0.5 * (emax - emin) + n * std::fabs(beta);
-    const Prepared prep{T, alpha};
+    const Prepared prep{T, have_q, alpha};
     if (!(r > 0.0)) {
         // H' = c I (here c = 0 as well): the identity
         if (psi_out == psi_in) return QW_OK;
@@ -811,13 +926,13 @@ qw_status scaled_action(int n, const double *h, const double *J, const EnergyTab
 }
 
 template qw_status prepare_energy<float>(int, const double *, const double *, void *, size_t, void *, EnergyTables *,
-                                         double *, double *);
+                                         bool *, double *, double *);
 template qw_status prepare_energy<double>(int, const double *, const double *, void *, size_t, void *, EnergyTables *,
-                                          double *, double *);
-template qw_status scaled_action<float>(int, const double *, const double *, const EnergyTables &, double, double,
+                                          bool *, double *, double *);
+template qw_status scaled_action<float>(int, const double *, const double *, const EnergyTables &, bool, double, double,
                                         double, double, double, const void *, void *, double, void *, size_t, void *,
                                         qw_info *);
-template qw_status scaled_action<double>(int, const double *, const double *, const EnergyTables &, double, double,
+template qw_status scaled_action<double>(int, const double *, const double *, const EnergyTables &, bool, double, double,
                                          double, double, double, const void *, void *, double, void *, size_t, void *,
                                          qw_info *);
 
@@ -1055,6 +1170,13 @@ int qw_debug_schedule(int K, int P, int *out, int cap)
             out[4 * i + 3] = S[i].fin;
         }
     return (int)S.size();
+}
+
+int qw_debug_start_patience(int looks)
+{
+    const int old = t_patience;
+    t_patience = looks < 0 ? RES_PATIENCE : looks;
+    return old;
 }
 
 // Host-only self check of the pass index maps; returns the number of passes or

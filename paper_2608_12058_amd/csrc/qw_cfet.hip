@@ -152,8 +152,9 @@ qw_status cfet_impl(int n, const double *h, const double *J, const double *A_coe
     };
 
     EnergyTables Tb{};
+    bool have_q = false;
     double emin = 0.0, emax = 0.0;
-    st = prepare_energy<R>(n, h, J, workspace, ws_bytes, stream, &Tb, &emin, &emax);
+    st = prepare_energy<R>(n, h, J, workspace, ws_bytes, stream, &Tb, &have_q, &emin, &emax);
     if (st != QW_OK) { cleanup(); return st; }
     Instance I{n, 0.5 * (emax - emin), std::max(std::fabs(emin), std::fabs(emax)), commutator_bound(n, h, J)};
 
@@ -195,7 +196,7 @@ qw_status cfet_impl(int n, const double *h, const double *J, const double *A_coe
         const double tol_exp = std::max(floor_tol, trunc_share * tol * hs / T);
         for (int e = 0; e < 2; ++e) {
             qw_info ai{};
-            st = scaled_action<R>(n, h, J, Tb, al[e], emin, emax, be[e], hs, src, psi_out, tol_exp, workspace,
+            st = scaled_action<R>(n, h, J, Tb, have_q, al[e], emin, emax, be[e], hs, src, psi_out, tol_exp, workspace,
                                   ws_bytes, stream, &ai);
             if (st != QW_OK) { cleanup(); return st; }
             src = psi_out;

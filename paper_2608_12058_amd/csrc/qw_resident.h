@@ -1,0 +1,467 @@
+// The whole recurrence of one instance in a single launch: the vectors stay in
+// the registers of W = 2^HC workgroups, one tile of 2^T consecutive amplitudes
+// each, and only b_{k+1} travels between them.
+#pragma once
+
+#include "qw_device.h"
+#include "qw_internal.h"
+#include "qw_kernels.h"
+
+#include <atomic>
+
+namespace qw {
+
+typedef int qw_i4 __attribute__((ext_vector_type(4)));
+
+static constexpr int RES_XCDS = 8;
+// One flag per wave, each on a cache line of its own (flags that shared lines
+// tripled the time of a round over 256 workgroups), and the start word and the
+// mask of XCDs on two more lines.
+static constexpr int RES_LINE = 32;            // 4-byte words per line
+static constexpr int RES_MAXFLAGS = 4096;
+static constexpr int RES_PATIENCE = 1 << 17;   // looks at the start word, some 0.1 s
+static constexpr int RES_POLLS = 1 << 24;      // looks at a flag, seconds
+
+template <typename R> struct ResArgs {
+    using C = typename Cplx<R>::T;
+    const C *psi;
+    C *out;               // may be psi
+    const R *diag;        // the caller's energies, or NULL: from (h, J)
+    const double *hJ;     // device: h (n), J (packed)
+    double c, inv_r;      // d~ = (E - c) inv_r
+    const C *coef;        // device: c_0 .. c_K
+    C *X0, *X1;           // exchange buffers of 2^n
+    R *d;                 // 2^n, used only when the workgroups cannot all start
+    int *start, *flags;   // 2 and RES_MAXFLAGS lines, cleared before the launch
+    R g, two, sub;        // gamma / r; Clenshaw 2 and 1, Horner's rule 1 and 0
+    R pr, pi;             // global phase
+    int n, K;
+    int stride, sel;      // workgroups with blockIdx.x % stride == sel take part
+    int patience;         // looks at the start word before giving up on a common start
+};
+
+// E(z) from couplings in LDS (h, then J packed), in double.
+__device__ inline double energy_direct(const double *hJ, int n, uint32_t z)
+{
+    double e = 0.0;
+    const double *J = hJ + n;
+#pragma unroll 1
+    for (int j = 0; j < n; ++j) {
+        double f = hJ[j];
+        for (int k = j + 1; k < n; ++k) {
+            const double x = *J++;
+            f += ((z >> k) & 1) ? -x : x;
+        }
+        e += ((z >> j) & 1) ? -f : f;
+    }
+    return e;
+}
+
+#define QW_AGENT __HIP_MEMORY_SCOPE_AGENT
+enum : int { RES_CNT = 0xfff, RES_EXIT = 1 << 12, RES_TRY = 1 << 28, RES_ABORT = 1 << 29, RES_GO = 1 << 30 };
+
+// Common start of W workgroups (one thread of each): true once all of them run.
+// From then on every wait between them ends, since none has to be placed any
+// more.  After `patience` looks the first one to lose patience decides for all,
+// by what the count was when it did.
+__device__ inline bool res_join(int *state, int W, int patience)
+{
+    int s = __hip_atomic_fetch_add(state, 1, __ATOMIC_RELAXED, QW_AGENT) + 1;
+    for (;;) {
+        if (s & RES_ABORT) return false;
+        if (s & RES_GO) return true;
+        if (!(s & RES_TRY)) {
+            if ((s & RES_CNT) == W) return true;
+            if (patience-- <= 0) {
+                const int old = __hip_atomic_fetch_or(state, (int)RES_TRY, __ATOMIC_RELAXED, QW_AGENT);
+                if (!(old & RES_TRY)) {
+                    const bool full = (old & RES_CNT) == W;
+                    (void)__hip_atomic_fetch_or(state, (int)(full ? RES_GO : RES_ABORT), __ATOMIC_RELAXED, QW_AGENT);
+                    return full;
+                }
+            }
+        }
+        s = __hip_atomic_load(state, __ATOMIC_RELAXED, QW_AGENT);
+    }
+}
+
+// The recurrence by one workgroup alone, from global memory: what the last
+// workgroup to leave does when the common start failed.
+template <typename R, int NT> __device__ __noinline__ void res_alone(ResArgs<R> a, const double *hJ)
+{
+    using C = typename Cplx<R>::T;
+    const uint32_t N = 1u << a.n;
+    C *b1 = a.X0, *b2 = a.X1;
+    const C cK = a.coef[a.K];
+#pragma unroll 1
+    for (uint32_t z = threadIdx.x; z < N; z += NT) {
+        const double E = a.diag ? (double)a.diag[z] : energy_direct(hJ, a.n, z);
+        a.d[z] = (R)((E - a.c) * a.inv_r);
+        const C p = a.psi[z];
+        b1[z] = C{fmad(cK.x, p.x, -(cK.y * p.y)), fmad(cK.x, p.y, cK.y * p.x)};
+        b2[z] = C{R(0), R(0)};
+    }
+    __syncthreads();
+    for (int k = a.K - 1; k >= 0; --k) {
+        const C ck = a.coef[k];
+        const R scale = (k == 0) ? R(1) : a.two;
+#pragma unroll 1
+        for (uint32_t z = threadIdx.x; z < N; z += NT) {
+            R sr = R(0), si = R(0);
+#pragma unroll 1
+            for (int j = 0; j < a.n; ++j) {
+                const C x = b1[z ^ (1u << j)];
+                sr += x.x;
+                si += x.y;
+            }
+            const C b = b1[z], s = b2[z], p = a.psi[z];
+            const R hr = fmad(a.d[z], b.x, a.g * sr), hi = fmad(a.d[z], b.y, a.g * si);
+            const R tr = fmad(scale, hr, -(a.sub * s.x)), ti = fmad(scale, hi, -(a.sub * s.y));
+            const C o{tr + fmad(ck.x, p.x, -(ck.y * p.y)), ti + fmad(ck.x, p.y, ck.y * p.x)};
+            if (k > 0) b2[z] = o;
+            else a.out[z] = C{fmad(a.pr, o.x, -(a.pi * o.y)), fmad(a.pr, o.y, a.pi * o.x)};
+        }
+        __syncthreads();
+        C *t = b1;
+        b1 = b2;
+        b2 = t;
+    }
+}
+
+// The vector of the lane that a DPP control names.
+template <typename R, int CTRL> __device__ __forceinline__ CVec<R> lane_flip(const CVec<R> &x)
+{
+    qw_i4 a = __builtin_bit_cast(qw_i4, x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = __builtin_amdgcn_update_dpp(0, a[i], CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(CVec<R>, a);
+}
+
+// One workgroup holds 2^T consecutive amplitudes of b_{k+1}, b_{k+2}, psi and the
+// diagonal in registers; tile w has the index bits T.. equal to w.  A term:
+//   - b_{k+1} goes to the workgroup's LDS tile and, for HC > 0, to one of two
+//     exchange buffers; each wave then raises its own flag to the round's number;
+//   - the flips of bit 0 (complex64) and of the bits that number a thread's own
+//     vectors come from its registers, those of three lane bits by DPP, the other
+//     lane bits and the wave bits from the LDS tile, while the flags travel;
+//   - a wave waits for the HC waves (one per flipped tile bit) that hold its
+//     flips, loads their vectors and forms b_k.
+// A wave overwrites a buffer only after the flags of the next round, which its
+// partners raise after they have read it, so two buffers and one barrier per
+// term (of the workgroup, for its LDS tile) suffice.
+// Every exchanged word passes the L1 (sc1 loads); stores go through to memory
+// unless all workgroups sit on one XCD, whose L2 they then share.
+// What bounds it: the latency of that round, not bytes: about 0.3 us for the
+// LDS tile alone, 0.9-1.4 us through one L2, 2.0 us over 128 workgroups on all
+// XCDs; from 18 qubits the exchanged bytes (8 partners of 8 B per amplitude:
+// 67 MB per term at 20 qubits, 9.5 TB/s).  The passes it replaces paid a launch
+// and a round trip of every vector per term (launch_resident lists both).
+template <typename R, int T, int NT, int HC, int WPE>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) k_resident(ResArgs<R> a)
+{
+    using C = typename Cplx<R>::T;
+    using V = CVec<R>;
+    constexpr int VE = V::N;                             // amplitudes per 16-byte vector
+    constexpr int PER = (1 << T) / (NT * VE);            // vectors per thread
+    constexpr int LT = (NT == 1024) ? 10 : (NT == 512) ? 9 : (NT == 256) ? 8 : (NT == 128) ? 7 : 6;
+    constexpr int QB = (PER == 8) ? 3 : (PER == 4) ? 2 : (PER == 2) ? 1 : 0;
+    static_assert((1 << LT) == NT && PER >= 1 && (1 << QB) == PER, "tile shape");
+    constexpr int W = 1 << HC, NW = NT / 64;
+    static_assert(W * NW <= RES_MAXFLAGS, "one flag per wave");
+    constexpr bool GUARD = (HC == 0 && NT == 64);        // the smallest shape also takes n < T
+    __shared__ V lds[2][PER * NT];
+    __shared__ double hJ[32 + 32 * 31 / 2];
+    __shared__ int go;
+
+    int w = 0;
+    if constexpr (HC > 0) {
+        if ((int)(blockIdx.x % a.stride) != a.sel) return;
+        w = __builtin_amdgcn_readfirstlane(blockIdx.x / a.stride);
+    }
+    const int tid = threadIdx.x;
+    const int n = a.n;
+    if (!a.diag)
+        for (int i = tid; i < n + n * (n - 1) / 2; i += NT) hJ[i] = a.hJ[i];
+    bool near = false;   // all workgroups on one XCD: its L2 is their common memory
+    if constexpr (HC > 0) {
+        if (tid == 0) {
+            const int xcc = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, 4 bits
+            (void)__hip_atomic_fetch_or(a.start + RES_LINE, 1 << xcc, __ATOMIC_RELAXED, QW_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            int ok = res_join(a.start, W, a.patience) ? 1 : 0;
+            if (ok) {
+                const int m = __hip_atomic_load(a.start + RES_LINE, __ATOMIC_RELAXED, QW_AGENT);
+                if ((m & (m - 1)) == 0) ok = 2;
+            } else {
+                const int old = __hip_atomic_fetch_add(a.start, (int)RES_EXIT, __ATOMIC_RELAXED, QW_AGENT);
+                if (((old >> 12) & RES_CNT) + 1 == W) ok = -1;   // the last one out
+            }
+            go = ok;
+        }
+        __syncthreads();
+        const int ok = __builtin_amdgcn_readfirstlane(go);
+        if (ok <= 0) {
+            if (ok < 0) res_alone<R, NT>(a, hJ);
+            return;
+        }
+        near = (ok == 2);
+    } else {
+        __syncthreads();
+    }
+
+    V b1[PER], b2[PER], ps[PER];
+    R d[PER][VE];
+    const int lane = tid & 63, wave = tid >> 6;
+    const uint32_t base = (uint32_t)w << T;
+    auto inside = [&](int q) { return !GUARD || (uint32_t)(q * NT + tid) * VE < (1u << n); };
+    C ck{R(0), R(0)};   // lane l: c_{64 i + l}
+    auto load_coef = [&](int k) {
+        const int i = (k & ~63) + lane;
+        if (i <= a.K) ck = a.coef[i];
+    };
+    auto lane_value = [&](R x, int l) -> R {
+        if constexpr (sizeof(R) == 4) {
+            return __builtin_bit_cast(R, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
+        } else {
+            const uint64_t u = __builtin_bit_cast(uint64_t, x);
+            const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, l);
+            const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+            return __builtin_bit_cast(R, ((uint64_t)hi << 32) | lo);
+        }
+    };
+    load_coef(a.K);
+    const R cKr = lane_value(ck.x, a.K & 63), cKi = lane_value(ck.y, a.K & 63);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+#pragma unroll
+        for (int v = 0; v < VE; ++v) {
+            ps[q].v[v] = C{R(0), R(0)};
+            b2[q].v[v] = C{R(0), R(0)};
+            d[q][v] = R(0);
+        }
+        if (inside(q)) {
+            const uint32_t z = base + (uint32_t)(q * NT + tid) * VE;
+            ps[q] = ld_v<R, false>(a.psi + z);
+#pragma unroll
+            for (int v = 0; v < VE; ++v) {
+                const double E = a.diag ? (double)a.diag[z + v] : energy_direct(hJ, n, z + v);
+                d[q][v] = (R)((E - a.c) * a.inv_r);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < VE; ++v) {
+            const C p = ps[q].v[v];
+            b1[q].v[v] = C{fmad(cKr, p.x, -(cKi * p.y)), fmad(cKr, p.y, cKi * p.x)};
+        }
+    }
+
+    const auto rs0 = __builtin_amdgcn_make_buffer_rsrc((void *)a.X0, 0, (int)(sizeof(C) << n), 0x00027000);
+    const auto rs1 = __builtin_amdgcn_make_buffer_rsrc((void *)a.X1, 0, (int)(sizeof(C) << n), 0x00027000);
+    constexpr int SC1 = 16;   // cache policy: past the L1, and (stores) through to memory
+    // lane j < HC looks at the flag of the wave that holds the flips of tile bit T + j
+    const int *peer = a.flags + (size_t)(((w ^ (lane < HC ? 1 << lane : 0)) * NW + wave) * RES_LINE);
+    int *mine = a.flags + (size_t)((w * NW + wave) * RES_LINE);
+    bool lost = false;
+    int t = 0;
+
+    auto publish = [&]() {   // b1 to the LDS tile and the exchange buffer of this round
+        ++t;
+        if constexpr (HC > 0) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const qw_i4 x = __builtin_bit_cast(qw_i4, b1[q]);
+                const int vo = (q * NT + tid) * 16, so = (int)(base * sizeof(C));
+                if (near) __builtin_amdgcn_raw_buffer_store_b128(x, (t & 1) ? rs1 : rs0, vo, so, 0);
+                else __builtin_amdgcn_raw_buffer_store_b128(x, (t & 1) ? rs1 : rs0, vo, so, SC1);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) lds[t & 1][q * NT + tid] = b1[q];
+        if constexpr (HC > 0) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the wave's part has arrived
+            if (lane == 0) __hip_atomic_store(mine, t, __ATOMIC_RELAXED, QW_AGENT);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    publish();
+
+    for (int k = a.K - 1; k >= 0; --k) {
+        if ((k & 63) == 63) load_coef(k);
+        const R cr = lane_value(ck.x, k & 63), ci = lane_value(ck.y, k & 63);
+        const R scale = (k == 0) ? R(1) : a.two;
+        R sr[PER][VE], si[PER][VE];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if constexpr (VE == 2) {
+                sr[q][0] = b1[q].v[1].x;
+                si[q][0] = b1[q].v[1].y;
+                sr[q][VE - 1] = b1[q].v[0].x;
+                si[q][VE - 1] = b1[q].v[0].y;
+            } else {
+                sr[q][0] = R(0);
+                si[q][0] = R(0);
+            }
+            auto add = [&](const V &x) {
+#pragma unroll
+                for (int v = 0; v < VE; ++v) {
+                    sr[q][v] += x.v[v].x;
+                    si[q][v] += x.v[v].y;
+                }
+            };
+#pragma unroll
+            for (int j = 0; j < QB; ++j) add(b1[q ^ (1 << j)]);
+            // lane bits 0, 1 and 3 within the row (DPP), the others from the LDS tile
+            add(lane_flip<R, 0xb1>(b1[q]));    // quad_perm 1 0 3 2
+            add(lane_flip<R, 0x4e>(b1[q]));    // quad_perm 2 3 0 1
+            add(lane_flip<R, 0x128>(b1[q]));   // row_ror 8
+#pragma unroll
+            for (int j = 2; j < LT; ++j)
+                if (j != 3) add(lds[t & 1][(q * NT + tid) ^ (1 << j)]);
+        }
+        if constexpr (HC > 0) {
+            if (!lost) {
+                int left = RES_POLLS;
+                while (__any(lane < HC && __hip_atomic_load(peer, __ATOMIC_RELAXED, QW_AGENT) < t))
+                    if (--left == 0) { lost = true; break; }
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                V x[HC > 0 ? HC : 1];
+#pragma unroll
+                for (int j = 0; j < HC; ++j) {
+                    // partner's tile in the scalar offset: one vector offset for all of them
+                    const int so = (int)((((uint32_t)w ^ (1u << j)) << T) * sizeof(C));
+                    const qw_i4 y = __builtin_amdgcn_raw_buffer_load_b128((t & 1) ? rs1 : rs0, (q * NT + tid) * 16,
+                                                                          so, SC1);
+                    x[j] = __builtin_bit_cast(V, y);
+                }
+#pragma unroll
+                for (int j = 0; j < HC; ++j)
+#pragma unroll
+                    for (int v = 0; v < VE; ++v) {
+                        sr[q][v] += x[j].v[v].x;
+                        si[q][v] += x[j].v[v].y;
+                    }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+#pragma unroll
+            for (int v = 0; v < VE; ++v) {
+                const C b = b1[q].v[v], s = b2[q].v[v], p = ps[q].v[v];
+                const R hr = fmad(d[q][v], b.x, a.g * sr[q][v]), hi = fmad(d[q][v], b.y, a.g * si[q][v]);
+                const R tr = fmad(scale, hr, -(a.sub * s.x)), ti = fmad(scale, hi, -(a.sub * s.y));
+                b2[q].v[v] = C{tr + fmad(cr, p.x, -(ci * p.y)), ti + fmad(cr, p.y, ci * p.x)};
+            }
+        // b2 holds b_k: the two swap roles; amplitudes beyond n stay zero
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (!inside(q))
+#pragma unroll
+                for (int v = 0; v < VE; ++v) b2[q].v[v] = C{R(0), R(0)};
+            const V x = b1[q];
+            b1[q] = b2[q];
+            b2[q] = x;
+        }
+        if (k > 0) publish();
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if (!inside(q)) continue;
+        V o;
+#pragma unroll
+        for (int v = 0; v < VE; ++v) {
+            const C y = b1[q].v[v];
+            o.v[v] = C{fmad(a.pr, y.x, -(a.pi * y.y)), fmad(a.pr, y.y, a.pi * y.x)};
+            if (lost) o.v[v] = C{R(NAN), R(NAN)};   // a wave that all were waiting for is gone
+        }
+        st_v<R, false>(a.out + base + (uint32_t)(q * NT + tid) * VE, o);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Host side
+// ---------------------------------------------------------------------------
+
+// Sizes that run in one launch.  Above them the passes are faster: complex64 21
+// qubits would take 2^13 amplitudes per workgroup, more than its registers hold
+// (41 us per term with the spills, 17 in passes); complex128 20 likewise.
+template <typename R> constexpr int resident_nmax() { return sizeof(R) == 4 ? 20 : 19; }
+
+template <typename R, int T, int NT, int HC, int STRIDE, int WPE, bool COOP>
+static hipError_t res_launch(ResArgs<R> a, hipStream_t s)
+{
+    // launches take turns over the XCDs, so that calls on several streams do not
+    // crowd one
+    static std::atomic<unsigned> turn{0};
+    a.stride = STRIDE;
+    a.sel = (STRIDE > 1) ? (int)(turn.fetch_add(1, std::memory_order_relaxed) % STRIDE) : 0;
+    const dim3 grid((1u << HC) * STRIDE), block(NT);
+    if constexpr (COOP) {
+        void *args[] = {&a};
+        return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(&k_resident<R, T, NT, HC, WPE>), grid, block,
+                                          args, 0, s);
+    } else {
+        hipLaunchKernelGGL((k_resident<R, T, NT, HC, WPE>), grid, block, 0, s, a);
+        return hipGetLastError();
+    }
+}
+
+// Whether the size's shape needs a cooperative launch: one workgroup fills a CU,
+// so two such calls on two streams could each hold half the chip and wait for
+// the other half.  The other shapes of several workgroups have at most 256
+// threads of at most 128 registers, four to a CU, and a process has four
+// hardware queues.  (Shapes of 512 and 1024 threads with more registers were up
+// to 15 % faster per term, but four threads calling at once then met failed
+// starts.)  A cooperative launch costs 8 us more than a plain one.
+template <typename R> constexpr bool resident_coop(int n) { return n >= (sizeof(R) == 4 ? 19 : 18); }
+
+// Tile, threads, workgroups and spread per size, the fastest of a sweep that
+// keeps to that (microseconds per term in the comments; in parentheses what the
+// passes, or up to 13 / 12 qubits the former one-workgroup kernel, took).  One
+// workgroup while the exchange would cost more than the shorter term saves;
+// then 2^HC workgroups on one XCD, where a round of stores, flags and loads
+// takes 0.9-1.4 us through its L2; from 16 / 15 qubits workgroups on all XCDs,
+// where it takes 2.0 us and more, since 32 CUs would spend longer on a term
+// (17 qubits: 5.2 us).
+template <typename R> static hipError_t launch_resident(const ResArgs<R> &a, hipStream_t s)
+{
+    if constexpr (sizeof(R) == 4) {
+        switch (a.n) {
+        case 8: return res_launch<R, 8, 128, 0, 1, 1, false>(a, s);       // 0.31 (1.2)
+        case 9: return res_launch<R, 9, 256, 0, 1, 1, false>(a, s);       // 0.36 (1.2)
+        case 10: return res_launch<R, 10, 512, 0, 1, 1, false>(a, s);     // 0.45 (1.3)
+        case 11: return res_launch<R, 11, 1024, 0, 1, 1, false>(a, s);    // 0.78 (1.9)
+        case 12: return res_launch<R, 8, 128, 4, 8, 1, false>(a, s);      // 0.91 (3.1)
+        case 13: return res_launch<R, 8, 128, 5, 8, 1, false>(a, s);      // 1.03 (5.6)
+        case 14: return res_launch<R, 9, 256, 5, 8, 1, false>(a, s);      // 1.25 (5.8)
+        case 15: return res_launch<R, 10, 256, 5, 8, 4, false>(a, s);     // 1.57 (5.8)
+        case 16: return res_launch<R, 9, 256, 7, 1, 4, false>(a, s);      // 2.12 (6.3)
+        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s);      // 2.60 (6.6)
+        case 18: return res_launch<R, 10, 256, 8, 1, 4, false>(a, s);     // 3.78 (7.6)
+        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s);      // 5.56 (9.7)
+        case 20: return res_launch<R, 12, 512, 8, 1, 1, true>(a, s);      // 7.09 (9.6)
+        default: return res_launch<R, 7, 64, 0, 1, 1, false>(a, s);       // 0.29 (1.2)
+        }
+    } else {
+        switch (a.n) {
+        case 7: return res_launch<R, 7, 128, 0, 1, 1, false>(a, s);       // 0.31 (1.1)
+        case 8: return res_launch<R, 8, 256, 0, 1, 1, false>(a, s);       // 0.31 (1.1)
+        case 9: return res_launch<R, 9, 512, 0, 1, 1, false>(a, s);       // 0.44 (1.2)
+        case 10: return res_launch<R, 10, 1024, 0, 1, 1, false>(a, s);    // 0.70 (1.3)
+        case 11: return res_launch<R, 8, 256, 3, 8, 1, false>(a, s);      // 0.79 (2.0)
+        case 12: return res_launch<R, 7, 128, 5, 8, 1, false>(a, s);      // 0.90 (3.4)
+        case 13: return res_launch<R, 8, 256, 5, 8, 1, false>(a, s);      // 1.11 (7.8)
+        case 14: return res_launch<R, 9, 256, 5, 8, 4, false>(a, s);      // 1.42 (8.1)
+        case 15: return res_launch<R, 8, 256, 7, 1, 4, false>(a, s);      // 2.01 (8.6)
+        case 16: return res_launch<R, 8, 256, 8, 1, 4, false>(a, s);      // 2.52 (9.1)
+        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s);      // 3.60 (10.3)
+        case 18: return res_launch<R, 10, 1024, 8, 1, 1, true>(a, s);     // 5.43 (12.3)
+        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s);      // 6.55 (13.0)
+        default: return res_launch<R, 6, 64, 0, 1, 1, false>(a, s);       // 0.25 (1.1)
+        }
+    }
+}
+
+}  // namespace qw
