@@ -114,36 +114,53 @@ static WsLayout ws_layout(int n, int prec, bool otf)
 }
 
 
-// Small host arrays travel as kernel arguments (a launch keeps its own copy, so
-// nothing on the host has to outlive the call and no copy engine is involved).
-struct PutBlob {
-    static constexpr int WORDS = 440;   // arguments stay below 4 KB
-    uint64_t v[WORDS];
-};
-
+// Copies count words to dst and count2 words to dst2, and clears the first word
+// of nlines lines and of the two lines at `two`.
 template <int D = 0>
-__global__ void __launch_bounds__(256) k_put(PutBlob b, int count, uint64_t *dst, int *lines, int nlines,
-                                             int *two)
+__global__ void __launch_bounds__(256) k_put(PutBlob b, int count, uint64_t *dst, int count2, uint64_t *dst2,
+                                             int *lines, int nlines, int *two)
 {
-    for (int i = threadIdx.x; i < count; i += 256) dst[i] = b.v[i];
+    for (int i = threadIdx.x; i < count + count2; i += 256) {
+        if (i < count) dst[i] = b.v[i];
+        else dst2[i - count] = b.v[i];
+    }
     for (int i = threadIdx.x; i < nlines; i += 256) lines[i * RES_LINE] = 0;
     if (nlines > 0 && threadIdx.x < 2) two[threadIdx.x * RES_LINE] = 0;
 }
 
-// Copies `count` 8-byte words to dst; the last launch also clears the first
-// word of nlines lines and of the two lines at `two`.
-static qw_status put(const void *src, size_t count, void *dst, hipStream_t s, int *lines = nullptr, int nlines = 0,
-                     int *two = nullptr)
+// The same from host arrays, in as many launches as it takes.
+static qw_status put(const void *src, size_t count, void *dst, hipStream_t s, const void *src2 = nullptr,
+                     size_t count2 = 0, void *dst2 = nullptr, int *lines = nullptr, int nlines = 0, int *two = nullptr)
 {
     PutBlob b;
-    for (size_t off = 0; off < count; off += PutBlob::WORDS) {
-        const size_t m = std::min<size_t>(PutBlob::WORDS, count - off);
-        std::memcpy(b.v, static_cast<const uint64_t *>(src) + off, m * sizeof(uint64_t));
-        hipLaunchKernelGGL(k_put<0>, dim3(1), dim3(256), 0, s, b, (int)m, static_cast<uint64_t *>(dst) + off, lines,
-                           off + m == count ? nlines : 0, two);
+    for (size_t off = 0; off < count + count2;) {
+        const size_t m = (off < count) ? std::min<size_t>(PutBlob::WORDS, count - off) : 0;
+        const size_t off2 = off + m - count;   // used once the first array is through
+        const size_t m2 = (off + m < count) ? 0 : std::min<size_t>(PutBlob::WORDS - m, count2 - off2);
+        if (m) std::memcpy(b.v, static_cast<const uint64_t *>(src) + off, m * sizeof(uint64_t));
+        if (m2) std::memcpy(b.v + m, static_cast<const uint64_t *>(src2) + off2, m2 * sizeof(uint64_t));
+        const bool last = off + m + m2 == count + count2;
+        hipLaunchKernelGGL(k_put<0>, dim3(1), dim3(256), 0, s, b, (int)m, static_cast<uint64_t *>(dst) + off, (int)m2,
+                           m2 ? static_cast<uint64_t *>(dst2) + off2 : nullptr, lines, last ? nlines : 0, two);
+        off += m + m2;
     }
     QW_HIP(hipGetLastError());
     return QW_OK;
+}
+
+// (h, J) in one array, as the device tables hold them.
+static std::vector<double> packed_couplings(int n, const double *h, const double *J)
+{
+    std::vector<double> hj(h, h + n);
+    if (n > 1) hj.insert(hj.end(), J, J + n * (n - 1) / 2);
+    return hj;
+}
+
+// The tables view of couplings that are (or will be) in the workspace.
+static EnergyTables tables_view(int n, char *ws, const WsLayout &L)
+{
+    double *dhj = reinterpret_cast<double *>(ws + L.hj);
+    return EnergyTables{dhj, dhj + n, reinterpret_cast<double *>(ws + L.q), n, std::min(n, LB_TAB)};
 }
 
 // Puts (h, J) into the workspace; returns the tables view, whose pair table is
@@ -151,17 +168,9 @@ static qw_status put(const void *src, size_t count, void *dst, hipStream_t s, in
 static qw_status upload_couplings(int n, const double *h, const double *J, char *ws, const WsLayout &L, hipStream_t s,
                                   EnergyTables *T)
 {
-    const int np = n * (n - 1) / 2;
-    std::vector<double> hj(n + np);
-    std::memcpy(hj.data(), h, n * sizeof(double));
-    if (np) std::memcpy(hj.data() + n, J, np * sizeof(double));
-    double *dhj = reinterpret_cast<double *>(ws + L.hj);
-    T->h = dhj;
-    T->J = dhj + n;
-    T->Q = reinterpret_cast<double *>(ws + L.q);
-    T->n = n;
-    T->LB = std::min(n, LB_TAB);
-    return put(hj.data(), hj.size(), dhj, s);
+    *T = tables_view(n, ws, L);
+    const std::vector<double> hj = packed_couplings(n, h, J);
+    return put(hj.data(), hj.size(), const_cast<double *>(T->h), s);
 }
 
 static qw_status build_qtable(const EnergyTables &T, hipStream_t s)
@@ -172,17 +181,18 @@ static qw_status build_qtable(const EnergyTables &T, hipStream_t s)
     return QW_OK;
 }
 
-// Min / max of E over all z by direct sums, for the sizes that run in one
-// launch and build no pair table.  256 threads.
+// Min / max of E over all z for the sizes that run in one launch and build no
+// pair table: one block per tile of 2^RANGE_T states.  (14 qubits and more.)
+static constexpr int RANGE_T = 10;
 template <int D = 0>
-__global__ void __launch_bounds__(256) k_minmax_direct(const double *hJ, int n, double *part)
+__global__ void __launch_bounds__(256) k_minmax_tile(const double *hJ, int n, double *part)
 {
-    __shared__ double c[32 + 32 * 31 / 2];
-    for (int i = threadIdx.x; i < n + n * (n - 1) / 2; i += 256) c[i] = hJ[i];
-    __syncthreads();
+    __shared__ TileEnergy<RANGE_T> en;
+    en.build<256>(hJ, n, blockIdx.x);
     double mn = INFINITY, mx = -INFINITY;
-    for (uint32_t z = blockIdx.x * 256 + threadIdx.x; z < (1u << n); z += gridDim.x * 256) {
-        const double e = energy_direct(c, n, z);
+#pragma unroll
+    for (int q = 0; q < (1 << RANGE_T) / 256; ++q) {
+        const double e = en.at(n, q * 256 + threadIdx.x);
         mn = fmin(mn, e);
         mx = fmax(mx, e);
     }
@@ -237,8 +247,9 @@ static qw_status minmax(int n, const R *diag, const EnergyTables *T, char *ws, c
         np = grid_for(N, 256 * 16, MAXPART);
         hipLaunchKernelGGL(k_minmax_diag<R>, dim3(np), dim3(256), 0, s, diag, N, part);
     } else if (direct) {
-        np = grid_for(uint64_t(1) << n, 256 * 4, MAXPART);
-        hipLaunchKernelGGL(k_minmax_direct<0>, dim3(np), dim3(256), 0, s, T->h, n, part);
+        static_assert(HOST_RANGE_NMAX >= RANGE_T, "whole tiles");
+        np = 1 << (n - RANGE_T);
+        hipLaunchKernelGGL(k_minmax_tile<0>, dim3(np), dim3(256), 0, s, T->h, n, part);
     } else {
         const uint64_t ntiles = uint64_t(1) << (n - T->LB);
         np = grid_for(ntiles, 1, MAXPART);
@@ -282,18 +293,25 @@ static qw_status validate(int n, const R *diag, const double *h, const double *J
 }
 
 // Couplings on the device and the range of E.  `resident`: for a call that runs
-// in one launch, without the pair table.
+// in one launch, without the pair table; if it also takes the couplings along
+// (`later`) and the range comes from the host, they are not uploaded here.
 template <typename R>
 static qw_status energy_range(int n, const R *diag, const double *h, const double *J, bool resident, char *ws,
-                              const WsLayout &L, hipStream_t s, EnergyTables *T, double *emin, double *emax)
+                              const WsLayout &L, hipStream_t s, EnergyTables *T, double *emin, double *emax,
+                              bool *later = nullptr)
 {
     if (diag) return minmax<R>(n, diag, T, ws, L, s, emin, emax);
-    qw_status st = upload_couplings(n, h, J, ws, L, s, T);
-    if (st != QW_OK) return st;
     if (resident && n <= HOST_RANGE_NMAX) {
         host_energy_range(n, h, J, emin, emax);
-        return QW_OK;
+        *T = tables_view(n, ws, L);
+        if (later) {
+            *later = true;
+            return QW_OK;
+        }
+        return upload_couplings(n, h, J, ws, L, s, T);
     }
+    qw_status st = upload_couplings(n, h, J, ws, L, s, T);
+    if (st != QW_OK) return st;
     if (!resident && (st = build_qtable(*T, s)) != QW_OK) return st;
     return minmax<R>(n, nullptr, T, ws, L, s, emin, emax, resident);
 }
@@ -303,10 +321,10 @@ static qw_status energy_range(int n, const R *diag, const double *h, const doubl
 template <typename R>
 static qw_status bound_impl(int n, const R *diag, const double *h, const double *J, double gamma, bool resident,
                             char *ws, const WsLayout &L, hipStream_t s, EnergyTables *T,
-                            double *c, double *r)
+                            double *c, double *r, bool *later = nullptr)
 {
     double emin, emax;
-    qw_status st = energy_range<R>(n, diag, h, J, resident, ws, L, s, T, &emin, &emax);
+    qw_status st = energy_range<R>(n, diag, h, J, resident, ws, L, s, T, &emin, &emax, later);
     if (st != QW_OK) return st;
     if (!finite(emin) || !finite(emax)) { set_error("diagonal has non-finite entries"); return QW_EINVAL; }
     *c = 0.5 * (emax + emin);
@@ -531,6 +549,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         resident = cap == hipStreamCaptureStatusNone;
     }
     bool have_q = !resident;   // pair table built
+    bool later = false;        // the couplings are still to be uploaded
     if (given_cr) {
         c = given_cr[0];
         r = given_cr[1];
@@ -540,13 +559,15 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
                 T = prep->T;
                 have_q = prep->have_q;
             } else {
-                st = upload_couplings(n, h, J, ws, L, s, &T);
+                T = tables_view(n, ws, L);
+                later = resident;
+                if (!later) st = upload_couplings(n, h, J, ws, L, s, &T);
                 if (st == QW_OK && have_q) st = build_qtable(T, s);
                 if (st != QW_OK) return st;
             }
         }
     } else {
-        st = bound_impl<R>(n, diag, h, J, gamma, resident, ws, L, s, &T, &c, &r);
+        st = bound_impl<R>(n, diag, h, J, gamma, resident, ws, L, s, &T, &c, &r, &later);
         if (st != QW_OK) return st;
     }
 
@@ -688,13 +709,26 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         ra.patience = t_patience;
         C *dcoef = reinterpret_cast<C *>(ws + (own_coef ? L.coef : L.qt));
         ra.coef = dcoef;
-        st = put(ch.data(), ch.size() * sizeof(C) / sizeof(uint64_t), dcoef, s, ra.flags, RES_MAXFLAGS, ra.start);
-        if (st != QW_OK) return st;
+        const std::vector<double> hj = later ? packed_couplings(n, h, J) : std::vector<double>();
+        const size_t wc = ch.size() * sizeof(C) / sizeof(uint64_t), wh = hj.size();
+        // one workgroup: both arrays with its launch if they fit (10 qubits in
+        // complex128, t = 1: 38 -> 33 us a call against an upload of its own)
+        const bool carry = resident_single<R>(n) && (later || diag) && wc + wh <= PutBlob::WORDS;
+        PutBlob blob;
+        if (carry) {
+            std::memcpy(blob.v, ch.data(), wc * sizeof(uint64_t));
+            if (wh) std::memcpy(blob.v + wc, hj.data(), wh * sizeof(uint64_t));
+        } else {
+            st = put(ch.data(), wc, dcoef, s, hj.data(), wh, const_cast<double *>(T.h), ra.flags, RES_MAXFLAGS,
+                     ra.start);
+            if (st != QW_OK) return st;
+        }
         timer.mark(1);
-        QW_HIP(launch_resident<R>(ra, s));
+        QW_HIP(launch_resident<R>(ra, s, carry ? &blob : nullptr));
         return timer.finish(info);
     }
 
+    if (later && (st = upload_couplings(n, h, J, ws, L, s, &T)) != QW_OK) return st;
     if (!otf && plan_reads_diag(plan)) {
         if (diag) {
             hipLaunchKernelGGL(k_normalize_diag<R>, dim3(grid_for(N, 256 * 8, 1 << 16)), dim3(256), 0, s,

@@ -8,6 +8,7 @@
 #include "qw_kernels.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace qw {
 
@@ -21,6 +22,14 @@ static constexpr int RES_LINE = 32;            // 4-byte words per line
 static constexpr int RES_MAXFLAGS = 4096;
 static constexpr int RES_PATIENCE = 1 << 17;   // looks at the start word, some 0.1 s
 static constexpr int RES_POLLS = 1 << 24;      // looks at a flag, seconds
+
+// Small host arrays travel as kernel arguments (a launch keeps its own copy, so
+// nothing on the host has to outlive the call and no copy engine is involved).
+struct PutBlob {
+    static constexpr int WORDS = 440;   // 8-byte words; arguments stay below 4 KB
+    uint64_t v[WORDS];
+};
+struct NoBlob {};
 
 template <typename R> struct ResArgs {
     using C = typename Cplx<R>::T;
@@ -56,6 +65,71 @@ __device__ inline double energy_direct(const double *hJ, int n, uint32_t z)
     }
     return e;
 }
+
+// Energies of a tile of 2^min(n, T) consecutive states, in double.  The tile's
+// bits split into a low and a high half,
+//   E = A[lo] + B[hi] + sum_{j in low half} s_j G_j[hi],
+// where A holds the low half's couplings and fields and the constant of the bits
+// above the tile, B the high half's, G_j the couplings of bit j to the high
+// half; a state then costs 2 + T / 2 LDS reads instead of the n (n + 1) / 2
+// couplings (over 32 us at 17 qubits, all latency; the tables take 2 us).
+template <int T> struct TileEnergy {
+    static constexpr int HA = T / 2, HB = T - T / 2;
+    double hJ[32 + 32 * 31 / 2];
+    double F[T], C, A[1 << HA], B[1 << HB], G[HA > 0 ? HA : 1][1 << HB];
+
+    // All NT threads of the block; ends with the tables visible to them.
+    template <int NT> __device__ void build(const double *dhJ, int n, uint32_t w)
+    {
+        const int tid = threadIdx.x;
+        for (int i = tid; i < n + n * (n - 1) / 2; i += NT) hJ[i] = dhJ[i];
+        __syncthreads();
+        const int nt = n < T ? n : T, a = nt / 2, b = nt - a;
+        const double *J = hJ + n;
+        auto flip = [](uint32_t z, int k, double x) { return ((z >> k) & 1) ? -x : x; };
+        if (tid < nt) {
+            double f = hJ[tid];
+            for (int k = nt; k < n; ++k) f += flip(w, k - nt, J[pair_off(n, tid, k)]);
+            F[tid] = f;
+        } else if (tid == NT - 1) {
+            double c = 0.0;
+            for (int j = nt; j < n; ++j) {
+                double f = hJ[j];
+                for (int k = j + 1; k < n; ++k) f += flip(w, k - nt, J[pair_off(n, j, k)]);
+                c += flip(w, j - nt, f);
+            }
+            C = c;
+        }
+        __syncthreads();
+        for (int i = tid; i < (1 << a) + (1 << b); i += NT) {
+            const bool hi = i >= (1 << a);
+            const int z = hi ? i - (1 << a) : i, o = hi ? a : 0, m = hi ? b : a;
+            double e = hi ? 0.0 : C;
+            for (int j = 0; j < m; ++j) {
+                double f = F[o + j];
+                for (int k = j + 1; k < m; ++k) f += flip(z, k, J[pair_off(n, o + j, o + k)]);
+                e += flip(z, j, f);
+            }
+            if (hi) B[z] = e;
+            else A[z] = e;
+        }
+        for (int i = tid; i < (a << b); i += NT) {
+            const int j = i >> b, z = i & ((1 << b) - 1);
+            double g = 0.0;
+            for (int k = 0; k < b; ++k) g += flip(z, k, J[pair_off(n, j, a + k)]);
+            G[j][z] = g;
+        }
+        __syncthreads();
+    }
+    __device__ double at(int n, uint32_t e) const
+    {
+        const int a = (n < T ? n : T) / 2;
+        const uint32_t lo = e & ((1u << a) - 1), hi = e >> a;
+        double x = A[lo] + B[hi];
+        for (int j = 0; j < a; ++j) x += ((lo >> j) & 1) ? -G[j][hi] : G[j][hi];
+        return x;
+    }
+};
 
 #define QW_AGENT __HIP_MEMORY_SCOPE_AGENT
 enum : int { RES_CNT = 0xfff, RES_EXIT = 1 << 12, RES_TRY = 1 << 28, RES_ABORT = 1 << 29, RES_GO = 1 << 30 };
@@ -156,8 +230,10 @@ template <typename R, int CTRL> __device__ __forceinline__ CVec<R> lane_flip(con
 // XCDs; from 18 qubits the exchanged bytes (8 partners of 8 B per amplitude:
 // 67 MB per term at 20 qubits, 9.5 TB/s).  The passes it replaces paid a launch
 // and a round trip of every vector per term (launch_resident lists both).
-template <typename R, int T, int NT, int HC, int WPE>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) k_resident(ResArgs<R> a)
+// BLOB = PutBlob (one workgroup): the coefficients and, behind them, (h, J) come
+// with the launch.
+template <typename R, int T, int NT, int HC, int WPE, typename BLOB = NoBlob>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) k_resident(ResArgs<R> a, BLOB blob)
 {
     using C = typename Cplx<R>::T;
     using V = CVec<R>;
@@ -170,7 +246,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
     static_assert(W * NW <= RES_MAXFLAGS, "one flag per wave");
     constexpr bool GUARD = (HC == 0 && NT == 64);        // the smallest shape also takes n < T
     __shared__ V lds[2][PER * NT];
-    __shared__ double hJ[32 + 32 * 31 / 2];
+    __shared__ TileEnergy<T> en;
     __shared__ int go;
 
     int w = 0;
@@ -180,8 +256,18 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
     }
     const int tid = threadIdx.x;
     const int n = a.n;
-    if (!a.diag)
-        for (int i = tid; i < n + n * (n - 1) / 2; i += NT) hJ[i] = a.hJ[i];
+    constexpr bool INLINE = std::is_same<BLOB, PutBlob>::value;
+    static_assert(!INLINE || HC == 0, "one workgroup");
+    __shared__ uint64_t words[INLINE ? PutBlob::WORDS : 1];
+    const C *coef = a.coef;
+    const double *hJ = a.hJ;
+    if constexpr (INLINE) {
+        for (int i = tid; i < PutBlob::WORDS; i += NT) words[i] = blob.v[i];
+        coef = reinterpret_cast<const C *>(words);
+        hJ = reinterpret_cast<const double *>(coef + a.K + 1);
+        __syncthreads();
+    }
+    if (!a.diag) en.template build<NT>(hJ, n, w);
     bool near = false;   // all workgroups on one XCD: its L2 is their common memory
     if constexpr (HC > 0) {
         if (tid == 0) {
@@ -201,12 +287,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
         __syncthreads();
         const int ok = __builtin_amdgcn_readfirstlane(go);
         if (ok <= 0) {
-            if (ok < 0) res_alone<R, NT>(a, hJ);
+            if (ok < 0) res_alone<R, NT>(a, en.hJ);
             return;
         }
         near = (ok == 2);
-    } else {
-        __syncthreads();
     }
 
     V b1[PER], b2[PER], ps[PER];
@@ -217,7 +301,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
     C ck{R(0), R(0)};   // lane l: c_{64 i + l}
     auto load_coef = [&](int k) {
         const int i = (k & ~63) + lane;
-        if (i <= a.K) ck = a.coef[i];
+        if (i <= a.K) ck = coef[i];
     };
     auto lane_value = [&](R x, int l) -> R {
         if constexpr (sizeof(R) == 4) {
@@ -244,7 +328,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
             ps[q] = ld_v<R, false>(a.psi + z);
 #pragma unroll
             for (int v = 0; v < VE; ++v) {
-                const double E = a.diag ? (double)a.diag[z + v] : energy_direct(hJ, n, z + v);
+                const double E = a.diag ? (double)a.diag[z + v] : en.at(n, z + v - base);
                 d[q][v] = (R)((E - a.c) * a.inv_r);
             }
         }
@@ -390,7 +474,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
 template <typename R> constexpr int resident_nmax() { return sizeof(R) == 4 ? 20 : 19; }
 
 template <typename R, int T, int NT, int HC, int STRIDE, int WPE, bool COOP>
-static hipError_t res_launch(ResArgs<R> a, hipStream_t s)
+static hipError_t res_launch(ResArgs<R> a, hipStream_t s, const PutBlob *blob)
 {
     // launches take turns over the XCDs, so that calls on several streams do not
     // crowd one
@@ -398,12 +482,19 @@ static hipError_t res_launch(ResArgs<R> a, hipStream_t s)
     a.stride = STRIDE;
     a.sel = (STRIDE > 1) ? (int)(turn.fetch_add(1, std::memory_order_relaxed) % STRIDE) : 0;
     const dim3 grid((1u << HC) * STRIDE), block(NT);
+    if constexpr (HC == 0) {
+        if (blob) {
+            hipLaunchKernelGGL((k_resident<R, T, NT, HC, WPE, PutBlob>), grid, block, 0, s, a, *blob);
+            return hipGetLastError();
+        }
+    }
     if constexpr (COOP) {
-        void *args[] = {&a};
+        NoBlob none;
+        void *args[] = {&a, &none};
         return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(&k_resident<R, T, NT, HC, WPE>), grid, block,
                                           args, 0, s);
     } else {
-        hipLaunchKernelGGL((k_resident<R, T, NT, HC, WPE>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_resident<R, T, NT, HC, WPE>), grid, block, 0, s, a, NoBlob{});
         return hipGetLastError();
     }
 }
@@ -417,6 +508,9 @@ static hipError_t res_launch(ResArgs<R> a, hipStream_t s)
 // starts.)  A cooperative launch costs 8 us more than a plain one.
 template <typename R> constexpr bool resident_coop(int n) { return n >= (sizeof(R) == 4 ? 19 : 18); }
 
+// Sizes of one workgroup, whose launch can carry coefficients and couplings.
+template <typename R> constexpr bool resident_single(int n) { return n <= (sizeof(R) == 4 ? 11 : 10); }
+
 // Tile, threads, workgroups and spread per size, the fastest of a sweep that
 // keeps to that (microseconds per term in the comments; in parentheses what the
 // passes, or up to 13 / 12 qubits the former one-workgroup kernel, took).  One
@@ -425,41 +519,42 @@ template <typename R> constexpr bool resident_coop(int n) { return n >= (sizeof(
 // takes 0.9-1.4 us through its L2; from 16 / 15 qubits workgroups on all XCDs,
 // where it takes 2.0 us and more, since 32 CUs would spend longer on a term
 // (17 qubits: 5.2 us).
-template <typename R> static hipError_t launch_resident(const ResArgs<R> &a, hipStream_t s)
+template <typename R>
+static hipError_t launch_resident(const ResArgs<R> &a, hipStream_t s, const PutBlob *blob)
 {
     if constexpr (sizeof(R) == 4) {
         switch (a.n) {
-        case 8: return res_launch<R, 8, 128, 0, 1, 1, false>(a, s);       // 0.31 (1.2)
-        case 9: return res_launch<R, 9, 256, 0, 1, 1, false>(a, s);       // 0.36 (1.2)
-        case 10: return res_launch<R, 10, 512, 0, 1, 1, false>(a, s);     // 0.45 (1.3)
-        case 11: return res_launch<R, 11, 1024, 0, 1, 1, false>(a, s);    // 0.78 (1.9)
-        case 12: return res_launch<R, 8, 128, 4, 8, 1, false>(a, s);      // 0.91 (3.1)
-        case 13: return res_launch<R, 8, 128, 5, 8, 1, false>(a, s);      // 1.03 (5.6)
-        case 14: return res_launch<R, 9, 256, 5, 8, 1, false>(a, s);      // 1.25 (5.8)
-        case 15: return res_launch<R, 10, 256, 5, 8, 4, false>(a, s);     // 1.57 (5.8)
-        case 16: return res_launch<R, 9, 256, 7, 1, 4, false>(a, s);      // 2.12 (6.3)
-        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s);      // 2.60 (6.6)
-        case 18: return res_launch<R, 10, 256, 8, 1, 4, false>(a, s);     // 3.78 (7.6)
-        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s);      // 5.56 (9.7)
-        case 20: return res_launch<R, 12, 512, 8, 1, 1, true>(a, s);      // 7.09 (9.6)
-        default: return res_launch<R, 7, 64, 0, 1, 1, false>(a, s);       // 0.29 (1.2)
+        case 8: return res_launch<R, 8, 128, 0, 1, 1, false>(a, s, blob);       // 0.31 (1.2)
+        case 9: return res_launch<R, 9, 256, 0, 1, 1, false>(a, s, blob);       // 0.36 (1.2)
+        case 10: return res_launch<R, 10, 512, 0, 1, 1, false>(a, s, blob);     // 0.45 (1.3)
+        case 11: return res_launch<R, 11, 1024, 0, 1, 1, false>(a, s, blob);    // 0.78 (1.9)
+        case 12: return res_launch<R, 8, 128, 4, 8, 1, false>(a, s, blob);      // 0.91 (3.1)
+        case 13: return res_launch<R, 8, 128, 5, 8, 1, false>(a, s, blob);      // 1.03 (5.6)
+        case 14: return res_launch<R, 9, 256, 5, 8, 1, false>(a, s, blob);      // 1.25 (5.8)
+        case 15: return res_launch<R, 10, 256, 5, 8, 4, false>(a, s, blob);     // 1.57 (5.8)
+        case 16: return res_launch<R, 9, 256, 7, 1, 4, false>(a, s, blob);      // 2.12 (6.3)
+        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s, blob);      // 2.60 (6.6)
+        case 18: return res_launch<R, 10, 256, 8, 1, 4, false>(a, s, blob);     // 3.78 (7.6)
+        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob);      // 5.56 (9.7)
+        case 20: return res_launch<R, 12, 512, 8, 1, 1, true>(a, s, blob);      // 7.09 (9.6)
+        default: return res_launch<R, 7, 64, 0, 1, 1, false>(a, s, blob);       // 0.29 (1.2)
         }
     } else {
         switch (a.n) {
-        case 7: return res_launch<R, 7, 128, 0, 1, 1, false>(a, s);       // 0.31 (1.1)
-        case 8: return res_launch<R, 8, 256, 0, 1, 1, false>(a, s);       // 0.31 (1.1)
-        case 9: return res_launch<R, 9, 512, 0, 1, 1, false>(a, s);       // 0.44 (1.2)
-        case 10: return res_launch<R, 10, 1024, 0, 1, 1, false>(a, s);    // 0.70 (1.3)
-        case 11: return res_launch<R, 8, 256, 3, 8, 1, false>(a, s);      // 0.79 (2.0)
-        case 12: return res_launch<R, 7, 128, 5, 8, 1, false>(a, s);      // 0.90 (3.4)
-        case 13: return res_launch<R, 8, 256, 5, 8, 1, false>(a, s);      // 1.11 (7.8)
-        case 14: return res_launch<R, 9, 256, 5, 8, 4, false>(a, s);      // 1.42 (8.1)
-        case 15: return res_launch<R, 8, 256, 7, 1, 4, false>(a, s);      // 2.01 (8.6)
-        case 16: return res_launch<R, 8, 256, 8, 1, 4, false>(a, s);      // 2.52 (9.1)
-        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s);      // 3.60 (10.3)
-        case 18: return res_launch<R, 10, 1024, 8, 1, 1, true>(a, s);     // 5.43 (12.3)
-        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s);      // 6.55 (13.0)
-        default: return res_launch<R, 6, 64, 0, 1, 1, false>(a, s);       // 0.25 (1.1)
+        case 7: return res_launch<R, 7, 128, 0, 1, 1, false>(a, s, blob);       // 0.31 (1.1)
+        case 8: return res_launch<R, 8, 256, 0, 1, 1, false>(a, s, blob);       // 0.31 (1.1)
+        case 9: return res_launch<R, 9, 512, 0, 1, 1, false>(a, s, blob);       // 0.44 (1.2)
+        case 10: return res_launch<R, 10, 1024, 0, 1, 1, false>(a, s, blob);    // 0.70 (1.3)
+        case 11: return res_launch<R, 8, 256, 3, 8, 1, false>(a, s, blob);      // 0.79 (2.0)
+        case 12: return res_launch<R, 7, 128, 5, 8, 1, false>(a, s, blob);      // 0.90 (3.4)
+        case 13: return res_launch<R, 8, 256, 5, 8, 1, false>(a, s, blob);      // 1.11 (7.8)
+        case 14: return res_launch<R, 9, 256, 5, 8, 4, false>(a, s, blob);      // 1.42 (8.1)
+        case 15: return res_launch<R, 8, 256, 7, 1, 4, false>(a, s, blob);      // 2.01 (8.6)
+        case 16: return res_launch<R, 8, 256, 8, 1, 4, false>(a, s, blob);      // 2.52 (9.1)
+        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s, blob);      // 3.60 (10.3)
+        case 18: return res_launch<R, 10, 1024, 8, 1, 1, true>(a, s, blob);     // 5.43 (12.3)
+        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob);      // 6.55 (13.0)
+        default: return res_launch<R, 6, 64, 0, 1, 1, false>(a, s, blob);       // 0.25 (1.1)
         }
     }
 }
