@@ -378,10 +378,45 @@ static void launch_pass(const PassArgs<R> &a, int mode, bool otf, uint64_t ntile
         if (cfg.stream) return launch_shape<R, Cfg<R>::TB, Cfg<R>::NT, true, true>(a, mode, otf, ntiles, s, kp);
         return launch_shape<R, Cfg<R>::TB, Cfg<R>::NT, true, false>(a, mode, otf, ntiles, s);
     } else {
+        if (cfg.tb == TB_WIDE_D) {
+            if (cfg.stream) return launch_shape<R, TB_WIDE_D, NT_WIDE, true, true>(a, mode, otf, ntiles, s, cfg.keep_pd);
+            return launch_shape<R, TB_WIDE_D, NT_WIDE, true, false>(a, mode, otf, ntiles, s);
+        }
         if (cfg.nt == NT_NARROW) return launch_shape<R, TB_NARROW, NT_NARROW, false, false>(a, mode, otf, ntiles, s);
         if (cfg.stream) return launch_shape<R, Cfg<R>::TB, Cfg<R>::NT, true, true>(a, mode, otf, ntiles, s, cfg.keep_pd);
         return launch_shape<R, Cfg<R>::TB, Cfg<R>::NT, true, false>(a, mode, otf, ntiles, s);
     }
+}
+
+// One pass over an orientation with cross bits; a fused one with the pass that
+// completes what its clusters may have left.
+template <typename R, bool OTF, bool KEEP_PD, int XH>
+static void launch_cross_shape(const PassArgs<R> &a, int mode, uint64_t ntiles, hipStream_t s)
+{
+    constexpr int TB = (sizeof(R) == 4) ? TB_WIDE : TB_WIDE_D;
+    const dim3 grid((unsigned)ntiles), block(NT_WIDE);
+    if (mode == PM_START) hipLaunchKernelGGL((k_pass_cross<R, TB, NT_WIDE, PM_START, OTF, true, KEEP_PD, XH>), grid, block, 0, s, a);
+    else if (mode == PM_ADD) hipLaunchKernelGGL((k_pass_cross<R, TB, NT_WIDE, PM_ADD, false, true, KEEP_PD, XH>), grid, block, 0, s, a);
+    else {
+        hipLaunchKernelGGL((k_pass_cross<R, TB, NT_WIDE, PM_FUSED, OTF, true, KEEP_PD, XH>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_pass_late<R, TB, NT_WIDE, OTF, true, KEEP_PD, XH>), dim3(256), block, 0, s, a, (int)ntiles);
+    }
+}
+
+template <typename R>
+static void launch_cross(const PassArgs<R> &a, int mode, bool otf, uint64_t ntiles, hipStream_t s, int xh)
+{
+    // one size per number of cross bits; the first (psi and the diagonal stay
+    // cacheable, the diagonal is stored) differs from the others
+    if (xh == 1) return launch_cross_shape<R, false, true, 1>(a, mode, ntiles, s);
+    if (otf) {
+        if (xh == 2) return launch_cross_shape<R, true, false, 2>(a, mode, ntiles, s);
+        if (xh == 3) return launch_cross_shape<R, true, false, 3>(a, mode, ntiles, s);
+        return launch_cross_shape<R, true, false, 4>(a, mode, ntiles, s);
+    }
+    if (xh == 2) return launch_cross_shape<R, false, false, 2>(a, mode, ntiles, s);
+    if (xh == 3) return launch_cross_shape<R, false, false, 3>(a, mode, ntiles, s);
+    return launch_cross_shape<R, false, false, 4>(a, mode, ntiles, s);
 }
 
 // Read back ||b_k||^2 (k = 1..K-1), ||y||^2 (slot 0) and ||v||^2 (slot K+1);
@@ -623,7 +658,10 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     double *qt = reinterpret_cast<double *>(ws + L.qt);
     // orientations and launch shapes; the end orientations rebuild the diagonal
     // where the plan says so, and the stored one is formed only if a pass reads it
-    const std::vector<OrientSpec> plan = action_plan<R>(n, diag == nullptr);
+    const std::vector<OrientSpec> general = action_plan<R>(n, diag == nullptr);
+    std::vector<OrientSpec> pair;
+    if (!monitor) pair = pair_plan<R>(n, diag == nullptr);
+    const std::vector<OrientSpec> &plan = pair.empty() ? general : pair;
     bool any_otf = false;
     for (const OrientSpec &o : plan) any_otf = any_otf || o.otf;
     if (any_otf && !(L.ft != size_t(-1))) { set_error("internal: no per-tile field table for this size"); return QW_EINVAL; }
@@ -654,9 +692,9 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         info->K = K;
         info->a = a;
         info->trunc_bound = err;
-        info->passes = (int)plan.size();
-        for (size_t o = 0; o < plan.size(); ++o)
-            if (plan[o].otf) info->otf_mask |= 1 << o;
+        info->passes = (int)general.size();
+        for (size_t o = 0; o < general.size(); ++o)
+            if (general[o].otf) info->otf_mask |= 1 << o;
     }
 
     if (K == 0) {
@@ -759,6 +797,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         const TileCfg &pc = plan[o].fused;
         const int log_nt = (pc.nt == 1024) ? 10 : 9;
         const bool shape_ok = (sizeof(R) == 4 && pc.tb == TB_WIDE && pc.nt == NT_WIDE) ||
+                              (sizeof(R) == 8 && pc.tb == TB_WIDE_D && pc.nt == NT_WIDE) ||
                               (pc.tb == Cfg<R>::TB && pc.nt == Cfg<R>::NT);
         if (pl.L + pl.h != pc.tb || !shape_ok || pc.tb - log_nt > QS_MAX_R) {
             set_error("internal: on-the-fly tile shape");
@@ -766,7 +805,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         }
         hipLaunchKernelGGL(k_qsplit_orient<0>, dim3(((1 << log_nt) + 255) / 256), dim3(256), 0, s, T.h, n, pl.L,
                            pl.g0, pl.h, log_nt, sizeof(R) == 4 ? 1 : 0, norm_inv_r, qt + (size_t)o * (1 << TB_WIDE));
-        const uint64_t nt = N >> (pl.L + pl.h);
+        const uint64_t nt = N >> (pl.L + pl.h);   // tiles, those of a cluster counted each
         hipLaunchKernelGGL(k_tile_fields<0>, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, T.h, n, pl.L,
                            pl.g0, pl.h, nt, norm_c, norm_inv_r, ft + (size_t)o * ft_stride);
     }
@@ -787,6 +826,17 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     pa.d = dn;
     pa.g = (R)g;
     pa.n = n;
+    if (plan[0].xh > 0) {
+        // flags and the list of late tiles, in the place of the norms
+        const uint64_t nt = N >> plan[0].fused.tb;
+        const size_t half = KMAX_MON * sizeof(double) / 2;
+        pa.flag = reinterpret_cast<int *>(norms);
+        pa.flag_step = (int)std::min<uint64_t>(RES_LINE, half / sizeof(int) / nt);
+        pa.late = reinterpret_cast<int *>(reinterpret_cast<char *>(norms) + half);
+        pa.patience = t_patience;
+        if (pa.flag_step < 1 || (nt + 1) * sizeof(int) > half) { set_error("internal: room for the flags"); return QW_EINVAL; }
+        hipLaunchKernelGGL(k_fill_zero<0>, dim3(64), dim3(256), 0, s, norms, (uint64_t)KMAX_MON);
+    }
     const std::vector<SchedPass> sched = fused_schedule(K, P);
     PassTimer ptimer(info && info->timing == 2, s, sched.size() + 1);
     ptimer.mark(-1);
@@ -846,7 +896,12 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         pa.ci = (R)ci;
         const uint64_t ntiles = N >> (pl.L + pl.h);
         pa.xcd_order = os.xcd;
-        launch_pass<R>(pa, sp.mode, pass_otf, ntiles, s, sp.mode == PM_ADD ? os.add : os.fused);
+        if (os.xh > 0) {
+            if (sp.mode == PM_FUSED) ++pa.round;
+            launch_cross<R>(pa, sp.mode, pass_otf, ntiles, s, os.xh);
+        } else {
+            launch_pass<R>(pa, sp.mode, pass_otf, ntiles, s, sp.mode == PM_ADD ? os.add : os.fused);
+        }
         ptimer.mark(sp.orient);
         if (sp.mode == PM_FUSED || (sp.mode == PM_START && P == 1)) std::swap(X, Y);
     }
@@ -876,9 +931,8 @@ static qw_status bound_entry(int n, const R *diag, const double *h, const double
 // Host-side check of a pass plan's index map (used by the CPU tests): every
 // (tile, element) pair must hit each index of [0, 2^n) exactly once and every
 // flipped partner must stay inside the tile.
-int check_plan(int n, int prec)
+static int check_orientations(const std::vector<OrientSpec> &spec, int n)
 {
-    const std::vector<OrientSpec> spec = (prec == 64) ? action_plan<float>(n, true) : action_plan<double>(n, true);
     const uint64_t N = uint64_t(1) << n;
     int covered_bits = 0;
     for (const OrientSpec &os : spec) {
@@ -889,8 +943,19 @@ int check_plan(int n, int prec)
         std::vector<uint8_t> seen(N, 0);
         const uint64_t ntiles = N >> (p.L + p.h);
         const uint32_t TE = 1u << (p.L + p.h);
-        for (uint64_t t = 0; t < ntiles; ++t) {
+        if (os.xh > 0 && (p.g0 + p.h + os.xh != n || ntiles % (uint64_t(8) << os.xh) != 0)) return -8;
+        for (uint64_t b = 0; b < ntiles; ++b) {
+            // the tile of block b; cross bits: the partner's partner map is checked on the bases
+            uint64_t t = b;
+            if (os.xh == 1) t = cross_tile<1>((uint32_t)b, (uint32_t)ntiles, p.g0 - p.L);
+            if (os.xh == 2) t = cross_tile<2>((uint32_t)b, (uint32_t)ntiles, p.g0 - p.L);
+            if (os.xh == 3) t = cross_tile<3>((uint32_t)b, (uint32_t)ntiles, p.g0 - p.L);
+            if (os.xh == 4) t = cross_tile<4>((uint32_t)b, (uint32_t)ntiles, p.g0 - p.L);
+            if (t >= ntiles) return -9;
             const uint64_t base = tile_base(t, p.L, p.g0, p.h);
+            for (int j = 0; j < os.xh; ++j)
+                if (tile_base(t ^ (uint64_t(1) << (p.g0 - p.L + j)), p.L, p.g0, p.h) !=
+                    (base ^ (uint64_t(1) << (p.g0 + p.h + j)))) return -10;
             for (uint32_t e = 0; e < TE; ++e) {
                 const uint64_t idx = tile_index(base, e, p.L, p.g0);
                 if (idx >= N || seen[idx]) return -3;
@@ -902,9 +967,19 @@ int check_plan(int n, int prec)
                 }
             }
         }
-        covered_bits += p.h;
+        covered_bits += p.h + os.xh;
     }
     return covered_bits == n ? (int)spec.size() : -6;
+}
+
+int check_plan(int n, int prec)
+{
+    const std::vector<OrientSpec> pair = (prec == 64) ? pair_plan<float>(n, true) : pair_plan<double>(n, true);
+    if (!pair.empty()) {
+        const int rc = check_orientations(pair, n);
+        if (rc < 0) return rc;
+    }
+    return check_orientations((prec == 64) ? action_plan<float>(n, true) : action_plan<double>(n, true), n);
 }
 
 template <typename R>

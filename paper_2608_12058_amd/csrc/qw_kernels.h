@@ -285,6 +285,10 @@ template <typename R> struct PassArgs {
     int n, L, g0, h;
     double *norm_acc = nullptr;   // if set: += sum |b|^2 of the completed vector (atomic, one per block)
     int xcd_order = 0;            // 1: blocks take tiles in XCD-major order (xcd_tile)
+    int *flag = nullptr;          // cross bits: one word per tile, flag[tile * flag_step]
+    int *late = nullptr;          // cross bits: tiles whose second half is left to k_pass_late
+    int flag_step = 0, round = 0; // the word of a tile that has reached this pass's middle: its round number
+    int patience = 0;             // looks at a flag before giving up
     int b1_scaled = 0;            // 1: b1 points at psi and b_{k+1} = (b1r + i b1i) psi (the
     R b1r = R(1), b1i = R(0);     //    Clenshaw start b_K = c_K psi, never stored)
 };
@@ -382,6 +386,29 @@ __global__ void __launch_bounds__(256) k_qsplit_orient(const double *hJ, int n, 
     }
 }
 
+// Meeting of the tiles of a cluster (cross bits of pass_tile).  The word of a
+// tile holds the round and the XCD it ran on.
+__device__ __forceinline__ int cross_word(int round)
+{
+    return round * 16 + (int)__builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, 4 bits
+}
+
+// One wave: true once the words of the XH partners of `tile` (its id with one of
+// the bits shift .. shift + XH - 1 flipped) equal `word`: all of them have
+// stored b_k, on this XCD.
+template <int XH>
+__device__ __forceinline__ bool cross_meet(const int *flag, int step, uint64_t tile, int shift, int word, int patience)
+{
+    const int lane = threadIdx.x & 63;
+    const int *p = flag + (tile ^ (lane < XH ? uint64_t(1) << (shift + lane) : 0)) * step;
+    bool met = false;
+    do {
+        met = !__any(lane < XH && __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != word);
+    } while (!met && --patience > 0);
+    asm volatile("" ::: "memory");
+    return met;
+}
+
 // One pass over one tile (see tile_base/tile_index); F_group sums the flips of
 // the tile's h group bits:
 //  START: dst = scale (d .* b1 + g F b1) - sub acc + c_k psi,        then *= (pr + i pi)
@@ -391,7 +418,15 @@ __global__ void __launch_bounds__(256) k_qsplit_orient(const double *hJ, int n, 
 // The Clenshaw recurrence uses scale 2 (1 on the final step) and sub 1; Horner's
 // rule (y_k = H y_{k+1} + a_k psi) the same passes with scale 1 and sub 0.
 // FUSED needs b_k of the whole tile, so the tile is re-staged through LDS.
-template <typename R, int TB, int NT, int MODE, bool OTF, bool STREAM = false, bool KEEP_PD = false>
+//
+// XH > 0: the orientation has XH more group bits, g0 + h .. g0 + h + XH - 1
+// (n - 1), than the tile: the tiles of one cluster of 2^XH differ in those bits
+// of their ids, and their flips come from the other tiles in memory.  b_{k+1} is
+// there when the pass starts; b_k, for the second half of FUSED, is once the
+// partner tile has stored it and raised its flag (see k_pass_cross).
+// LATE: only the second half of FUSED, b_k taken from dst.
+template <typename R, int TB, int NT, int MODE, bool OTF, bool STREAM = false, bool KEEP_PD = false, int XH = 0,
+          bool LATE = false>
 __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, typename Cplx<R>::T *lds)
 {
     using C = typename Cplx<R>::T;
@@ -429,6 +464,31 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
     constexpr bool PD_HINT = STREAM && !KEEP_PD;   // hint on the psi and diagonal loads
     constexpr bool EARLY_PSI = DIAG && !OTF && (MODE != PM_FUSED || !C64);
     constexpr bool EARLY_D = (MODE == PM_FUSED) && !OTF && C64;
+    // sums over the partner tiles' vectors (cross bits)
+    const int gx = a.g0 + a.h;
+    auto cross = [&](const C *src, uint64_t idx, bool scaled, R (&sr)[VE], R (&si)[VE]) {
+        V x[XH > 0 ? XH : 1];
+#pragma unroll
+        for (int j = 0; j < XH; ++j) x[j] = ld_v<R, false>(src + (idx ^ (uint64_t(1) << (gx + j))));
+        R tr[VE], ti[VE];
+#pragma unroll
+        for (int v = 0; v < VE; ++v) {
+            tr[v] = x[0].v[v].x;
+            ti[v] = x[0].v[v].y;
+#pragma unroll
+            for (int j = 1; j < XH; ++j) {
+                tr[v] += x[j].v[v].x;
+                ti[v] += x[j].v[v].y;
+            }
+            if (scaled) {
+                const R p = tr[v], q = ti[v];
+                tr[v] = fmad(a.b1r, p, -(a.b1i * q));
+                ti[v] = fmad(a.b1r, q, a.b1i * p);
+            }
+            sr[v] += tr[v];
+            si[v] += ti[v];
+        }
+    };
     V psiv[EARLY_PSI ? PER : 1];
     R dv[EARLY_D ? PER : 1][VE];
 #pragma unroll
@@ -436,7 +496,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
         const uint32_t e = (uint32_t)(q * NT + threadIdx.x) * VE;
         if (e < TE) {
             const uint64_t idx = tile_index(base, e, a.L, a.g0);
-            own[q] = ld_v<R, STREAM>(a.b1 + idx);
+            own[q] = ld_v<R, STREAM && XH == 0>(a.b1 + idx);   // cross bits: kept in L2 for the partners
             if (a.b1_scaled) {
 #pragma unroll
                 for (int v = 0; v < VE; ++v) {
@@ -444,11 +504,23 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
                     own[q].v[v] = C{fmad(a.b1r, p.x, -(a.b1i * p.y)), fmad(a.b1r, p.y, a.b1i * p.x)};
                 }
             }
-            if (a.acc) {
+            if constexpr (LATE) {
+                accv[q] = ld_v<R, false>(a.dst + idx);   // b_k
+            } else if (a.acc) {
                 accv[q] = ld_v<R, STREAM>(a.acc + idx);
             } else {
 #pragma unroll
                 for (int v = 0; v < VE; ++v) accv[q].v[v] = C{R(0), R(0)};
+            }
+            if constexpr (XH > 0 && MODE == PM_FUSED && !LATE) {
+                R sr[VE] = {}, si[VE] = {};
+                cross(a.b1, idx, false, sr, si);   // the first fused pass, whose b_{k+1} is scaled psi, has no cross bits
+                const R sg = a.scale * a.g;
+#pragma unroll
+                for (int v = 0; v < VE; ++v) {
+                    accv[q].v[v].x = fmad(sg, sr[v], accv[q].v[v].x);
+                    accv[q].v[v].y = fmad(sg, si[v], accv[q].v[v].y);
+                }
             }
             if constexpr (EARLY_PSI) psiv[q] = ld_v<R, PD_HINT>(a.psi + idx);
             if constexpr (EARLY_D) {
@@ -584,11 +656,12 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
 
     double nrm = 0.0;
     if constexpr (MODE == PM_FUSED) {
-        // complete b_k in registers (complex64: and store it at once)
+        // complete b_k in registers (complex64 and cross bits: and store it at once)
+        constexpr bool STORE_NOW = C64 || XH > 0;
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const uint32_t e = (uint32_t)(q * NT + threadIdx.x) * VE;
-            if (e < TE) {
+            if (e < TE && !LATE) {
                 R sr[VE], si[VE];
                 flips(q, e, own, sr, si);
                 const R sg = a.scale * a.g;
@@ -597,10 +670,16 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
                     accv[q].v[v].x = fmad(sg, sr[v], accv[q].v[v].x);
                     accv[q].v[v].y = fmad(sg, si[v], accv[q].v[v].y);
                 }
-                if constexpr (C64) st_v<R, STREAM>(a.dst + tile_index(base, e, a.L, a.g0), accv[q]);
+                if constexpr (STORE_NOW) st_v<R, STREAM && XH == 0>(a.dst + tile_index(base, e, a.L, a.g0), accv[q]);
             }
         }
+        if constexpr (XH > 0 && !LATE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // b_k has arrived in L2
         __syncthreads();   // every flip of b_{k+1} has been read
+        if constexpr (XH > 0 && !LATE) {
+            if (threadIdx.x == 0)
+                __hip_atomic_store(a.flag + tile * a.flag_step, cross_word(a.round), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const uint32_t e = (uint32_t)(q * NT + threadIdx.x) * VE;
@@ -609,7 +688,23 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
                 for (int v = 0; v < VE; ++v) lds[e + v] = accv[q].v[v];
             }
         }
-        __syncthreads();
+        if constexpr (XH > 0 && !LATE) {
+            __shared__ int met;
+            if (threadIdx.x < 64) {
+                const bool ok = cross_meet<XH>(a.flag, a.flag_step, tile, a.g0 - a.L, cross_word(a.round), a.patience);
+                if (threadIdx.x == 0) {
+                    met = ok;
+                    if (!ok) {
+                        a.late[1 + tile] = a.round;
+                        (void)__hip_atomic_fetch_add(a.late, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+            }
+            __syncthreads();
+            if (!__builtin_amdgcn_readfirstlane(met)) return;
+        } else {
+            __syncthreads();
+        }
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const uint32_t e = (uint32_t)(q * NT + threadIdx.x) * VE;
@@ -620,6 +715,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
                 V psl;   // one 16-byte load, hinted as the pass
                 if constexpr (!EARLY_PSI) psl = ld_v<R, PD_HINT>(a.psi + idx);
                 flips(q, e, accv, sr, si);
+                if constexpr (XH > 0) cross(a.dst, idx, false, sr, si);
 #pragma unroll
                 for (int v = 0; v < VE; ++v) {
                     R dd;
@@ -630,7 +726,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
                     out.v[v] = first_part(dd, bk, sr[v], si[v], bp, ps, a.scale2);
                     if (a.norm_acc) nrm += (double)bk.x * bk.x + (double)bk.y * bk.y;
                 }
-                if constexpr (!C64) st_v<R, STREAM>(a.dst + idx, accv[q]);
+                if constexpr (!STORE_NOW) st_v<R, STREAM>(a.dst + idx, accv[q]);
                 st_v<R, STREAM>(a.dst2 + idx, out);
             }
         }
@@ -643,6 +739,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
                 V out;
                 R sr_[VE], si_[VE];
                 flips(q, e, own, sr_, si_);
+                if constexpr (XH > 0) cross(a.b1, idx, a.b1_scaled != 0, sr_, si_);
 #pragma unroll
                 for (int v = 0; v < VE; ++v) {
                     const R sr = sr_[v], si = si_[v];
@@ -677,6 +774,58 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_
     __shared__ typename Cplx<R>::T lds[1 << TB];
     const uint64_t tile = a.xcd_order ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
     pass_tile<R, TB, NT, MODE, OTF, STREAM, KEEP_PD>(a, tile, lds);
+}
+
+// A pass whose orientation has XH more group bits than its tile (pass_tile with
+// cross bits): two orientations where tiles alone need three, so a term moves 40
+// or 44 bytes per amplitude instead of 64 (complex64).  The 2^XH tiles of a
+// cluster are neighbours in the launch order of one XCD, so they run side by side
+// and read each other's b_{k+1} and b_k from its L2 (both are therefore loaded
+// and stored without the streaming hint: with it 26 qubits took 684 us per term
+// instead of 612).  FUSED waits in the middle for its XH partners.  They have been
+// launched before it or are the next in line on that XCD, so the wait is short
+// unless other work holds the CUs (without it 26 qubits took 615 us against 616);
+// it ends after `patience` looks in any case, or in vain if a partner ran on
+// another XCD, and then the tile's second half is left to k_pass_late, which
+// follows every FUSED pass and finds nothing to do as a rule.  A tile writes
+// b_{k-1} over b_{k+1} only after its partners, which read it, have passed their
+// middle.  A stale L1 line cannot be met: the vectors of a partner's tile are read
+// only by that tile and, after its flag, by its partners, and a store by the same
+// CU replaces the line.
+// What bounds it: rows of 128 B and one workgroup per CU, 3.9 TB/s at 25-27
+// qubits (the contiguous 2^14 tiles: 5.5); each cross bit adds 2 % at two bits and
+// 8 % at four, where the partners' vectors outgrow the L2.  Rows of 256 B with one
+// more cross bit were slower (26 qubits 631 us per term, rows of 512 B 675), as
+// were 2^13 tiles, two to a CU (617; 28 qubits 3053 against 2723), and psi or
+// c psi - b_{k+1} formed ahead of the meeting (604-674).
+// Clusters in XCD-major order (neighbouring rows on one XCD), except pairs, which
+// are faster dealt out in turn (25 qubits: 312 us per term against 329; 26: 646
+// against 615).
+template <int XH> __host__ __device__ __forceinline__ uint64_t cross_tile(uint32_t b, uint32_t nb, int shift)
+{
+    const uint32_t x = b % 8, i = b / 8, m = i & ((1u << XH) - 1);
+    const uint32_t cluster = (XH == 1) ? (i >> XH) * 8 + x : x * (nb >> (3 + XH)) + (i >> XH);
+    return ((uint64_t)m << shift) | cluster;
+}
+
+template <typename R, int TB, int NT, int MODE, bool OTF, bool STREAM, bool KEEP_PD, int XH>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_pass_cross(PassArgs<R> a)
+{
+    __shared__ typename Cplx<R>::T lds[1 << TB];
+    const uint64_t tile = cross_tile<XH>(blockIdx.x, gridDim.x, a.g0 - a.L);
+    pass_tile<R, TB, NT, MODE, OTF, STREAM, KEEP_PD, XH>(a, tile, lds);
+}
+
+template <typename R, int TB, int NT, bool OTF, bool STREAM, bool KEEP_PD, int XH>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_pass_late(PassArgs<R> a, int ntiles)
+{
+    __shared__ typename Cplx<R>::T lds[1 << TB];
+    if (a.late[0] == 0) return;
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        if (a.late[1 + t] != a.round) continue;
+        __syncthreads();   // lds of the tile before
+        pass_tile<R, TB, NT, PM_FUSED, OTF, STREAM, KEEP_PD, XH, true>(a, (uint64_t)t, lds);
+    }
 }
 
 // Whole recurrence of one small instance (n <= TB) inside one workgroup.
@@ -835,7 +984,7 @@ template <typename R> inline std::vector<PassPlan> plan_passes(int n)
 // pass 1114 -> 1077); 25, 26, 27 qubits: 405 -> 396, 818 -> 792, 1650 -> 1604 us.
 // From 29 qubits one high group takes 9 or 10 bits (128-byte rows): the
 // per-orientation plans of action_plan.
-static constexpr int TB_WIDE = 14, NT_WIDE = 1024;
+static constexpr int TB_WIDE = 14, TB_WIDE_D = 13, NT_WIDE = 1024;
 static constexpr int TB_NARROW = 12, NT_NARROW = 1024;
 static constexpr int NT_MID = 1024;   // complex64 2^13 tiles, 8 amplitudes per thread
 static constexpr int SPLIT_NMIN = 25, SPLIT_NMAX = 28;
@@ -926,6 +1075,7 @@ struct OrientSpec {
     TileCfg add;     // shape of its ADD passes
     bool otf;        // START / FUSED rebuild the diagonal from the tile fields
     int xcd;         // blocks take tiles in XCD-major order (xcd_tile)
+    int xh = 0;      // cross bits above the group (k_pass_cross)
 };
 
 // Complex64 from 25 qubits: the contiguous orientation in the middle (an add
@@ -1004,6 +1154,37 @@ template <typename R> inline std::vector<OrientSpec> action_plan(int n, bool dia
         S.front().otf = true;
         S.back().otf = true;
     }
+    return S;
+}
+
+// Two orientations where action_plan has three; used without the norm monitor
+// (whose sums the passes with cross bits do not form); empty where there is none.
+// The contiguous orientation takes tiles of 128 KB whole (2^14 amplitudes in
+// complex64, 2^13 in complex128), the other one the rest in rows of 128 B: 10
+// bits per tile and up to four cross bits.  Measured in microseconds per term,
+// action_plan in parentheses: complex64 25 qubits 312 (383), 26: 612 (758), 27:
+// 1205 (1503), 28: 2710 (2970); complex128 22: 63.6 (94.1), 23: 137 (199), 24:
+// 344 (415), 25: 693 (810), 26: 1195 (1570), 27: 2705 (3190).  Five cross bits
+// are slower than a third orientation (28 qubits on 2^13 tiles: 3053).  The
+// strided orientation rebuilds the diagonal from 26 qubits; the contiguous one
+// does in complex128, while in complex64 its 4 of 44 bytes are cheaper read (28
+// qubits: 2006 us per pass against 2131).
+template <typename R> inline std::vector<OrientSpec> pair_plan(int n, bool diag_from_tables)
+{
+    std::vector<OrientSpec> S;
+    const bool st = stream_for<R>(n);
+    const bool kp = st && std::ldexp(sizeof(R) == 4 ? 12.0 : 24.0, n) <= 384.0 * (1 << 20);
+    constexpr int TB = (sizeof(R) == 4) ? TB_WIDE : TB_WIDE_D;     // 128 KB of LDS
+    constexpr int H = TB - Cfg<R>::LMIN;                           // in rows of 128 B
+    const int xh = std::max(0, n - TB - H);
+    if (n < (sizeof(R) == 4 ? 25 : 22) || n > (sizeof(R) == 4 ? 28 : 27)) return S;
+    const TileCfg wide{TB, NT_WIDE, st, 0, kp};
+    const int h = n - TB - xh;
+    const bool otf = diag_from_tables && n >= OTF_TOP_NMIN;
+    // the orientation with cross bits first: with one term it reads psi, and the
+    // last pass, which may write over psi, is the other
+    S.push_back({{TB - h, TB, h}, wide, wide, otf, 0, xh});
+    S.push_back({{0, 0, TB}, wide, wide, otf && sizeof(R) == 8, 1, 0});
     return S;
 }
 
