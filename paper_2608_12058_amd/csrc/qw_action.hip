@@ -730,20 +730,16 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         ra.out = out;
         ra.diag = diag;
         ra.hJ = T.h;
-        ra.c = norm_c;
-        ra.inv_r = norm_inv_r;
+        ra.first = ResStep<R>{norm_c, norm_inv_r, (R)g, (R)ph_r, (R)ph_i, K, 0};
+        ra.nsteps = 1;
         ra.X0 = X;
         ra.X1 = Y;
         ra.d = dn;
         ra.start = reinterpret_cast<int *>(ws + L.items);
         ra.flags = reinterpret_cast<int *>(norms);
-        ra.g = (R)g;
         ra.two = horner ? R(1) : R(2);
         ra.sub = horner ? R(0) : R(1);
-        ra.pr = (R)ph_r;
-        ra.pi = (R)ph_i;
         ra.n = n;
-        ra.K = K;
         ra.patience = t_patience;
         C *dcoef = reinterpret_cast<C *>(ws + (own_coef ? L.coef : L.qt));
         ra.coef = dcoef;
@@ -1034,6 +1030,91 @@ qw_status scaled_action(int n, const double *h, const double *J, const EnergyTab
                           cr, nullptr, &prep);
 }
 
+template <typename R>
+qw_status scaled_chain(int n, const EnergyTables &T, double emin, double emax, const std::vector<ChainItem> &items,
+                       const void *psi_in, void *psi_out, void *workspace, size_t ws_bytes, void *stream,
+                       long long *terms)
+{
+    using C = typename Cplx<R>::T;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    char *ws = static_cast<char *>(workspace);
+    const WsLayout L = ws_layout(n, prec_of<R>(), false);
+    if (!chain_fits<R>(n) || ws_bytes < L.total) { set_error("internal: chain of exponentials"); return QW_EINVAL; }
+    std::vector<ResStep<R>> steps;
+    std::vector<C> coef;
+    for (const ChainItem &it : items) {
+        // as scaled_action and action_impl
+        double c = it.alpha * 0.5 * (emax + emin);
+        double r = std::fabs(it.alpha) * 0.5 * (emax - emin) + n * std::fabs(it.beta);
+        if (!(r > 0.0)) continue;   // H' = c I, here c = 0 as well: the identity
+        double g = it.beta / r;
+        if (sizeof(R) == 4 && it.beta != 0.0) {
+            float gf = (float)g;
+            if (std::fabs((double)gf) > std::fabs(g)) gf = std::nextafter(gf, 0.0f);
+            g = (double)gf;
+            r = it.beta / g;
+        }
+        std::vector<double> alpha;
+        int K = 0;
+        double err = 0.0;
+        if (coefficients(it.t * r, it.tol, QW_CHEB, alpha, &K, &err) != 0) { set_error("coefficient setup failed"); return QW_ENOCONV; }
+        const double es = it.alpha;
+        steps.push_back({(es != 0.0) ? c / es : 0.0, es / r, (R)g, (R)std::cos(it.t * c), (R)-std::sin(it.t * c), K,
+                         (int)coef.size()});
+        for (int k = 0; k <= K; ++k) {
+            double cr, ci;
+            coef_of(alpha, k, cr, ci);
+            coef.push_back(C{(R)cr, (R)ci});
+        }
+        *terms += K;
+    }
+    if (steps.empty()) {
+        if (psi_out != psi_in)
+            QW_HIP(hipMemcpyAsync(psi_out, psi_in, (size_t(1) << n) * sizeof(C), hipMemcpyDeviceToDevice, s));
+        return QW_OK;
+    }
+    const bool own_coef = L.coef != size_t(-1);
+    const size_t room = own_coef ? (size_t)(KMAX_ONCHIP + 1) : 4 * (size_t(1) << TB_WIDE) * sizeof(double) / sizeof(C);
+    static_assert(sizeof(ResStep<R>) % sizeof(uint64_t) == 0, "whole words");
+    static_assert((CHAIN_ITEMS - 1) * sizeof(ResStep<R>) <= (size_t(1) << LB_TAB) * sizeof(double), "room for the steps");
+    if (steps.size() > CHAIN_ITEMS || coef.size() > room) { set_error("internal: chain too long"); return QW_ENOMEM; }
+    ResArgs<R> ra{};
+    ra.psi = static_cast<const C *>(psi_in);
+    ra.out = static_cast<C *>(psi_out);
+    ra.hJ = T.h;
+    ra.first = steps[0];
+    ra.nsteps = (int)steps.size();
+    ra.more = reinterpret_cast<const ResStep<R> *>(ws + L.q);
+    C *dcoef = reinterpret_cast<C *>(ws + (own_coef ? L.coef : L.qt));
+    ra.coef = dcoef;
+    ra.X0 = reinterpret_cast<C *>(ws + L.b1);
+    ra.X1 = reinterpret_cast<C *>(ws + L.b2);
+    ra.d = reinterpret_cast<R *>(ws + L.d);
+    ra.start = reinterpret_cast<int *>(ws + L.items);
+    ra.flags = reinterpret_cast<int *>(ws + L.norms);
+    ra.two = R(2);
+    ra.sub = R(1);
+    ra.n = n;
+    ra.patience = t_patience;
+    const qw_status st = put(steps.data() + 1, (steps.size() - 1) * sizeof(ResStep<R>) / sizeof(uint64_t), ws + L.q, s,
+                             coef.data(), coef.size() * sizeof(C) / sizeof(uint64_t), dcoef, ra.flags, RES_MAXFLAGS,
+                             ra.start);
+    if (st != QW_OK) return st;
+    QW_HIP(launch_resident<R>(ra, s, nullptr));
+    return QW_OK;
+}
+
+template <typename R> bool chain_fits(int n) { return n >= 1 && n <= resident_nmax<R>(); }
+template <typename R> bool chain_captures(int n) { return !resident_coop<R>(n); }
+
+template bool chain_fits<float>(int);
+template bool chain_fits<double>(int);
+template bool chain_captures<float>(int);
+template bool chain_captures<double>(int);
+template qw_status scaled_chain<float>(int, const EnergyTables &, double, double, const std::vector<ChainItem> &,
+                                       const void *, void *, void *, size_t, void *, long long *);
+template qw_status scaled_chain<double>(int, const EnergyTables &, double, double, const std::vector<ChainItem> &,
+                                        const void *, void *, void *, size_t, void *, long long *);
 template qw_status prepare_energy<float>(int, const double *, const double *, void *, size_t, void *, EnergyTables *,
                                          bool *, double *, double *);
 template qw_status prepare_energy<double>(int, const double *, const double *, void *, size_t, void *, EnergyTables *,

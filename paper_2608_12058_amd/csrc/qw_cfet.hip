@@ -171,6 +171,23 @@ qw_status cfet_impl(int n, const double *h, const double *J, const double *A_coe
     long long terms = 0;
     double errb = 0.0, hmin = T, hmax = 0.0, t = 0.0;
     const void *src = psi_in;
+    // sizes whose recurrence is one launch apply several exponentials per launch:
+    // the host prepares the next launch while one runs
+    bool chain = chain_fits<R>(n);
+    if (chain && !chain_captures<R>(n)) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        chain = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    }
+    std::vector<ChainItem> items;
+    size_t batch = 4;   // a short first launch, so that the device starts early
+    auto flush = [&]() -> qw_status {
+        if (items.empty()) return QW_OK;
+        const qw_status fs = scaled_chain<R>(n, Tb, emin, emax, items, src, psi_out, workspace, ws_bytes, stream, &terms);
+        src = psi_out;
+        items.clear();
+        batch = CHAIN_ITEMS;
+        return fs;
+    };
     while (t < T) {
         double hs;
         double b = step_bound(S, I, t);
@@ -195,6 +212,18 @@ qw_status cfet_impl(int n, const double *h, const double *J, const double *A_coe
         const double be[2] = {a1 * B1 + a2 * B2, a2 * B1 + a1 * B2};
         const double tol_exp = std::max(floor_tol, trunc_share * tol * hs / T);
         for (int e = 0; e < 2; ++e) {
+            if (chain) {
+                // a degree too large to share a launch runs by itself
+                const double r = std::fabs(al[e]) * I.pshift + n * std::fabs(be[e]);
+                const bool large = hs * r > 512.0;
+                if (large || items.size() >= batch) st = flush();
+                if (st != QW_OK) { cleanup(); return st; }
+                if (!large) {
+                    items.push_back({al[e], be[e], hs, tol_exp});
+                    ++nexp;
+                    continue;
+                }
+            }
             qw_info ai{};
             st = scaled_action<R>(n, h, J, Tb, have_q, al[e], emin, emax, be[e], hs, src, psi_out, tol_exp, workspace,
                                   ws_bytes, stream, &ai);
@@ -211,6 +240,7 @@ qw_status cfet_impl(int n, const double *h, const double *J, const double *A_coe
         t += hs;
         if (!adaptive && nsteps == steps) break;
     }
+    if ((st = flush()) != QW_OK) { cleanup(); return st; }
     if (info) {
         info->steps = nsteps;
         info->exponentials = nexp;

@@ -31,20 +31,30 @@ struct PutBlob {
 };
 struct NoBlob {};
 
+// One exponential of a chain: psi stays in registers from one to the next (an
+// anneal of 128 exponentials of about five terms at 18 qubits: 2.65 ms, with a
+// launch and an upload each 4.79).
+template <typename R> struct ResStep {
+    double c, inv_r;      // d~ = (E - c) inv_r
+    R g, pr, pi;          // gamma / r, global phase
+    int K, coef;          // degree, place of c_0 .. c_K
+};
+
 template <typename R> struct ResArgs {
     using C = typename Cplx<R>::T;
     const C *psi;
     C *out;               // may be psi
     const R *diag;        // the caller's energies, or NULL: from (h, J)
     const double *hJ;     // device: h (n), J (packed)
-    double c, inv_r;      // d~ = (E - c) inv_r
-    const C *coef;        // device: c_0 .. c_K
+    ResStep<R> first;
+    const ResStep<R> *more;   // device: the nsteps - 1 steps after the first
+    int nsteps;
+    const C *coef;        // device: coefficients of all steps
     C *X0, *X1;           // exchange buffers of 2^n
     R *d;                 // 2^n, used only when the workgroups cannot all start
     int *start, *flags;   // 2 and RES_MAXFLAGS lines, cleared before the launch
-    R g, two, sub;        // gamma / r; Clenshaw 2 and 1, Horner's rule 1 and 0
-    R pr, pi;             // global phase
-    int n, K;
+    R two, sub;           // Clenshaw 2 and 1, Horner's rule 1 and 0
+    int n;
     int stride, sel;      // workgroups with blockIdx.x % stride == sel take part
     int patience;         // looks at the start word before giving up on a common start
 };
@@ -57,6 +67,7 @@ __device__ inline double energy_direct(const double *hJ, int n, uint32_t z)
 #pragma unroll 1
     for (int j = 0; j < n; ++j) {
         double f = hJ[j];
+#pragma unroll 1
         for (int k = j + 1; k < n; ++k) {
             const double x = *J++;
             f += ((z >> k) & 1) ? -x : x;
@@ -161,44 +172,51 @@ __device__ inline bool res_join(int *state, int W, int patience)
 
 // The recurrence by one workgroup alone, from global memory: what the last
 // workgroup to leave does when the common start failed.
-template <typename R, int NT> __device__ __noinline__ void res_alone(ResArgs<R> a, const double *hJ)
+template <typename R, int NT> __device__ __forceinline__ void res_alone(const ResArgs<R> &a, const double *hJ)
 {
     using C = typename Cplx<R>::T;
     const uint32_t N = 1u << a.n;
-    C *b1 = a.X0, *b2 = a.X1;
-    const C cK = a.coef[a.K];
 #pragma unroll 1
-    for (uint32_t z = threadIdx.x; z < N; z += NT) {
-        const double E = a.diag ? (double)a.diag[z] : energy_direct(hJ, a.n, z);
-        a.d[z] = (R)((E - a.c) * a.inv_r);
-        const C p = a.psi[z];
-        b1[z] = C{fmad(cK.x, p.x, -(cK.y * p.y)), fmad(cK.x, p.y, cK.y * p.x)};
-        b2[z] = C{R(0), R(0)};
-    }
-    __syncthreads();
-    for (int k = a.K - 1; k >= 0; --k) {
-        const C ck = a.coef[k];
-        const R scale = (k == 0) ? R(1) : a.two;
+    for (int i = 0; i < a.nsteps; ++i) {
+        const ResStep<R> st = i == 0 ? a.first : a.more[i - 1];
+        const C *coef = a.coef + st.coef, *psi = i == 0 ? a.psi : a.out;
+        C *b1 = a.X0, *b2 = a.X1;
+        const C cK = coef[st.K];
 #pragma unroll 1
         for (uint32_t z = threadIdx.x; z < N; z += NT) {
-            R sr = R(0), si = R(0);
-#pragma unroll 1
-            for (int j = 0; j < a.n; ++j) {
-                const C x = b1[z ^ (1u << j)];
-                sr += x.x;
-                si += x.y;
-            }
-            const C b = b1[z], s = b2[z], p = a.psi[z];
-            const R hr = fmad(a.d[z], b.x, a.g * sr), hi = fmad(a.d[z], b.y, a.g * si);
-            const R tr = fmad(scale, hr, -(a.sub * s.x)), ti = fmad(scale, hi, -(a.sub * s.y));
-            const C o{tr + fmad(ck.x, p.x, -(ck.y * p.y)), ti + fmad(ck.x, p.y, ck.y * p.x)};
-            if (k > 0) b2[z] = o;
-            else a.out[z] = C{fmad(a.pr, o.x, -(a.pi * o.y)), fmad(a.pr, o.y, a.pi * o.x)};
+            const double E = a.diag ? (double)a.diag[z] : energy_direct(hJ, a.n, z);
+            a.d[z] = (R)((E - st.c) * st.inv_r);
+            const C p = psi[z];
+            b1[z] = C{fmad(cK.x, p.x, -(cK.y * p.y)), fmad(cK.x, p.y, cK.y * p.x)};
+            b2[z] = C{R(0), R(0)};
+            if (st.K == 0) a.out[z] = C{fmad(st.pr, b1[z].x, -(st.pi * b1[z].y)), fmad(st.pr, b1[z].y, st.pi * b1[z].x)};
         }
         __syncthreads();
-        C *t = b1;
-        b1 = b2;
-        b2 = t;
+#pragma unroll 1
+        for (int k = st.K - 1; k >= 0; --k) {
+            const C ck = coef[k];
+            const R scale = (k == 0) ? R(1) : a.two;
+#pragma unroll 1
+            for (uint32_t z = threadIdx.x; z < N; z += NT) {
+                R sr = R(0), si = R(0);
+#pragma unroll 1
+                for (int j = 0; j < a.n; ++j) {
+                    const C x = b1[z ^ (1u << j)];
+                    sr += x.x;
+                    si += x.y;
+                }
+                const C b = b1[z], s = b2[z], p = psi[z];
+                const R hr = fmad(a.d[z], b.x, st.g * sr), hi = fmad(a.d[z], b.y, st.g * si);
+                const R tr = fmad(scale, hr, -(a.sub * s.x)), ti = fmad(scale, hi, -(a.sub * s.y));
+                const C o{tr + fmad(ck.x, p.x, -(ck.y * p.y)), ti + fmad(ck.x, p.y, ck.y * p.x)};
+                if (k > 0) b2[z] = o;
+                else a.out[z] = C{fmad(st.pr, o.x, -(st.pi * o.y)), fmad(st.pr, o.y, st.pi * o.x)};
+            }
+            __syncthreads();
+            C *t = b1;
+            b1 = b2;
+            b2 = t;
+        }
     }
 }
 
@@ -228,7 +246,7 @@ template <typename R, int CTRL> __device__ __forceinline__ CVec<R> lane_flip(con
 // What bounds it: the latency of that round, not bytes: about 0.3 us for the
 // LDS tile alone, 0.9-1.4 us through one L2, 2.0 us over 128 workgroups on all
 // XCDs; from 18 qubits the exchanged bytes (8 partners of 8 B per amplitude:
-// 67 MB per term at 20 qubits, 9.5 TB/s).  The passes it replaces paid a launch
+// 67 MB per term at 20 qubits, 10.5 TB/s).  The passes it replaces paid a launch
 // and a round trip of every vector per term (launch_resident lists both).
 // BLOB = PutBlob (one workgroup): the coefficients and, behind them, (h, J) come
 // with the launch.
@@ -264,7 +282,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
     if constexpr (INLINE) {
         for (int i = tid; i < PutBlob::WORDS; i += NT) words[i] = blob.v[i];
         coef = reinterpret_cast<const C *>(words);
-        hJ = reinterpret_cast<const double *>(coef + a.K + 1);
+        hJ = reinterpret_cast<const double *>(coef + a.first.K + 1);
         __syncthreads();
     }
     if (!a.diag) en.template build<NT>(hJ, n, w);
@@ -299,10 +317,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
     const uint32_t base = (uint32_t)w << T;
     auto inside = [&](int q) { return !GUARD || (uint32_t)(q * NT + tid) * VE < (1u << n); };
     C ck{R(0), R(0)};   // lane l: c_{64 i + l}
-    auto load_coef = [&](int k) {
-        const int i = (k & ~63) + lane;
-        if (i <= a.K) ck = coef[i];
-    };
     auto lane_value = [&](R x, int l) -> R {
         if constexpr (sizeof(R) == 4) {
             return __builtin_bit_cast(R, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
@@ -313,29 +327,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
             return __builtin_bit_cast(R, ((uint64_t)hi << 32) | lo);
         }
     };
-    load_coef(a.K);
-    const R cKr = lane_value(ck.x, a.K & 63), cKi = lane_value(ck.y, a.K & 63);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-#pragma unroll
-        for (int v = 0; v < VE; ++v) {
-            ps[q].v[v] = C{R(0), R(0)};
-            b2[q].v[v] = C{R(0), R(0)};
-            d[q][v] = R(0);
-        }
         if (inside(q)) {
-            const uint32_t z = base + (uint32_t)(q * NT + tid) * VE;
-            ps[q] = ld_v<R, false>(a.psi + z);
+            ps[q] = ld_v<R, false>(a.psi + base + (uint32_t)(q * NT + tid) * VE);
+        } else {
 #pragma unroll
-            for (int v = 0; v < VE; ++v) {
-                const double E = a.diag ? (double)a.diag[z + v] : en.at(n, z + v - base);
-                d[q][v] = (R)((E - a.c) * a.inv_r);
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < VE; ++v) {
-            const C p = ps[q].v[v];
-            b1[q].v[v] = C{fmad(cKr, p.x, -(cKi * p.y)), fmad(cKr, p.y, cKi * p.x)};
+            for (int v = 0; v < VE; ++v) ps[q].v[v] = C{R(0), R(0)};
         }
     }
 
@@ -367,100 +365,128 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
-    publish();
 
-    for (int k = a.K - 1; k >= 0; --k) {
-        if ((k & 63) == 63) load_coef(k);
-        const R cr = lane_value(ck.x, k & 63), ci = lane_value(ck.y, k & 63);
-        const R scale = (k == 0) ? R(1) : a.two;
-        R sr[PER][VE], si[PER][VE];
+    for (int step = 0; step < a.nsteps; ++step) {
+        ResStep<R> st = a.first;
+        if (step > 0) st = wave_uniform(a.more[step - 1]);
+        auto load_coef = [&](int k) {
+            const int i = (k & ~63) + lane;
+            if (i <= st.K) ck = coef[st.coef + i];
+        };
+        load_coef(st.K);
+        const R cKr = lane_value(ck.x, st.K & 63), cKi = lane_value(ck.y, st.K & 63);
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
-            if constexpr (VE == 2) {
-                sr[q][0] = b1[q].v[1].x;
-                si[q][0] = b1[q].v[1].y;
-                sr[q][VE - 1] = b1[q].v[0].x;
-                si[q][VE - 1] = b1[q].v[0].y;
-            } else {
-                sr[q][0] = R(0);
-                si[q][0] = R(0);
-            }
-            auto add = [&](const V &x) {
+            const uint32_t z = base + (uint32_t)(q * NT + tid) * VE;
 #pragma unroll
-                for (int v = 0; v < VE; ++v) {
-                    sr[q][v] += x.v[v].x;
-                    si[q][v] += x.v[v].y;
+            for (int v = 0; v < VE; ++v) {
+                const C p = ps[q].v[v];
+                b1[q].v[v] = C{fmad(cKr, p.x, -(cKi * p.y)), fmad(cKr, p.y, cKi * p.x)};
+                b2[q].v[v] = C{R(0), R(0)};
+                d[q][v] = R(0);
+                if (inside(q)) {
+                    const double E = a.diag ? (double)a.diag[z + v] : en.at(n, z + v - base);
+                    d[q][v] = (R)((E - st.c) * st.inv_r);
                 }
-            };
-#pragma unroll
-            for (int j = 0; j < QB; ++j) add(b1[q ^ (1 << j)]);
-            // lane bits 0, 1 and 3 within the row (DPP), the others from the LDS tile
-            add(lane_flip<R, 0xb1>(b1[q]));    // quad_perm 1 0 3 2
-            add(lane_flip<R, 0x4e>(b1[q]));    // quad_perm 2 3 0 1
-            add(lane_flip<R, 0x128>(b1[q]));   // row_ror 8
-#pragma unroll
-            for (int j = 2; j < LT; ++j)
-                if (j != 3) add(lds[t & 1][(q * NT + tid) ^ (1 << j)]);
-        }
-        if constexpr (HC > 0) {
-            if (!lost) {
-                int left = RES_POLLS;
-                while (__any(lane < HC && __hip_atomic_load(peer, __ATOMIC_RELAXED, QW_AGENT) < t))
-                    if (--left == 0) { lost = true; break; }
             }
-            asm volatile("" ::: "memory");
+        }
+        if (st.K > 0) publish();
+        for (int k = st.K - 1; k >= 0; --k) {
+            if ((k & 63) == 63) load_coef(k);
+            const R cr = lane_value(ck.x, k & 63), ci = lane_value(ck.y, k & 63);
+            const R scale = (k == 0) ? R(1) : a.two;
+            R sr[PER][VE], si[PER][VE];
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
-                V x[HC > 0 ? HC : 1];
-#pragma unroll
-                for (int j = 0; j < HC; ++j) {
-                    // partner's tile in the scalar offset: one vector offset for all of them
-                    const int so = (int)((((uint32_t)w ^ (1u << j)) << T) * sizeof(C));
-                    const qw_i4 y = __builtin_amdgcn_raw_buffer_load_b128((t & 1) ? rs1 : rs0, (q * NT + tid) * 16,
-                                                                          so, SC1);
-                    x[j] = __builtin_bit_cast(V, y);
+                if constexpr (VE == 2) {
+                    sr[q][0] = b1[q].v[1].x;
+                    si[q][0] = b1[q].v[1].y;
+                    sr[q][VE - 1] = b1[q].v[0].x;
+                    si[q][VE - 1] = b1[q].v[0].y;
+                } else {
+                    sr[q][0] = R(0);
+                    si[q][0] = R(0);
                 }
-#pragma unroll
-                for (int j = 0; j < HC; ++j)
+                auto add = [&](const V &x) {
 #pragma unroll
                     for (int v = 0; v < VE; ++v) {
-                        sr[q][v] += x[j].v[v].x;
-                        si[q][v] += x[j].v[v].y;
+                        sr[q][v] += x.v[v].x;
+                        si[q][v] += x.v[v].y;
                     }
+                };
+#pragma unroll
+                for (int j = 0; j < QB; ++j) add(b1[q ^ (1 << j)]);
+                // lane bits 0, 1 and 3 within the row (DPP), the others from the LDS tile
+                add(lane_flip<R, 0xb1>(b1[q]));    // quad_perm 1 0 3 2
+                add(lane_flip<R, 0x4e>(b1[q]));    // quad_perm 2 3 0 1
+                add(lane_flip<R, 0x128>(b1[q]));   // row_ror 8
+#pragma unroll
+                for (int j = 2; j < LT; ++j)
+                    if (j != 3) add(lds[t & 1][q * NT + (tid ^ (1 << j))]);
             }
+            if constexpr (HC > 0) {
+                if (!lost) {
+                    int left = RES_POLLS;
+                    while (__any(lane < HC && __hip_atomic_load(peer, __ATOMIC_RELAXED, QW_AGENT) < t))
+                        if (--left == 0) { lost = true; break; }
+                }
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int q = 0; q < PER; ++q) {
+                    V x[HC > 0 ? HC : 1];
+#pragma unroll
+                    for (int j = 0; j < HC; ++j) {
+                        // partner's tile in the scalar offset: one vector offset for all of them
+                        const int so = (int)((((uint32_t)w ^ (1u << j)) << T) * sizeof(C));
+                        const qw_i4 y = __builtin_amdgcn_raw_buffer_load_b128((t & 1) ? rs1 : rs0, (q * NT + tid) * 16,
+                                                                              so, SC1);
+                        x[j] = __builtin_bit_cast(V, y);
+                    }
+#pragma unroll
+                    for (int j = 0; j < HC; ++j)
+#pragma unroll
+                        for (int v = 0; v < VE; ++v) {
+                            sr[q][v] += x[j].v[v].x;
+                            si[q][v] += x[j].v[v].y;
+                        }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+#pragma unroll
+                for (int v = 0; v < VE; ++v) {
+                    const C b = b1[q].v[v], s = b2[q].v[v], p = ps[q].v[v];
+                    const R hr = fmad(d[q][v], b.x, st.g * sr[q][v]), hi = fmad(d[q][v], b.y, st.g * si[q][v]);
+                    const R tr = fmad(scale, hr, -(a.sub * s.x)), ti = fmad(scale, hi, -(a.sub * s.y));
+                    b2[q].v[v] = C{tr + fmad(cr, p.x, -(ci * p.y)), ti + fmad(cr, p.y, ci * p.x)};
+                }
+            // b2 holds b_k: the two swap roles; amplitudes beyond n stay zero
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                if (!inside(q))
+#pragma unroll
+                    for (int v = 0; v < VE; ++v) b2[q].v[v] = C{R(0), R(0)};
+                const V x = b1[q];
+                b1[q] = b2[q];
+                b2[q] = x;
+            }
+            if (k > 0) publish();
         }
 #pragma unroll
         for (int q = 0; q < PER; ++q)
 #pragma unroll
             for (int v = 0; v < VE; ++v) {
-                const C b = b1[q].v[v], s = b2[q].v[v], p = ps[q].v[v];
-                const R hr = fmad(d[q][v], b.x, a.g * sr[q][v]), hi = fmad(d[q][v], b.y, a.g * si[q][v]);
-                const R tr = fmad(scale, hr, -(a.sub * s.x)), ti = fmad(scale, hi, -(a.sub * s.y));
-                b2[q].v[v] = C{tr + fmad(cr, p.x, -(ci * p.y)), ti + fmad(cr, p.y, ci * p.x)};
+                const C y = b1[q].v[v];
+                ps[q].v[v] = C{fmad(st.pr, y.x, -(st.pi * y.y)), fmad(st.pr, y.y, st.pi * y.x)};
             }
-        // b2 holds b_k: the two swap roles; amplitudes beyond n stay zero
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            if (!inside(q))
-#pragma unroll
-                for (int v = 0; v < VE; ++v) b2[q].v[v] = C{R(0), R(0)};
-            const V x = b1[q];
-            b1[q] = b2[q];
-            b2[q] = x;
-        }
-        if (k > 0) publish();
     }
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         if (!inside(q)) continue;
-        V o;
 #pragma unroll
-        for (int v = 0; v < VE; ++v) {
-            const C y = b1[q].v[v];
-            o.v[v] = C{fmad(a.pr, y.x, -(a.pi * y.y)), fmad(a.pr, y.y, a.pi * y.x)};
-            if (lost) o.v[v] = C{R(NAN), R(NAN)};   // a wave that all were waiting for is gone
-        }
-        st_v<R, false>(a.out + base + (uint32_t)(q * NT + tid) * VE, o);
+        for (int v = 0; v < VE; ++v)
+            if (lost) ps[q].v[v] = C{R(NAN), R(NAN)};   // a wave that all were waiting for is gone
+        st_v<R, false>(a.out + base + (uint32_t)(q * NT + tid) * VE, ps[q]);
     }
 }
 
@@ -536,7 +562,7 @@ static hipError_t launch_resident(const ResArgs<R> &a, hipStream_t s, const PutB
         case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s, blob);      // 2.60 (6.6)
         case 18: return res_launch<R, 10, 256, 8, 1, 4, false>(a, s, blob);     // 3.78 (7.6)
         case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob);      // 5.56 (9.7)
-        case 20: return res_launch<R, 12, 512, 8, 1, 1, true>(a, s, blob);      // 7.09 (9.6)
+        case 20: return res_launch<R, 12, 512, 8, 1, 1, true>(a, s, blob);      // 6.40 (9.6)
         default: return res_launch<R, 7, 64, 0, 1, 1, false>(a, s, blob);       // 0.29 (1.2)
         }
     } else {
@@ -553,7 +579,7 @@ static hipError_t launch_resident(const ResArgs<R> &a, hipStream_t s, const PutB
         case 16: return res_launch<R, 8, 256, 8, 1, 4, false>(a, s, blob);      // 2.52 (9.1)
         case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s, blob);      // 3.60 (10.3)
         case 18: return res_launch<R, 10, 1024, 8, 1, 1, true>(a, s, blob);     // 5.43 (12.3)
-        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob);      // 6.55 (13.0)
+        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob);      // 6.35 (13.0)
         default: return res_launch<R, 6, 64, 0, 1, 1, false>(a, s, blob);       // 0.25 (1.1)
         }
     }

@@ -86,6 +86,49 @@ def test_long_coefficient_arrays(env, n, prec, K):
     assert _rel(y.cpu().numpy().astype(np.complex128), ref) <= bar
 
 
+@pytest.mark.parametrize("prec,n", [(64, 3), (64, 11), (64, 13), (64, 18), (64, 20), (128, 9), (128, 12), (128, 17)])
+@pytest.mark.parametrize("steps", [1, 2, 3, 19, 40])
+def test_chained_exponentials(env, prec, n, steps):
+    """An anneal's exponentials several to a launch (2, 4, 4 + 2, 4 + 32 + 2, 4 + 32
+    + 32 + 12): against the same exponentials as single calls on scaled couplings."""
+    torch, qw = env
+    h, J = synth.sk_instance(n, 21)
+    x = torch.as_tensor(synth.random_state(n, 22)).to(torch.complex64 if prec == 64 else torch.complex128).cuda()
+    T, tol = 0.9, 1e-6 if prec == 64 else 1e-11
+    y, info, sizes = qw.anneal_cfet4(x, h, J, [0.2, 0.8], [1.0, -0.9], T, steps=steps, tol=tol)
+    assert info["exponentials"] == 2 * steps and len(sizes) == steps
+    z, t = x, 0.0
+    r3 = np.sqrt(3.0)
+    for hs in sizes:
+        s1, s2 = (t + (0.5 - r3 / 6) * hs) / T, (t + (0.5 + r3 / 6) * hs) / T
+        for w1, w2 in ((0.25 + r3 / 6, 0.25 - r3 / 6), (0.25 - r3 / 6, 0.25 + r3 / 6)):
+            al = w1 * (0.2 + 0.8 * s1) + w2 * (0.2 + 0.8 * s2)
+            be = w1 * (1.0 - 0.9 * s1) + w2 * (1.0 - 0.9 * s2)
+            z, _ = qw.expm_action(z, be, hs, h=al * h, J=al * J, tol=0.5 * tol * hs / T)
+        t += hs
+    # the truncation budget of the anneal, and the rounding of as many single calls
+    bar = 2 * tol + (2e-6 if prec == 64 else 1e-13)
+    assert float(torch.linalg.vector_norm(y - z) / torch.linalg.vector_norm(z)) <= bar
+
+
+@pytest.mark.parametrize("prec,n", [(64, 13), (64, 17), (128, 14)])
+def test_one_workgroup_takes_over_a_chain(env, prec, n):
+    torch, qw = env
+    h, J = synth.sk_instance(n, 31)
+    x = torch.as_tensor(synth.random_state(n, 32)).to(torch.complex64 if prec == 64 else torch.complex128).cuda()
+    run = lambda out: qw.anneal_cfet4(x, h, J, [0.0, 1.0], [1.0, -1.0], 0.5, steps=4, tol=1e-5, out=out)[0]  # noqa: E731
+    y = run(None)
+    lib = qw.lib()
+    lib.qw_debug_start_patience.argtypes = [ctypes.c_int]
+    lib.qw_debug_start_patience(0)
+    try:
+        z = run(x)   # in place
+    finally:
+        lib.qw_debug_start_patience(-1)
+    # the same series, summed in another order
+    assert float(torch.linalg.vector_norm(y - z) / torch.linalg.vector_norm(y)) <= (4e-6 if prec == 64 else 1e-13)
+
+
 @pytest.mark.parametrize("n", [10, 14, 18, 20])
 def test_recorded_into_a_graph(env, n):
     """A polynomial with given shift and radius on a caller diagonal records into
