@@ -19,6 +19,7 @@
 // forward sweep.  dE/dh, dE/dJ follow from G_i = sum_s dL/dd~_{s,i}/r_s +
 // |psi_S,i|^2 by a Walsh-type reduction over the basis states.
 #include "qw_kernels.h"
+#include "qw_resident.h"
 
 namespace qw {
 
@@ -49,36 +50,71 @@ struct AdjArgs {
     int L, g0, h;
 };
 
-// One element of the first pass of step k: the start of beta_{k+1} and the
-// accumulations that use beta_k (b = beta_k, p = beta_{k-1}, bx = b_{k+1},
-// x = v, (sr, si) = flips of beta_k over the pass's group).
-__device__ __forceinline__ float2 adj_start_elem(const AdjStep &s, float dscale, float g, float er, float2 b,
-                                                 float2 p, float2 bx, float2 x, float sr, float si, float2 &vb,
-                                                 float &gg, double &dt, double &dg)
+// Element arithmetic of the adjoint.  Every fused multiply-add is explicit and
+// nothing else is contracted, so that all kernels round alike whatever the compiler
+// makes of their surroundings.
+
+// Re(dc conj(b) x) = dcr Re(conj(b) x) - dci Im(conj(b) x), added to dt.
+__device__ __forceinline__ void dt_elem(double dcr, double dci, float2 b, float2 x, double &dt)
 {
-    dg += s.wk * (double)(sr * bx.x + si * bx.y);
-    const float d = er * dscale;
-    float2 o;
-    o.x = s.scale * (d * b.x + g * sr) - p.x;
-    o.y = s.scale * (d * b.y + g * si) - p.y;
-    vb.x += s.ckr * b.x + s.cki * b.y;
-    vb.y += s.ckr * b.y - s.cki * b.x;
-    gg += s.gw * (b.x * bx.x + b.y * bx.y);
-    const double pr = (double)b.x * x.x + (double)b.y * x.y;
-    const double pi = (double)b.x * x.y - (double)b.y * x.x;
-    dt += s.dcr * pr - s.dci * pi;
-    return o;
+#pragma clang fp contract(off)
+    const double bx = b.x, by = b.y, xx = x.x, xy = x.y;
+    const double pr = fmad(bx, xx, by * xy), pi = fmad(bx, xy, -(by * xx));
+    dt += fmad(dcr, pr, -(dci * pi));
 }
 
-// One element of a later pass of step k: p = partial beta_{k+1}.
+// vbar += conj(c) b with conj(c) = (cr, -ci) given as c.
+__device__ __forceinline__ void vbar_elem(float cr, float ci, float2 b, float2 &vb)
+{
+#pragma clang fp contract(off)
+    vb.x += fmad(cr, b.x, ci * b.y);
+    vb.y += fmad(cr, b.y, -(ci * b.x));
+}
+
+// The accumulations of step k that need beta_k alone (b = beta_k, bx = b_{k+1}, x = v).
+__device__ __forceinline__ void adj_sums_elem(const AdjStep &s, float2 b, float2 bx, float2 x, float2 &vb, float &gg,
+                                              double &dt)
+{
+    vbar_elem(s.ckr, s.cki, b, vb);
+    gg = fmad(s.gw, fmad(b.x, bx.x, b.y * bx.y), gg);
+    dt_elem(s.dcr, s.dci, b, x, dt);
+}
+
+// The first pass of step k: the start of beta_{k+1} (p = beta_{k-1}, (sr, si) =
+// flips of beta_k over the pass's group).
+__device__ __forceinline__ float2 adj_start_elem(const AdjStep &s, float dscale, float g, float er, float2 b,
+                                                 float2 p, float2 bx, float sr, float si, double &dg)
+{
+#pragma clang fp contract(off)
+    dg = fmad(s.wk, (double)fmad(sr, bx.x, si * bx.y), dg);
+    const float d = er * dscale;
+    return make_float2(fmad(s.scale, fmad(g, sr, d * b.x), -p.x), fmad(s.scale, fmad(g, si, d * b.y), -p.y));
+}
+
+// A later pass of step k: p = partial beta_{k+1}.
 __device__ __forceinline__ float2 adj_add_elem(const AdjStep &s, float g, float2 p, float2 bx, float sr, float si,
                                                double &dg)
 {
-    dg += s.wk * (double)(sr * bx.x + si * bx.y);
-    float2 o;
-    o.x = p.x + s.scale * g * sr;
-    o.y = p.y + s.scale * g * si;
-    return o;
+#pragma clang fp contract(off)
+    dg = fmad(s.wk, (double)fmad(sr, bx.x, si * bx.y), dg);
+    const float sg = s.scale * g;
+    return make_float2(fmad(sg, sr, p.x), fmad(sg, si, p.y));
+}
+
+// beta_0 = conj(phase) ybar; ph += Im(conj(ybar) psi_s).
+__device__ __forceinline__ float2 beta0_elem(float cr, float ci, float2 yb, float2 p, double &ph)
+{
+#pragma clang fp contract(off)
+    ph += fmad((double)yb.x, (double)p.y, -((double)yb.y * p.x));
+    return make_float2(fmad(cr, yb.x, -(ci * yb.y)), fmad(ci, yb.x, cr * yb.y));
+}
+
+// The last step: vbar += conj(c_K) beta_K, dt += Re(dc_K/dt conj(beta_K) v).
+__device__ __forceinline__ void adj_last_elem(float cr, float ci, double dcr, double dci, float2 b, float2 x,
+                                              float2 &vb, double &dt)
+{
+    vbar_elem(cr, ci, b, vb);
+    dt_elem(dcr, dci, b, x, dt);
 }
 
 __device__ inline void block_add2(double x, double y, double *out)
@@ -176,10 +212,11 @@ __global__ void __launch_bounds__(NT) k_adj_pass(AdjArgs a)
             for (int v = 0; v < VE; ++v) {
                 float sr, si;
                 flips(e + v, sr, si);
-                if constexpr (START)
-                    out.v[v] = adj_start_elem(a.st, a.dscale, a.g, er[q][v], own[q].v[v], pv[q].v[v], bn[q].v[v],
-                                              vv[q].v[v], sr, si, vb[q].v[v], gg[q][v], acc_dt, acc_dg);
-                else
+                if constexpr (START) {
+                    adj_sums_elem(a.st, own[q].v[v], bn[q].v[v], vv[q].v[v], vb[q].v[v], gg[q][v], acc_dt);
+                    out.v[v] = adj_start_elem(a.st, a.dscale, a.g, er[q][v], own[q].v[v], pv[q].v[v], bn[q].v[v], sr,
+                                              si, acc_dg);
+                } else
                     out.v[v] = adj_add_elem(a.st, a.g, pv[q].v[v], bn[q].v[v], sr, si, acc_dg);
             }
             if constexpr (MODE == AM_FUSED) {
@@ -223,8 +260,9 @@ __global__ void __launch_bounds__(NT) k_adj_pass(AdjArgs a)
                     float sr, si;
                     flips(e + v, sr, si);
                     float gq = a.G[idx + v];
+                    adj_sums_elem(a.st2, pv[q].v[v], bx.v[v], x.v[v], vbq.v[v], gq, dt2);
                     out.v[v] = adj_start_elem(a.st2, a.dscale, a.g, a.erel[idx + v], pv[q].v[v], own[q].v[v],
-                                              bx.v[v], x.v[v], sr, si, vbq.v[v], gq, dt2, dg2);
+                                              bx.v[v], sr, si, dg2);
                     a.G[idx + v] = gq;
                 }
                 st_v<float, STREAM>(a.dst + idx, pv[q]);
@@ -258,14 +296,9 @@ __global__ void __launch_bounds__(256) k_adj_last(EwArgs a)
     const uint64_t base = (uint64_t)blockIdx.x * a.TE;
     double acc = 0.0;
     for (uint32_t e = threadIdx.x; e < a.TE; e += blockDim.x) {
-        const float2 b = a.x[base + e], x = a.v[base + e];
         float2 vb = a.y[base + e];
-        vb.x += a.cr * b.x + a.ci * b.y;
-        vb.y += a.cr * b.y - a.ci * b.x;
+        adj_last_elem(a.cr, a.ci, a.dcr, a.dci, a.x[base + e], a.v[base + e], vb, acc);
         a.y[base + e] = vb;
-        const double pr = (double)b.x * x.x + (double)b.y * x.y;
-        const double pi = (double)b.x * x.y - (double)b.y * x.x;
-        acc += a.dcr * pr - a.dci * pi;
     }
     block_add2(acc, 0.0, a.part + 2 * blockIdx.x);
 }
@@ -292,9 +325,7 @@ __global__ void __launch_bounds__(256) k_beta0(EwArgs a)
     const uint64_t base = (uint64_t)blockIdx.x * a.TE;
     double acc = 0.0;
     for (uint32_t e = threadIdx.x; e < a.TE; e += blockDim.x) {
-        const float2 yb = a.x[base + e], p = a.v[base + e];
-        acc += (double)yb.x * p.y - (double)yb.y * p.x;   // Im(conj(ybar) psi)
-        a.y[base + e] = make_float2(a.cr * yb.x - a.ci * yb.y, a.cr * yb.y + a.ci * yb.x);
+        a.y[base + e] = beta0_elem(a.cr, a.ci, a.x[base + e], a.v[base + e], acc);
         a.z[base + e] = make_float2(0.f, 0.f);
     }
     block_add2(a.c * acc, 0.0, a.part + 2 * blockIdx.x);
@@ -373,6 +404,517 @@ __global__ void __launch_bounds__(256) k_walsh_reduce(const double *in, int ntil
 }
 
 // ---------------------------------------------------------------------------
+// The sweeps in one launch each
+// ---------------------------------------------------------------------------
+
+static constexpr int GRES_NMIN = 8, GRES_NMAX = 20;
+static constexpr int GRES_MAXW = 256;      // workgroups of a launch
+static constexpr uint64_t GRES_NONE = ~uint64_t(0);
+
+struct GradSeg {
+    float inv_r, g, ph_r, ph_i;
+    int K, coef;           // degree, place of c_0 .. c_K (and dc_k, and where b_k goes)
+    int win, nwin;         // its windows in the list
+};
+struct GradWin {
+    int B, T;              // b_B .. b_T
+    int fresh;             // 1: recomputed from b_K = c_K v, 0: from x1, x2, -1: stored by the forward sweep
+    int pad;
+    uint64_t x1, x2, at;   // byte offsets in the workspace: b_{T+1}, b_{T+2} (GRES_NONE: zero), b_B
+};
+
+struct GradRes {
+    char *ws;
+    float2 *states;            // psi_s of the launch's first segment; psi_{s+1} .. behind it
+    float2 *X0, *X1;           // exchange buffers
+    float2 *vbar;
+    float *G;
+    const float *erel;
+    const GradSeg *seg;        // of the launch's first segment
+    const GradWin *win;
+    const float2 *coef;        // c_k
+    const double2 *dcoef;      // r dc_k/da
+    const uint64_t *place;     // byte offset of b_k, GRES_NONE: an exchange buffer
+    double *part;              // per segment and workgroup: dt, dgamma, phase sums
+    int *start, *flags;        // 2 and RES_MAXFLAGS lines, cleared before the launch
+    double c;
+    int nseg;
+    int stride, sel;           // workgroups with blockIdx.x % stride == sel take part
+};
+
+// One sweep over all segments by W = 2^HC workgroups that hold one tile of 2^T
+// consecutive amplitudes each: the two vectors of the recurrence and, in the
+// backward sweep, beta_k and beta_{k-1} in registers, psi, vbar and G of the
+// backward sweep in LDS (in registers as well they spilled: 14.9 ms for the call
+// below).  Per term only b_{k+1} (beta_k) travels between the workgroups, as in
+// k_resident, whose exchange, flags and flips these are.  The launch is
+// cooperative, so every wait ends.  The vectors that the backward sweep needs again
+// are exchange buffers themselves: b_k is written to the place where it is to stay.
+// The sums over beta_k alone are formed while its flags travel.
+//
+// Every sum has the operands and the order of the passes: an element's flips are
+// summed in increasing bit order in two groups, the tile and HA cross bits (up to
+// bit 12 or 13) and, from 14 qubits, the HB bits above, and term by term the groups
+// take turns in coming first.  So states, b_k, beta_k, vbar and G are those of the
+// passes bit for bit (dt and dgamma add their doubles in another order).  The
+// rounding of the forward states is most of the error of dE/dt, which another
+// order would redraw.
+//
+// What bounds it: as in k_resident, the round trip of an exchange, and from 18
+// qubits the exchanged bytes: 20 qubits take 6.6 us per term forwards and 13.6
+// backwards (b_k again and an adjoint step), where the passes took 9.8 and 28.5.
+template <int T, int NT, int HC, bool BACK> __global__ void __launch_bounds__(NT) k_grad_resident(GradRes a)
+{
+    using C = float2;
+    using V = CVec<float>;
+    constexpr int VE = V::N;
+    constexpr int PER = (1 << T) / (NT * VE);
+    constexpr int LT = (NT == 1024) ? 10 : (NT == 512) ? 9 : (NT == 256) ? 8 : (NT == 128) ? 7 : 6;
+    constexpr int QB = (PER == 8) ? 3 : (PER == 4) ? 2 : (PER == 2) ? 1 : 0;
+    static_assert((1 << LT) == NT && PER >= 1 && (1 << QB) == PER, "tile shape");
+    constexpr int n = T + HC, W = 1 << HC, NW = NT / 64;
+    constexpr int HB = (n > GTB) ? n - TB_NARROW : 0, HA = HC - HB;   // cross bits of the two groups
+    static_assert(W * NW <= RES_MAXFLAGS && HA >= 0, "one flag per wave");
+    constexpr int SC1 = 16;   // cache policy: past the L1, and (stores) through to memory
+    constexpr int BYTES = (int)(sizeof(C) << n);
+    __shared__ V lds[2][PER * NT];
+    __shared__ int go;
+    __shared__ double red[BACK ? NW : 1][3];
+    // backward: vbar and G, each thread's own; a term needs them only while it waits
+    __shared__ V vbl[BACK ? PER * NT : 1];
+    __shared__ C ggl[BACK ? PER * NT : 1];
+    __shared__ V psl[BACK ? PER * NT : 1];   // and v
+
+    int w = 0;
+    if constexpr (HC > 0) {
+        if ((int)(blockIdx.x % a.stride) != a.sel) return;
+        w = __builtin_amdgcn_readfirstlane(blockIdx.x / a.stride);
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    bool near = false, lost = false;
+    if constexpr (HC > 0) {
+        if (tid == 0) {
+            const int xcc = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, 4 bits
+            (void)__hip_atomic_fetch_or(a.start + RES_LINE, 1 << xcc, __ATOMIC_RELAXED, QW_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const bool ok = res_join(a.start, W, RES_POLLS);
+            const int m = __hip_atomic_load(a.start + RES_LINE, __ATOMIC_RELAXED, QW_AGENT);
+            go = !ok ? 0 : (m & (m - 1)) == 0 ? 2 : 1;
+        }
+        __syncthreads();
+        const int ok = __builtin_amdgcn_readfirstlane(go);
+        near = (ok == 2);
+        lost = (ok == 0);
+    }
+
+    const uint32_t base = (uint32_t)w << T;
+    auto at = [&](int q) { return base + (uint32_t)(q * NT + tid) * VE; };
+    auto rsrc = [&](const void *p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, BYTES, 0x00027000); };
+    auto own = [&](const void *p, int q) {   // a vector of this tile that the launch may have written
+        return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc(p), (q * NT + tid) * 16,
+                                                                            (int)(base * sizeof(C)), SC1));
+    };
+    auto keep = [&](const V (&x)[PER], void *p) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const qw_i4 y = __builtin_bit_cast(qw_i4, x[q]);
+            const int vo = (q * NT + tid) * 16, so = (int)(base * sizeof(C));
+            if (near) __builtin_amdgcn_raw_buffer_store_b128(y, rsrc(p), vo, so, 0);
+            else __builtin_amdgcn_raw_buffer_store_b128(y, rsrc(p), vo, so, SC1);
+        }
+    };
+    const int *peer = a.flags + (size_t)(((w ^ (lane < HC ? 1 << lane : 0)) * NW + wave) * RES_LINE);
+    int *mine = a.flags + (size_t)((w * NW + wave) * RES_LINE);
+    int t = 0;
+    auto ring = [&]() -> void * { return (t & 1) ? a.X0 : a.X1; };   // of the next round
+    // x to the LDS tile and to p, where its partners look for it (there already
+    // unless `store`)
+    auto publish = [&](const V (&x)[PER], void *p, bool store) {
+        ++t;
+        if (HC > 0 || BACK)
+            if (store) keep(x, p);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) lds[t & 1][q * NT + tid] = x[q];
+        if constexpr (HC > 0) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the wave's part has arrived
+            if (lane == 0) __hip_atomic_store(mine, t, __ATOMIC_RELAXED, QW_AGENT);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    auto add = [](V &s, const V &y) {
+#pragma unroll
+        for (int v = 0; v < VE; ++v) {
+            s.v[v].x += y.v[v].x;
+            s.v[v].y += y.v[v].y;
+        }
+    };
+    // Flips of the published x, whose other tiles are at p, handed to elem(q, the
+    // first group's sum, the second's).  The partners' vectors of QG of a thread's
+    // own are under way at a time: with two or four instead of one of its four, 20
+    // qubits spilled in the terms (16 segments in 12.6 and 13.0 ms against 12.1).
+    constexpr int QG = (PER > 2) ? 1 : PER;
+    auto flips = [&](const V (&x)[PER], const void *p, auto elem) {
+        V sa[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            sa[q].v[0] = x[q].v[1];
+            sa[q].v[1] = x[q].v[0];
+            add(sa[q], lane_flip<float, 0xb1>(x[q]));    // quad_perm 1 0 3 2
+            add(sa[q], lane_flip<float, 0x4e>(x[q]));    // quad_perm 2 3 0 1
+            add(sa[q], lds[t & 1][q * NT + (tid ^ 4)]);
+            add(sa[q], lane_flip<float, 0x128>(x[q]));   // row_ror 8
+#pragma unroll
+            for (int j = 4; j < LT; ++j) add(sa[q], lds[t & 1][q * NT + (tid ^ (1 << j))]);
+#pragma unroll
+            for (int j = 0; j < QB; ++j) add(sa[q], x[q ^ (1 << j)]);
+            if (PER > QG && (q + 1) % QG == 0) __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (HC > 0) {
+            if (!lost) {
+                int left = RES_POLLS;
+                while (__any(lane < HC && __hip_atomic_load(peer, __ATOMIC_RELAXED, QW_AGENT) < t))
+                    if (--left == 0) { lost = true; break; }
+            }
+            asm volatile("" ::: "memory");
+        }
+        const auto rs = rsrc(p);
+#pragma unroll
+        for (int q0 = 0; q0 < PER; q0 += QG) {
+            V y[QG][HC > 0 ? HC : 1], sb[QG];
+#pragma unroll
+            for (int q = 0; q < QG; ++q)
+#pragma unroll
+                for (int j = 0; j < HC; ++j) {
+                    const int so = (int)((((uint32_t)w ^ (1u << j)) << T) * sizeof(C));
+                    y[q][j] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rs, ((q0 + q) * NT + tid) * 16,
+                                                                                          so, SC1));
+                }
+#pragma unroll
+            for (int q = 0; q < QG; ++q) {
+#pragma unroll
+                for (int v = 0; v < VE; ++v) sb[q].v[v] = C{0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < HC; ++j) add(j < HA ? sa[q0 + q] : sb[q], y[q][j]);
+                elem(q0 + q, sa[q0 + q], sb[q]);
+            }
+            if (PER > QG) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto lane32 = [](float x, int l) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
+    };
+    auto lane64 = [](uint64_t u, int l) {
+        return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
+    };
+
+    V ps[BACK ? 1 : PER];     // v
+    auto v_of = [&](int q) -> V {
+        if constexpr (BACK) return psl[q * NT + tid];
+        else return ps[q];
+    };
+    float er[PER][VE];        // E - c
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+#pragma unroll
+        for (int v = 0; v < VE; ++v) er[q][v] = a.erel[at(q) + v];
+
+    GradSeg sg{};
+    C ck{0.f, 0.f};           // lane l: c_{64 i + l}
+    double dx = 0.0, dy = 0.0;
+    uint64_t pl = 0;
+    // c_k, dc_k (backward) and the places of b_k (forward) of k's 64
+    auto load_terms = [&](int k, bool derivs) {
+        const int i = (k & ~63) + lane;
+        if (i <= sg.K) {
+            ck = a.coef[sg.coef + i];
+            if constexpr (!BACK) pl = a.place[sg.coef + i];
+            else if (derivs) {
+                const double2 d = a.dcoef[sg.coef + i];
+                dx = d.x;
+                dy = d.y;
+            }
+        }
+    };
+    // b_K = c_K v and b_{K+1} = 0
+    auto fresh_start = [&](V (&b1)[PER], V (&b2)[PER]) {
+#pragma clang fp contract(off)
+        const float cr = lane32(ck.x, sg.K & 63), ci = lane32(ck.y, sg.K & 63);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const V x = v_of(q);
+#pragma unroll
+            for (int v = 0; v < VE; ++v) {
+                const C p = x.v[v];
+                b1[q].v[v] = C{fmad(cr, p.x, -(ci * p.y)), fmad(cr, p.y, ci * p.x)};
+                b2[q].v[v] = C{0.f, 0.f};
+            }
+        }
+    };
+    // b_k over b_{k+2} (b2) from the published b_{k+1} (b1)
+    auto term = [&](int k, const V (&b1)[PER], V (&b2)[PER], const void *p) {
+        if ((k & 63) == 63) load_terms(k, false);
+        const float cr = lane32(ck.x, k & 63), ci = lane32(ck.y, k & 63);
+        const float scale = (k == 0) ? 1.f : 2.f, sgg = scale * sg.g;
+        const bool low = HB == 0 || ((sg.K - 1 - k) & 1) == 0;   // the low group first
+        flips(b1, p, [&](int q, const V &sa, const V &sb) {
+#pragma clang fp contract(off)
+            const V pv = v_of(q);
+#pragma unroll
+            for (int v = 0; v < VE; ++v) {
+                const C b = b1[q].v[v], s = b2[q].v[v], x = pv.v[v];
+                const C f1 = low ? sa.v[v] : sb.v[v], f2 = low ? sb.v[v] : sa.v[v];
+                const float d = er[q][v] * sg.inv_r;
+                const float hr = fmad(d, b.x, sg.g * f1.x), hi = fmad(d, b.y, sg.g * f1.y);
+                const float tr = fmad(scale, hr, -s.x), ti = fmad(scale, hi, -s.y);
+                C o{tr + fmad(cr, x.x, -(ci * x.y)), ti + fmad(cr, x.y, ci * x.x)};
+                if constexpr (HB > 0) o = C{fmad(sgg, f2.x, o.x), fmad(sgg, f2.y, o.y)};
+                b2[q].v[v] = o;
+            }
+        });
+    };
+    auto swap = [](V (&x)[PER], V (&y)[PER]) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const V z = x[q];
+            x[q] = y[q];
+            y[q] = z;
+        }
+    };
+    const uint64_t N = uint64_t(1) << n;
+
+    if constexpr (!BACK) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) ps[q] = ld_v<float, false>(a.states + at(q));
+        for (int i = 0; i < a.nseg; ++i) {
+            sg = wave_uniform(a.seg[i]);
+            load_terms(sg.K, false);
+            V b1[PER], b2[PER];
+            auto place = [&](int k) -> void * {
+                const uint64_t o = lane64(pl, k & 63);
+                return o == GRES_NONE ? ring() : a.ws + o;
+            };
+            auto send = [&](int k) -> void * {   // b_k = b1
+                void *p = place(k);
+                if (HC == 0 && lane64(pl, k & 63) != GRES_NONE) keep(b1, p);
+                publish(b1, p, true);
+                return p;
+            };
+            fresh_start(b1, b2);
+            const void *p = send(sg.K);
+            for (int k = sg.K - 1; k >= 0; --k) {
+                term(k, b1, b2, p);
+                swap(b1, b2);
+                if (k > 0) p = send(k);
+            }
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+#pragma unroll
+                for (int v = 0; v < VE; ++v) {
+                    const C y = b1[q].v[v];
+                    ps[q].v[v] = C{fmad(sg.ph_r, y.x, -(sg.ph_i * y.y)), fmad(sg.ph_r, y.y, sg.ph_i * y.x)};
+                    if (lost) ps[q].v[v] = C{NAN, NAN};
+                }
+                st_v<float, false>(a.states + (i + 1) * N + at(q), ps[q]);
+            }
+        }
+    } else {
+        V be[PER], bp[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            vbl[q * NT + tid] = ld_v<float, false>(a.vbar + at(q));
+            ggl[q * NT + tid] = C{a.G[at(q)], a.G[at(q) + 1]};
+        }
+        for (int i = a.nseg - 1; i >= 0; --i) {
+            sg = wave_uniform(a.seg[i]);
+            double sdt = 0.0, sdg = 0.0, sph = 0.0;
+            // beta_0 = conj(phase) ybar
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const V y = ld_v<float, false>(a.states + (i + 1) * N + at(q));
+                const V yb = vbl[q * NT + tid];
+                psl[q * NT + tid] = ld_v<float, false>(a.states + i * N + at(q));
+#pragma unroll
+                for (int v = 0; v < VE; ++v) {
+                    be[q].v[v] = beta0_elem(sg.ph_r, -sg.ph_i, yb.v[v], y.v[v], sph);
+                    bp[q].v[v] = C{0.f, 0.f};
+                }
+                vbl[q * NT + tid] = bp[q];
+            }
+            for (int j = 0; j < sg.nwin; ++j) {
+                const GradWin wn = wave_uniform(a.win[sg.win + j]);
+                char *const win = a.ws + wn.at;
+                auto wat = [&](int k) -> void * { return win + (uint64_t)(k - wn.B) * N * sizeof(C); };
+                if (wn.fresh >= 0) {   // b_T .. b_B again
+                    V b1[PER], b2[PER];
+                    const int k0 = wn.fresh ? sg.K - 1 : wn.T;
+                    load_terms(wn.fresh ? sg.K : k0, false);
+                    const void *p;
+                    if (wn.fresh) {
+                        fresh_start(b1, b2);
+                        p = wat(sg.K);
+                        // every round is waited for by its partners before the next but
+                        // one writes its buffer, so none is begun that nobody reads
+                        if (k0 >= wn.B) publish(b1, wat(sg.K), true);
+                        else keep(b1, wat(sg.K));
+                    } else {
+                        p = a.ws + wn.x1;
+#pragma unroll
+                        for (int q = 0; q < PER; ++q) {
+                            b1[q] = own(p, q);
+                            if (wn.x2 != GRES_NONE) b2[q] = own(a.ws + wn.x2, q);
+                            else
+#pragma unroll
+                                for (int v = 0; v < VE; ++v) b2[q].v[v] = C{0.f, 0.f};
+                        }
+                        publish(b1, nullptr, false);
+                    }
+                    for (int k = k0; k >= wn.B; --k) {
+                        term(k, b1, b2, p);
+                        swap(b1, b2);
+                        p = wat(k);
+                        if (k > wn.B) publish(b1, wat(k), true);
+                        else keep(b1, wat(k));
+                    }
+                }
+                load_terms(wn.B - 1, true);
+                for (int k = wn.B - 1; k < wn.T; ++k) {
+                    if ((k & 63) == 0) load_terms(k, true);
+                    AdjStep st;
+                    const double wk = (k == 0) ? 1.0 : 2.0;
+                    st.scale = (k == 0) ? 1.f : 2.f;
+                    st.ckr = lane32(ck.x, k & 63);
+                    st.cki = lane32(ck.y, k & 63);
+                    st.gw = (k == 0) ? sg.inv_r : 2.f * sg.inv_r;   // exact: a power of two
+                    st.wk = wk;
+                    st.dcr = __builtin_bit_cast(double, lane64(__builtin_bit_cast(uint64_t, dx), k & 63));
+                    st.dci = __builtin_bit_cast(double, lane64(__builtin_bit_cast(uint64_t, dy), k & 63));
+                    void *const p = ring();
+                    publish(be, p, HC > 0);
+                    V bx[PER];
+#pragma unroll
+                    for (int q = 0; q < PER; ++q) bx[q] = own(wat(k + 1), q);
+#pragma unroll
+                    for (int q = 0; q < PER; ++q) {
+                        V vb = vbl[q * NT + tid];
+                        C gg = ggl[q * NT + tid];
+                        const V pv = psl[q * NT + tid];
+                        adj_sums_elem(st, be[q].v[0], bx[q].v[0], pv.v[0], vb.v[0], gg.x, sdt);
+                        adj_sums_elem(st, be[q].v[1], bx[q].v[1], pv.v[1], vb.v[1], gg.y, sdt);
+                        vbl[q * NT + tid] = vb;
+                        ggl[q * NT + tid] = gg;
+                        if (PER > 2) __builtin_amdgcn_sched_barrier(0);
+                    }
+                    const bool low = HB == 0 || (k & 1) == 0;
+                    flips(be, p, [&](int q, const V &sa, const V &sb) {
+#pragma unroll
+                        for (int v = 0; v < VE; ++v) {
+                            const C f1 = low ? sa.v[v] : sb.v[v], f2 = low ? sb.v[v] : sa.v[v];
+                            C o = adj_start_elem(st, sg.inv_r, sg.g, er[q][v], be[q].v[v], bp[q].v[v], bx[q].v[v],
+                                                 f1.x, f1.y, sdg);
+                            if constexpr (HB > 0) o = adj_add_elem(st, sg.g, o, bx[q].v[v], f2.x, f2.y, sdg);
+                            bp[q].v[v] = be[q].v[v];
+                            be[q].v[v] = o;
+                        }
+                    });
+                }
+            }
+            load_terms(sg.K, true);
+            {
+                const float cr = lane32(ck.x, sg.K & 63), ci = lane32(ck.y, sg.K & 63);
+                const double dcr = __builtin_bit_cast(double, lane64(__builtin_bit_cast(uint64_t, dx), sg.K & 63));
+                const double dci = __builtin_bit_cast(double, lane64(__builtin_bit_cast(uint64_t, dy), sg.K & 63));
+#pragma unroll
+                for (int q = 0; q < PER; ++q) {
+                    V vb = vbl[q * NT + tid];
+                    const V pv = psl[q * NT + tid];
+#pragma unroll
+                    for (int v = 0; v < VE; ++v)
+                        adj_last_elem(cr, ci, dcr, dci, be[q].v[v], pv.v[v], vb.v[v], sdt);
+                    vbl[q * NT + tid] = vb;
+                }
+            }
+            sph *= a.c;
+            for (int o = 32; o > 0; o >>= 1) {
+                sdt += __shfl_xor(sdt, o);
+                sdg += __shfl_xor(sdg, o);
+                sph += __shfl_xor(sph, o);
+            }
+            if (lane == 0) {
+                red[wave][0] = lost ? NAN : sdt;
+                red[wave][1] = sdg;
+                red[wave][2] = sph;
+            }
+            __syncthreads();
+            if (tid < 3) {
+                double s = 0.0;
+                for (int j = 0; j < NW; ++j) s += red[j][tid];
+                a.part[((uint64_t)i * W + w) * 3 + tid] = s;
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const C gg = ggl[q * NT + tid];
+            st_v<float, false>(a.vbar + at(q), vbl[q * NT + tid]);
+            a.G[at(q)] = lost ? NAN : gg.x;
+            a.G[at(q) + 1] = lost ? NAN : gg.y;
+        }
+    }
+}
+
+// sums[3 i + j] = sum over the W workgroups of part[3 (i W + w) + j]; one wave each.
+__global__ void __launch_bounds__(64) k_grad_sums(const double *part, int W, double *sums)
+{
+    const double *p = part + (uint64_t)(blockIdx.x / 3) * W * 3 + blockIdx.x % 3;
+    double s = 0.0;
+    for (int w = threadIdx.x; w < W; w += 64) s += p[3 * w];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (threadIdx.x == 0) sums[blockIdx.x] = s;
+}
+
+template <int T, int NT, int HC, int STRIDE> static hipError_t grad_res_launch(GradRes a, bool back, hipStream_t s)
+{
+    static std::atomic<unsigned> turn{0};   // launches take turns over the XCDs
+    a.stride = STRIDE;
+    a.sel = (STRIDE > 1) ? (int)(turn.fetch_add(1, std::memory_order_relaxed) % STRIDE) : 0;
+    const dim3 grid((1u << HC) * STRIDE), block(NT);
+    if constexpr (HC == 0) {
+        if (back) hipLaunchKernelGGL((k_grad_resident<T, NT, HC, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_grad_resident<T, NT, HC, false>), grid, block, 0, s, a);
+        return hipGetLastError();
+    }
+    void *args[] = {&a};
+    const void *f = back ? reinterpret_cast<const void *>(&k_grad_resident<T, NT, HC, true>)
+                         : reinterpret_cast<const void *>(&k_grad_resident<T, NT, HC, false>);
+    return hipLaunchCooperativeKernel(f, grid, block, args, 0, s);
+}
+
+// Shapes of launch_resident's exchanges; milliseconds per call in the comments (3
+// segments of about 30 terms from 8 to 17 qubits and at 19, 4 segments at 16 and
+// 18, 16 segments of 35 terms at 20; windows of 1 to 8, none at 10 and 18), what
+// the passes took in parentheses.  One CU holds one workgroup at 19 and 20 qubits,
+// so like the smaller sizes they are launched cooperatively.
+static hipError_t launch_grad_resident(int n, const GradRes &a, bool back, hipStream_t s)
+{
+    switch (n) {
+    case 8: return grad_res_launch<8, 128, 0, 1>(a, back, s);   // 0.25 (0.85)
+    case 9: return grad_res_launch<9, 256, 0, 1>(a, back, s);   // 0.35 (1.4)
+    case 10: return grad_res_launch<10, 512, 0, 1>(a, back, s);   // 0.28 (0.81)
+    case 11: return grad_res_launch<11, 512, 0, 1>(a, back, s);   // 0.46 (1.4)
+    case 12: return grad_res_launch<8, 128, 4, 8>(a, back, s);   // 0.60 (2.0)
+    case 13: return grad_res_launch<8, 128, 5, 8>(a, back, s);   // 0.79 (3.3)
+    case 14: return grad_res_launch<9, 256, 5, 8>(a, back, s);   // 0.90 (2.9)
+    case 15: return grad_res_launch<10, 256, 5, 8>(a, back, s);   // 0.93 (2.8)
+    case 16: return grad_res_launch<9, 256, 7, 1>(a, back, s);   // 1.30 (3.7)
+    case 17: return grad_res_launch<9, 256, 8, 1>(a, back, s);   // 1.18 (3.1)
+    case 18: return grad_res_launch<10, 256, 8, 1>(a, back, s);   // 1.49 (3.9)
+    case 19: return grad_res_launch<11, 512, 8, 1>(a, back, s);   // 1.93 (4.3)
+    default: return grad_res_launch<12, 512, 8, 1>(a, back, s);  // 12.1 (24.4)
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
 
@@ -387,6 +929,7 @@ struct SegPlan {
 
 struct GradLayout {
     size_t states, erel, A, B, vbar, G, win, ckpt, part, partm, walsh, wres, hj, q, red, mpart, total;
+    size_t sync, segs, wins, coef, dcoef, place, rpart, sums, total_res;   // behind `total`: the one-launch sweeps
     int nwin, nckpt, ntiles_lo, npar;
     bool store;   // every b_k of every segment kept (win holds them all, no recomputation)
 };
@@ -434,6 +977,10 @@ static TileCfg grad_cfg(int n)
     return (c.tb == TB_WIDE) ? TileCfg{GTB, GNT, c.stream} : c;
 }
 
+// Sizes whose sweeps run in one launch each.  Below 8 qubits a wave has lanes to
+// spare; above 20 the backward sweep's vectors exceed the registers.
+static bool grad_resident(int n) { return n >= GRES_NMIN && n <= GRES_NMAX; }
+
 static int grad_window(int ckpt_every, int K) { return (ckpt_every <= 0 || ckpt_every > K) ? K : ckpt_every; }
 
 static GradLayout grad_layout(int n, int S, const int *Kb, int ckpt_every)
@@ -478,7 +1025,63 @@ static GradLayout grad_layout(int n, int S, const int *Kb, int ckpt_every)
     L.red = take(2 * sizeof(double));
     L.mpart = take(2 * sizeof(double) * MAXPART);
     L.total = off;
+    L.total_res = 0;
+    if (grad_resident(n)) {
+        size_t terms = 0, wins = 0;
+        for (int s = 0; s < S; ++s) {
+            const int K = std::max(Kb[s], 1), C = L.store ? K : grad_window(ckpt_every, K);
+            terms += K + 1;
+            wins += (K + C - 1) / C;
+        }
+        L.sync = take(sizeof(int) * RES_LINE * (2 + RES_MAXFLAGS));
+        L.segs = take(sizeof(GradSeg) * S);
+        L.wins = take(sizeof(GradWin) * wins);
+        L.coef = take(sizeof(float2) * terms);
+        L.dcoef = take(sizeof(double2) * terms);
+        L.place = take(sizeof(uint64_t) * terms);
+        L.rpart = take(sizeof(double) * 3 * GRES_MAXW * S);
+        L.sums = take(sizeof(double) * 3 * S);
+        L.total_res = off;
+    }
     return L;
+}
+
+// Segments, windows, coefficients and places of the one-launch sweeps, as they lie
+// from L.segs; `vec_bytes` is the size of a vector.
+static std::vector<char> grad_tables(const GradLayout &L, const std::vector<SegPlan> &seg, size_t vec_bytes)
+{
+    std::vector<char> buf(L.rpart - L.segs, 0);
+    auto at = [&](size_t off) { return buf.data() + (off - L.segs); };
+    GradSeg *gs = reinterpret_cast<GradSeg *>(at(L.segs));
+    GradWin *gw = reinterpret_cast<GradWin *>(at(L.wins));
+    float2 *cf = reinterpret_cast<float2 *>(at(L.coef));
+    double2 *dc = reinterpret_cast<double2 *>(at(L.dcoef));
+    uint64_t *place = reinterpret_cast<uint64_t *>(at(L.place));
+    int nc = 0, nw = 0;
+    for (size_t q = 0; q < seg.size(); ++q) {
+        const SegPlan &sp = seg[q];
+        gs[q] = {(float)sp.inv_r, (float)sp.g, sp.ph_r, sp.ph_i, sp.K, nc, nw, sp.W};
+        auto saved = [&](int k) { return L.ckpt + (size_t)sp.slot[k] * vec_bytes; };
+        for (int k = 0; k <= sp.K; ++k, ++nc) {
+            double cr, ci, dr, di;
+            coef_of(sp.alpha, k, cr, ci);
+            coef_of(sp.dalpha, k, dr, di);
+            cf[nc] = make_float2((float)cr, (float)ci);
+            dc[nc] = make_double2(dr * sp.r, di * sp.r);
+            if (k >= 1 && L.store) place[nc] = L.win + (sp.sbase + (size_t)(k - 1)) * vec_bytes;
+            else place[nc] = (k >= 1 && sp.slot[k] >= 0) ? saved(k) : GRES_NONE;
+        }
+        for (int w = 0; w < sp.W; ++w, ++nw) {
+            GradWin &g = gw[nw];
+            g.B = w * sp.C + 1;
+            g.T = std::min((w + 1) * sp.C, sp.K);
+            g.fresh = L.store ? -1 : g.T == sp.K ? 1 : 0;
+            g.x1 = g.fresh == 0 ? saved(g.T + 1) : GRES_NONE;
+            g.x2 = (g.fresh == 0 && g.T + 2 <= sp.K) ? saved(g.T + 2) : GRES_NONE;
+            g.at = L.win + (L.store ? sp.sbase * vec_bytes : 0);
+        }
+    }
+    return buf;
 }
 
 static int grad_degree_bound(int n, const double *h, const double *J, double gamma, double t)
@@ -488,6 +1091,12 @@ static int grad_degree_bound(int n, const double *h, const double *J, double gam
     for (int p = 0; p < n * (n - 1) / 2; ++p) s += std::fabs(J[p]);
     const double rmax = s + n * std::fabs(gamma);
     return bessel_cutoff(std::fabs(t) * rmax * 1.01 + 1.0) + 2;
+}
+
+// Workgroups of launch_grad_resident.
+static int grad_resident_groups(int n)
+{
+    return n <= 11 ? 1 : n == 12 ? 16 : n <= 15 ? 32 : n == 16 ? 128 : 256;
 }
 
 static qw_status grad_validate(int n, const double *h, const double *J, int S, const double *gamma,
@@ -648,13 +1257,47 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
     const uint32_t TEw = (uint32_t)std::min<uint64_t>(N, uint64_t(1) << GTB);
     const int ntw = (int)(N / TEw);
 
-    // forward sweep
+    // the one-launch sweeps, where the size and the workspace have room for them
     long long amp_terms = 0;
-    for (int q = 0; q < S; ++q) {
+    for (int q = 0; q < S; ++q) amp_terms += (long long)seg[q].K << n;
+    GradRes ra{};
+    std::vector<char> tables;
+    bool resident = grad_resident(n) && ws_bytes >= L.total_res && plan[0].h == std::min(n, n > GTB ? TB_NARROW : GTB);
+    for (const SegPlan &sp : seg) resident = resident && sp.K >= 1;
+    auto clear_sync = [&]() {
+        hipLaunchKernelGGL(k_zero_f64, dim3(64), dim3(256), 0, s, reinterpret_cast<double *>(ws + L.sync),
+                           (int)(sizeof(int) * RES_LINE * (2 + RES_MAXFLAGS) / sizeof(double)));
+    };
+    if (resident) {
+        tables = grad_tables(L, seg, N * sizeof(C));
+        QW_HIP(hipMemcpyAsync(ws + L.segs, tables.data(), tables.size(), hipMemcpyHostToDevice, s));
+        ra.ws = ws;
+        ra.states = states;
+        ra.X0 = vec(L.A, 0);
+        ra.X1 = vec(L.B, 0);
+        ra.vbar = vbar;
+        ra.G = G;
+        ra.erel = erel;
+        ra.seg = reinterpret_cast<const GradSeg *>(ws + L.segs);
+        ra.win = reinterpret_cast<const GradWin *>(ws + L.wins);
+        ra.coef = reinterpret_cast<const float2 *>(ws + L.coef);
+        ra.dcoef = reinterpret_cast<const double2 *>(ws + L.dcoef);
+        ra.place = reinterpret_cast<const uint64_t *>(ws + L.place);
+        ra.part = reinterpret_cast<double *>(ws + L.rpart);
+        ra.start = reinterpret_cast<int *>(ws + L.sync);
+        ra.flags = ra.start + 2 * RES_LINE;
+        ra.c = c;
+        ra.nseg = S;
+        clear_sync();
+        resident = launch_grad_resident(n, ra, false, s) == hipSuccess;
+        if (!resident) (void)hipGetLastError();   // no cooperative launch here
+    }
+
+    // forward sweep
+    for (int q = 0; q < S && !resident; ++q) {
         const SegPlan &sp = seg[q];
         const C *v = states + (size_t)q * N;
         C *y = states + (size_t)(q + 1) * N;
-        amp_terms += (long long)sp.K << n;
         double cr, ci;
         if (sp.K == 0) {
             coef_of(sp.alpha, 0, cr, ci);
@@ -749,13 +1392,28 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
     QW_HIP(hipGetLastError());
     std::vector<double> hp(2 * std::max(L.ntiles_lo * 4, ntw));
     QW_HIP(hipMemcpyAsync(hp.data(), partm, 2 * ntw * sizeof(double), hipMemcpyDeviceToHost, s));
-    QW_HIP(hipStreamSynchronize(s));
+    if (resident) {
+        clear_sync();
+        QW_HIP(launch_grad_resident(n, ra, true, s));
+        hipLaunchKernelGGL(k_grad_sums, dim3(3 * S), dim3(64), 0, s, (const double *)ra.part, grad_resident_groups(n),
+                           reinterpret_cast<double *>(ws + L.sums));
+        QW_HIP(hipGetLastError());
+        std::vector<double> sums(3 * (size_t)S);
+        QW_HIP(hipMemcpyAsync(sums.data(), ws + L.sums, sums.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+        QW_HIP(hipStreamSynchronize(s));
+        for (int q = 0; q < S; ++q) {
+            dt[q] = sums[3 * q] + sums[3 * q + 2];
+            dgamma[q] = sums[3 * q + 1] / seg[q].r;
+        }
+    } else {
+        QW_HIP(hipStreamSynchronize(s));
+    }
     double energy = 0.0;
     for (int i = 0; i < ntw; ++i) energy += hp[2 * i];
     *E_out = energy;
 
     // backward sweep
-    for (int q = S - 1; q >= 0; --q) {
+    for (int q = S - 1; q >= 0 && !resident; --q) {
         const SegPlan &sp = seg[q];
         const C *v = states + (size_t)q * N;
         const C *y = states + (size_t)(q + 1) * N;
@@ -976,7 +1634,8 @@ size_t qw_anneal_workspace_bytes_c64(int n, const double *h, const double *J, in
 {
     if (grad_validate(n, h, J, S, gamma, t, 1.0) != QW_OK) return 0;
     const std::vector<int> Kb = grad_bounds(n, h, J, S, gamma, t);
-    return grad_layout(n, S, Kb.data(), ckpt_every).total;
+    const GradLayout L = grad_layout(n, S, Kb.data(), ckpt_every);
+    return std::max(L.total, L.total_res);
 }
 
 qw_status qw_anneal_energy_grad_c64(int n, const double *h, const double *J, int S, const double *gamma,
