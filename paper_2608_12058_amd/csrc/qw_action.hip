@@ -382,6 +382,7 @@ static void launch_pass(const PassArgs<R> &a, int mode, bool otf, uint64_t ntile
             if (cfg.stream) return launch_shape<R, TB_WIDE_D, NT_WIDE, true, true>(a, mode, otf, ntiles, s, cfg.keep_pd);
             return launch_shape<R, TB_WIDE_D, NT_WIDE, true, false>(a, mode, otf, ntiles, s);
         }
+        if (cfg.tb == TB_LOW_D) return launch_shape<R, TB_LOW_D, 1024, false, false>(a, mode, otf, ntiles, s);
         if (cfg.nt == NT_NARROW) return launch_shape<R, TB_NARROW, NT_NARROW, false, false>(a, mode, otf, ntiles, s);
         if (cfg.stream) return launch_shape<R, Cfg<R>::TB, Cfg<R>::NT, true, true>(a, mode, otf, ntiles, s, cfg.keep_pd);
         return launch_shape<R, Cfg<R>::TB, Cfg<R>::NT, true, false>(a, mode, otf, ntiles, s);

@@ -985,6 +985,7 @@ template <typename R> inline std::vector<PassPlan> plan_passes(int n)
 // From 29 qubits one high group takes 9 or 10 bits (128-byte rows): the
 // per-orientation plans of action_plan.
 static constexpr int TB_WIDE = 14, TB_WIDE_D = 13, NT_WIDE = 1024;
+static constexpr int TB_LOW_D = 11;   // complex128, 1024 threads
 static constexpr int TB_NARROW = 12, NT_NARROW = 1024;
 static constexpr int NT_MID = 1024;   // complex64 2^13 tiles, 8 amplitudes per thread
 static constexpr int SPLIT_NMIN = 25, SPLIT_NMAX = 28;
@@ -1078,6 +1079,34 @@ struct OrientSpec {
     int xh = 0;      // cross bits above the group (k_pass_cross)
 };
 
+// Two orientations of vectors that fit in the memory-side cache, complex64 21-23
+// and complex128 20-21 qubits: there a pass is bound by how many loads are under
+// way and not by HBM, so tiles are small with 1024 threads (two workgroups per CU,
+// one or two vectors per thread), and rows may be 64 B where the tiles that share
+// their cache lines are neighbours on one XCD.  The
+// smallest tile that needs no third orientation is not always the fastest: of a
+// sweep of tiles, threads, group sizes and both block orders these were.
+// Microseconds per term, in parentheses with rows of 128 B and more on 2^13 (23
+// qubits: 2^14; complex128: 2^12) tiles: complex64 21 qubits 15.8 (17.6), 22: 29.1
+// (33.0), 23: 57.7 (61.7); complex128 20: 16.2 (17.6), 21: 30.9 (34.9).
+template <typename R> inline std::vector<OrientSpec> cached_plan(int n)
+{
+    std::vector<OrientSpec> S;
+    auto add = [&](int tb, int nt, int g0, int h) {
+        const TileCfg c{tb, nt, false, 0, false};
+        S.push_back({{g0 ? tb - h : 0, g0, h}, c, c, false, g0 ? 1 : 0, 0});
+    };
+    if constexpr (sizeof(R) == 4) {
+        if (n == 21) { add(TB_NARROW, NT_NARROW, 0, 12); add(TB_NARROW, NT_NARROW, 12, 9); }
+        if (n == 22) { add(Cfg<R>::TB, NT_MID, 0, 13); add(TB_NARROW, NT_NARROW, 13, 9); }
+        if (n == 23) { add(Cfg<R>::TB, NT_MID, 0, 13); add(TB_WIDE, NT_WIDE, 13, 10); }
+    } else {
+        if (n == 20) { add(TB_LOW_D, 1024, 0, 11); add(TB_LOW_D, 1024, 11, 9); }
+        if (n == 21) { add(TB_LOW_D, 1024, 0, 11); add(Cfg<R>::TB, Cfg<R>::NT, 11, 10); }
+    }
+    return S;
+}
+
 // Complex64 from 25 qubits: the contiguous orientation in the middle (an add
 // pass every term, 12 or 13 bits), the two high groups at the ends (one fused
 // pass each every other term).  The fused pass of the lower high group runs on
@@ -1097,7 +1126,8 @@ struct OrientSpec {
 // from 29 qubits the sweep chose it for the lower high group.
 template <typename R> inline std::vector<OrientSpec> action_plan(int n, bool diag_from_tables)
 {
-    std::vector<OrientSpec> S;
+    std::vector<OrientSpec> S = cached_plan<R>(n);
+    if (!S.empty()) return S;
     const bool otf_all = sizeof(R) == 4 && diag_from_tables && n >= OTF_NMIN;
     if constexpr (sizeof(R) == 4) {
         const bool st = stream_for<R>(n);
@@ -1163,9 +1193,12 @@ template <typename R> inline std::vector<OrientSpec> action_plan(int n, bool dia
 // complex64, 2^13 in complex128), the other one the rest in rows of 128 B: 10
 // bits per tile and up to four cross bits.  Measured in microseconds per term,
 // action_plan in parentheses: complex64 25 qubits 312 (383), 26: 612 (758), 27:
-// 1205 (1503), 28: 2710 (2970); complex128 22: 63.6 (94.1), 23: 137 (199), 24:
-// 344 (415), 25: 693 (810), 26: 1195 (1570), 27: 2705 (3190).  Five cross bits
-// are slower than a third orientation (28 qubits on 2^13 tiles: 3053).  The
+// 1205 (1503), 28: 2710 (2970); complex128 23: 137 (199), 24: 344 (415), 25: 693
+// (810), 26: 1195 (1570), 27: 2705 (3190).  Five cross bits are slower than a third
+// orientation (28 qubits on 2^13 tiles: 3053); at 24 qubits complex64 keeps its two
+// orientations of 2^14 tiles (140; contiguous 2^12 tiles and two cross bits 153).
+// Complex128 at 22 qubits needs no cross bit with rows of 64 B, as at 21
+// (cached_plan): 61.4 (94.1; rows of 128 B 63.9).  The
 // strided orientation rebuilds the diagonal from 26 qubits; the contiguous one
 // does in complex128, while in complex64 its 4 of 44 bytes are cheaper read (28
 // qubits: 2006 us per pass against 2131).
@@ -1178,6 +1211,12 @@ template <typename R> inline std::vector<OrientSpec> pair_plan(int n, bool diag_
     constexpr int H = TB - Cfg<R>::LMIN;                           // in rows of 128 B
     const int xh = std::max(0, n - TB - H);
     if (n < (sizeof(R) == 4 ? 25 : 22) || n > (sizeof(R) == 4 ? 28 : 27)) return S;
+    if (sizeof(R) == 8 && n == 22) {
+        const TileCfg low{TB_LOW_D, 1024, false, 0, false}, full{TB, NT_WIDE, false, 0, false};
+        S.push_back({{0, 0, TB}, full, full, false, 0, 0});
+        S.push_back({{TB_LOW_D - 9, TB, 9}, low, low, false, 1, 0});
+        return S;
+    }
     const TileCfg wide{TB, NT_WIDE, st, 0, kp};
     const int h = n - TB - xh;
     const bool otf = diag_from_tables && n >= OTF_TOP_NMIN;

@@ -1,5 +1,5 @@
 """The two-orientation plan of 22-28 qubits, whose strided passes take flips from
-other tiles of their cluster: polynomials of low degree against torch in
+other tiles of their cluster, and the small tiles of 20-23 qubits: polynomials of low degree against torch in
 complex128 (start, fused and last passes with and without cross bits, in place),
 the passes that complete what a cluster left, and long series against the general
 plan, which calls with the norm monitor keep."""
@@ -44,7 +44,10 @@ def _h(torch, n, d, g, x):
 CASES = [(64, 25), (64, 26), (64, 28), (128, 22), (128, 23), (128, 24), (128, 26), (128, 27)]
 
 
-@pytest.mark.parametrize("prec,n", CASES)
+SMALL = [(64, 21), (64, 22), (64, 23), (128, 20), (128, 21)]
+
+
+@pytest.mark.parametrize("prec,n", CASES + SMALL)
 @pytest.mark.parametrize("diag", [False, True])
 @pytest.mark.parametrize("patience", [-1, 0])
 def test_low_degrees_match_torch(env, prec, n, diag, patience):
