@@ -489,10 +489,10 @@ static qw_status replay(const std::vector<BLaunch> &Ls, const BatchDesc *dD, con
     return QW_OK;
 }
 
-// Instantiated graphs of recent calls, keyed by the device, the workspace and
-// the exact launch sequence (which fixes every kernel argument: descriptors
-// and tile tables are re-uploaded into the same workspace places before each
-// replay).  At most GRAPH_CACHE entries; the oldest is destroyed first, after
+// Instantiated graphs of recent calls, keyed by the device and the exact launch
+// sequence with every kernel argument (the places of the descriptors, items, order
+// and tile tables, which are uploaded anew before each replay; two batches in one
+// workspace may have them in different places).  At most GRAPH_CACHE entries; the oldest is destroyed first, after
 // its device has finished its work (an eviction waits for the whole device).
 static constexpr size_t GRAPH_CACHE = 4;
 struct GraphEntry {
@@ -503,10 +503,11 @@ struct GraphEntry {
 static std::mutex g_graph_mu;
 static std::vector<GraphEntry> g_graphs;
 
-static std::string launch_key(const std::vector<BLaunch> &Ls, const void *ws, int conc)
+static std::string launch_key(const std::vector<BLaunch> &Ls, const void *desc, const void *items, const void *order,
+                              size_t nsmall, int conc)
 {
     std::ostringstream os;
-    os << ws << ':' << conc;
+    os << desc << ',' << items << ',' << order << ',' << nsmall << ':' << conc;
     for (const BLaunch &L : Ls)
         os << ';' << L.onchip << ',' << L.cls << ',' << L.mode << ',' << L.high << ',' << L.stream_hint << ','
            << L.grid << ',' << static_cast<const void *>(L.tiles) << ',' << L.step;
@@ -777,7 +778,7 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
     if (use_graph && !Ls.empty()) {
         int dev = 0;
         QW_HIP(hipGetDevice(&dev));
-        const std::string key = launch_key(Ls, workspace, conc ? 1 : 0);
+        const std::string key = launch_key(Ls, dD, ditems, dorder, run.small.size(), conc ? 1 : 0);
         std::lock_guard<std::mutex> lock(g_graph_mu);
         for (const GraphEntry &e : g_graphs)
             if (e.dev == dev && e.key == key) exec = e.exec;
