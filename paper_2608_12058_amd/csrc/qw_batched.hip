@@ -19,6 +19,7 @@
 // Spectral bounds and normalised diagonals are generated on the device from
 // the couplings of every instance (section III.A: only the couplings are sent).
 #include "qw_kernels.h"
+#include "qw_resident.h"
 
 #include <chrono>
 #include <cstdio>
@@ -135,6 +136,143 @@ __global__ void __launch_bounds__(256) k_minmax_instances(const BatchDesc *D, co
     }
 }
 
+// ---------------------------------------------------------------------------
+// Instances of one workgroup
+// ---------------------------------------------------------------------------
+
+static constexpr int ONCHIP_NT = 1024;
+
+struct OnchipItem {
+    const float2 *psi;
+    float2 *out;
+    const float *d;
+    const float2 *coef;   // c_0 .. c_K
+    float g, pr, pi;      // pr + i pi: global phase
+    int n, K;
+};
+
+// The recurrence of one instance of at most 11 + log2(PER) qubits, its vectors in
+// registers and b_{k+1} in LDS besides, where a term reads the flips of the lane
+// and wave bits (three lane bits by DPP, bit 0 and a thread's own vectors from its
+// registers).  Smaller instances leave threads without an amplitude: those keep
+// zeros, so that every thread sums the same flips and the reads go out together.
+template <int PER> __device__ __forceinline__ void onchip_run(const OnchipItem &I, CVec<float> *lds)
+{
+    using C = float2;
+    using V = CVec<float>;
+    constexpr int VE = V::N, NT = ONCHIP_NT, LT = 10, QB = (PER == 4) ? 2 : (PER == 2) ? 1 : 0;
+    constexpr bool TWICE = PER * NT * 2 <= (1 << (Cfg<float>::TB - 1));   // room for two tiles: one barrier per term
+    const int tid = threadIdx.x, lane = tid & 63;
+    auto inside = [&](int q) { return PER > 1 || (uint32_t)tid * VE < (1u << I.n); };
+    V b1[PER], b2[PER], ps[PER];
+    float d[PER][VE];
+    C ck{0.f, 0.f};           // lane l: c_{64 i + l}
+    auto load_coef = [&](int k) {
+        const int i = (k & ~63) + lane;
+        if (i <= I.K) ck = I.coef[i];
+    };
+    auto lane_value = [](float x, int l) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
+    };
+    load_coef(I.K);
+    const float cKr = lane_value(ck.x, I.K & 63), cKi = lane_value(ck.y, I.K & 63);
+    int t = 0;
+    auto share = [&]() {
+        if (TWICE) t ^= 1;
+        else __syncthreads();   // every flip of the last term has been read
+#pragma unroll
+        for (int q = 0; q < PER; ++q) lds[t * PER * NT + q * NT + tid] = b1[q];
+        __syncthreads();
+    };
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const uint32_t e = (uint32_t)(q * NT + tid) * VE;
+#pragma unroll
+        for (int v = 0; v < VE; ++v) {
+            ps[q].v[v] = C{0.f, 0.f};
+            d[q][v] = 0.f;
+            if (inside(q)) {
+                ps[q].v[v] = I.psi[e + v];
+                d[q][v] = I.d[e + v];
+            }
+            const C p = ps[q].v[v];
+            b1[q].v[v] = C{fmad(cKr, p.x, -(cKi * p.y)), fmad(cKr, p.y, cKi * p.x)};
+            b2[q].v[v] = C{0.f, 0.f};
+        }
+    }
+    if (I.K > 0) share();
+    for (int k = I.K - 1; k >= 0; --k) {
+        if ((k & 63) == 63) load_coef(k);
+        const float cr = lane_value(ck.x, k & 63), ci = lane_value(ck.y, k & 63);
+        const float scale = (k == 0) ? 1.f : 2.f;
+        V f[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            auto add = [&](const V &y) {
+#pragma unroll
+                for (int v = 0; v < VE; ++v) {
+                    f[q].v[v].x += y.v[v].x;
+                    f[q].v[v].y += y.v[v].y;
+                }
+            };
+            f[q].v[0] = b1[q].v[1];
+            f[q].v[1] = b1[q].v[0];
+#pragma unroll
+            for (int j = 0; j < QB; ++j) add(b1[q ^ (1 << j)]);
+            add(lane_flip<float, 0xb1>(b1[q]));    // quad_perm 1 0 3 2
+            add(lane_flip<float, 0x4e>(b1[q]));    // quad_perm 2 3 0 1
+            add(lane_flip<float, 0x128>(b1[q]));   // row_ror 8
+#pragma unroll
+            for (int j = 2; j < LT; ++j)
+                if (j != 3) add(lds[t * PER * NT + q * NT + (tid ^ (1 << j))]);
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+#pragma unroll
+            for (int v = 0; v < VE; ++v) {
+                const C b = b1[q].v[v], s = b2[q].v[v], p = ps[q].v[v], x = f[q].v[v];
+                const float hr = fmad(d[q][v], b.x, I.g * x.x), hi = fmad(d[q][v], b.y, I.g * x.y);
+                const float tr = fmad(scale, hr, -s.x), ti = fmad(scale, hi, -s.y);
+                b2[q].v[v] = b;
+                b1[q].v[v] = C{tr + fmad(cr, p.x, -(ci * p.y)), ti + fmad(cr, p.y, ci * p.x)};
+                if (!inside(q)) b1[q].v[v] = C{0.f, 0.f};
+            }
+        if (k > 0) share();
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+#pragma unroll
+        for (int v = 0; v < VE; ++v) {
+            const C y = b1[q].v[v];
+            if (inside(q))
+                I.out[(uint32_t)(q * NT + tid) * VE + v] =
+                    C{fmad(I.pr, y.x, -(I.pi * y.y)), fmad(I.pr, y.y, I.pi * y.x)};
+        }
+    __syncthreads();   // lds is reused by the next instance
+}
+
+// Whole recurrences of the small instances, one workgroup each; the workgroups
+// drain the list, costliest first.  Bounded by LDS reads at 13 qubits (7 of 16 B
+// per two amplitudes and term) and by the latency of a term's reads, sums and
+// barrier below.  Microseconds per term, in parentheses with the amplitudes 8 B
+// apart, all flips read from LDS and coefficients loaded where they were used:
+// 13 qubits 2.6 (5.6; 256 instances 2.9 (5.9)), 12: 1.1 (3.0), 11: 0.78 (1.8), 10
+// and less 0.78 (10: 1.3, 8: 1.1, 4: 0.89).
+__global__ void __launch_bounds__(ONCHIP_NT) k_onchip(const OnchipItem *items, const int *order, int count)
+{
+    __shared__ CVec<float> lds[1 << (Cfg<float>::TB - 1)];
+    for (int it = blockIdx.x; it < count; it += gridDim.x) {
+        const OnchipItem I = wave_uniform(items[__builtin_amdgcn_readfirstlane(order[it])]);
+        if (I.n == 13) onchip_run<4>(I, lds);
+        else if (I.n == 12) onchip_run<2>(I, lds);
+        else onchip_run<1>(I, lds);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Instances in grouped passes
+// ---------------------------------------------------------------------------
+
 // Global step `step` of the fused two-orientation schedule for the tile
 // (instance, t) of this block.  Every instance of the multi-pass class runs
 // K + 1 passes: step 0 starts term K-1 in the low orientation (MODE START);
@@ -250,13 +388,16 @@ struct BatchSched {
 };
 
 // Class actually used for a multi-pass instance of n qubits: the requested
-// one, else NARROW for n = 13 (the only class with two orientations there)
-// and MID above.
+// one, else NARROW up to 20 qubits, MID above, where 2^12 tiles would have rows
+// below 128 B (21) or a third orientation (22).  The smaller tiles give twice the
+// workgroups, which counts at the steps that only a few instances still take: 48
+// instances of 12 to 20 qubits 42.8 ms against 45.0 with MID, 9 of 14 to 19 7.8
+// against 9.1, 34 of 11 to 17 5.8 against 6.9.
 static int class_for(const BatchSched &S, int n)
 {
     const int c = S.cls[n];
     if (c >= 0) return c;
-    return (n <= 13) ? (int)BC_NARROW : (int)BC_MID;
+    return (n <= 20) ? (int)BC_NARROW : (int)BC_MID;
 }
 
 static qw_status validate_sched(const BatchSched &S)
@@ -330,7 +471,7 @@ static BatchPlan plan_batch(const qw_batch_item *items, int count, const double 
     P.off_hj = take(sizeof(double) * P.hj_count);
     P.off_q = take(sizeof(double) * (size_t(1) << LB_TAB) * count);
     P.off_coef = take(sizeof(float2) * P.coef_slots);
-    P.off_items = take(sizeof(OnchipItem<float>) * count);
+    P.off_items = take(sizeof(OnchipItem) * count);
     P.off_order = take(sizeof(int) * count);
     P.total = off;
     return P;
@@ -461,7 +602,7 @@ static qw_status side_stream(hipStream_t *out)
 // Enqueues the launches on s (captured or not).  The one-workgroup launch goes
 // first; with `side` it runs on the side stream between a fork and a join
 // event, so it overlaps the passes.
-static qw_status replay(const std::vector<BLaunch> &Ls, const BatchDesc *dD, const OnchipItem<float> *ditems,
+static qw_status replay(const std::vector<BLaunch> &Ls, const BatchDesc *dD, const OnchipItem *ditems,
                         const int *dorder, int nsmall, hipStream_t s, hipStream_t side, hipEvent_t fork,
                         hipEvent_t join)
 {
@@ -475,7 +616,7 @@ static qw_status replay(const std::vector<BLaunch> &Ls, const BatchDesc *dD, con
                 os = side;
                 joined = false;
             }
-            hipLaunchKernelGGL((k_onchip<float, Cfg<float>::TB, ONCHIP_NT>), dim3(L.grid), dim3(ONCHIP_NT), 0, os,
+            hipLaunchKernelGGL(k_onchip, dim3(L.grid), dim3(ONCHIP_NT), 0, os,
                                ditems, dorder, nsmall);
             if (side) QW_HIP(hipEventRecord(join, side));
             continue;
@@ -610,7 +751,7 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
     BatchRun run;
     run.K.resize(count);
     std::vector<float2> coefh(P.coef_slots);
-    std::vector<OnchipItem<float>> oitems(count);
+    std::vector<OnchipItem> oitems(count);
     float2 *dcoef = reinterpret_cast<float2 *>(ws + P.off_coef);
     int coff = 0;
     for (int i = 0; i < count; ++i) {
@@ -663,7 +804,7 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
         run.amp_terms += (long long)K << it.n;
         if (small) run.small.push_back(i);
         else run.large.push_back(i);
-        oitems[i] = OnchipItem<float>{b.psi, b.out, b.d, b.coef, b.g, b.pr, b.pi, it.n, K};
+        oitems[i] = OnchipItem{b.psi, b.out, b.d, b.coef, b.g, b.pr, b.pi, it.n, K};
     }
     QW_HIP(hipMemcpyAsync(dcoef, coefh.data(), coefh.size() * sizeof(float2), hipMemcpyHostToDevice, s));
     QW_HIP(hipMemcpyAsync(dD, desc.data(), desc.size() * sizeof(BatchDesc), hipMemcpyHostToDevice, s));
@@ -675,9 +816,9 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
     std::sort(run.small.begin(), run.small.end(), [&](int a, int b) {
         return ((long long)run.K[a] << items[a].n) > ((long long)run.K[b] << items[b].n);
     });
-    OnchipItem<float> *ditems = reinterpret_cast<OnchipItem<float> *>(ws + P.off_items);
+    OnchipItem *ditems = reinterpret_cast<OnchipItem *>(ws + P.off_items);
     int *dorder = reinterpret_cast<int *>(ws + P.off_order);
-    QW_HIP(hipMemcpyAsync(ditems, oitems.data(), oitems.size() * sizeof(OnchipItem<float>), hipMemcpyHostToDevice, s));
+    QW_HIP(hipMemcpyAsync(ditems, oitems.data(), oitems.size() * sizeof(OnchipItem), hipMemcpyHostToDevice, s));
     if (!run.small.empty())
         QW_HIP(hipMemcpyAsync(dorder, run.small.data(), run.small.size() * sizeof(int), hipMemcpyHostToDevice, s));
 

@@ -31,7 +31,6 @@ template <> struct Cfg<double> {
     static constexpr int NT = 512;
     static constexpr int LMIN = 3;
 };
-static constexpr int ONCHIP_NT = 1024;
 static constexpr int MAXPART = 4096;          // reduction partials
 static constexpr int KMAX_ONCHIP = 1 << 17;   // coefficient slots for on-chip runs
 static constexpr int LB_TAB = 13;             // low bits of the energy tables
@@ -825,108 +824,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_
         if (a.late[1 + t] != a.round) continue;
         __syncthreads();   // lds of the tile before
         pass_tile<R, TB, NT, PM_FUSED, OTF, STREAM, KEEP_PD, XH, true>(a, (uint64_t)t, lds);
-    }
-}
-
-// Whole recurrence of one small instance (n <= TB) inside one workgroup.
-template <typename R> struct OnchipItem {
-    using C = typename Cplx<R>::T;
-    const C *psi;
-    C *out;
-    const R *d;
-    const C *coef;  // c_0..c_K
-    R g;
-    R pr, pi;       // global phase
-    int n, K;
-    R two = R(2), sub = R(1);   // Clenshaw (2, 1); Horner's rule (1, 0)
-};
-
-template <typename R, int TB, int NT>
-__global__ void __launch_bounds__(NT) k_onchip(const OnchipItem<R> *items, const int *order, int count)
-{
-    using C = typename Cplx<R>::T;
-    constexpr int PER = (1 << TB) / NT;
-    static_assert(PER >= 1, "");
-    __shared__ C lds[1 << TB];
-    for (int it = blockIdx.x; it < count; it += gridDim.x) {
-        const OnchipItem<R> I = items[order ? order[it] : it];
-        const uint32_t N = 1u << I.n;
-        C ps[PER], b1[PER], b2[PER];
-        R dd[PER];
-        const C cK = I.coef[I.K];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const uint32_t e = q * NT + threadIdx.x;
-            if (e < N) {
-                ps[q] = I.psi[e];
-                dd[q] = I.d[e];
-                b1[q].x = cK.x * ps[q].x - cK.y * ps[q].y;
-                b1[q].y = cK.x * ps[q].y + cK.y * ps[q].x;
-                b2[q].x = R(0);
-                b2[q].y = R(0);
-                lds[e] = b1[q];
-            }
-        }
-        __syncthreads();
-        for (int k = I.K - 1; k >= 1; --k) {
-            const C ck = I.coef[k];
-            C nb[PER];
-#pragma unroll
-            for (int q = 0; q < PER; ++q) {
-                const uint32_t e = q * NT + threadIdx.x;
-                if (e < N) {
-                    R sr = R(0), si = R(0);
-                    for (int j = 0; j < I.n; ++j) {
-                        const C x = lds[e ^ (1u << j)];
-                        sr += x.x;
-                        si += x.y;
-                    }
-                    const R hr = dd[q] * b1[q].x + I.g * sr;
-                    const R hi = dd[q] * b1[q].y + I.g * si;
-                    nb[q].x = (I.two * hr - I.sub * b2[q].x) + (ck.x * ps[q].x - ck.y * ps[q].y);
-                    nb[q].y = (I.two * hi - I.sub * b2[q].y) + (ck.x * ps[q].y + ck.y * ps[q].x);
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < PER; ++q) {
-                const uint32_t e = q * NT + threadIdx.x;
-                if (e < N) {
-                    b2[q] = b1[q];
-                    b1[q] = nb[q];
-                    lds[e] = nb[q];
-                }
-            }
-            __syncthreads();
-        }
-        const C c0 = I.coef[0];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const uint32_t e = q * NT + threadIdx.x;
-            if (e < N) {
-                C y;
-                if (I.K == 0) {
-                    y.x = c0.x * ps[q].x - c0.y * ps[q].y;
-                    y.y = c0.x * ps[q].y + c0.y * ps[q].x;
-                } else {
-                    R sr = R(0), si = R(0);
-                    for (int j = 0; j < I.n; ++j) {
-                        const C x = lds[e ^ (1u << j)];
-                        sr += x.x;
-                        si += x.y;
-                    }
-                    const R hr = dd[q] * b1[q].x + I.g * sr;
-                    const R hi = dd[q] * b1[q].y + I.g * si;
-                    y.x = (hr - I.sub * b2[q].x) + (c0.x * ps[q].x - c0.y * ps[q].y);
-                    y.y = (hi - I.sub * b2[q].y) + (c0.x * ps[q].y + c0.y * ps[q].x);
-                }
-                C o;
-                o.x = I.pr * y.x - I.pi * y.y;
-                o.y = I.pr * y.y + I.pi * y.x;
-                I.out[e] = o;
-            }
-        }
-        __syncthreads();  // lds is reused by the next instance
     }
 }
 
