@@ -30,7 +30,9 @@
  *   - The recurrence of n <= 20 qubits (complex128: 19) without norm monitor is
  *     one launch whose workgroups exchange data; workgroups that cannot all
  *     start together (the device shared with many waiting kernels) make one of
- *     them run it alone, slowly, with results that differ by rounding.
+ *     them run it alone, slowly, with results that differ by rounding.  The two
+ *     largest sizes in each precision are launched cooperatively, and in passes
+ *     where a stream is being captured.
  *   - Errors: every call returns a qw_status; nothing is thrown across the ABI.
  *     qw_last_error() returns a thread-local message for the last failure.
  *   - Calls on distinct workspaces may run concurrently from different threads.
@@ -61,7 +63,10 @@ typedef enum { QW_CHEB = 0, QW_CF = 1 } qw_method;
 typedef struct {
     int n;              /* qubits                                                 */
     int K;              /* polynomial degree; K+1 coefficients                    */
-    int passes;         /* global passes per Clenshaw term                        */
+    int passes;         /* global passes per Clenshaw term with the norm monitor
+                           (without it, complex64 25-28 and complex128 22-27
+                           qubits take two where this says three, and sizes of
+                           one launch none)                                       */
     int method;         /* qw_method actually used                                */
     double shift_c;     /* spectral shift c = (max E + min E)/2                   */
     double radius_r;    /* bound r on the spectral radius of H - cI               */
@@ -73,14 +78,16 @@ typedef struct {
                            2 also records one after every pass (multi-pass path) */
     float setup_ms;     /* out (timing): bound, diagonal, coefficients            */
     float loop_ms;      /* out (timing): all Clenshaw terms and the final step    */
-    float pass_ms[4];   /* out (timing 2): pass p summed over all terms           */
+    float pass_ms[4];   /* out (timing 2): pass p summed over all terms (0 beyond
+                           the passes that ran)                                   */
     int monitor;        /* in: nonzero measures ||b_k|| of every term (fused in the
                            last pass), fills eval_bound and checks the growth      */
     double growth;      /* out (monitor): max over k of ||b_k|| / its limit for a
                            valid bound (> 1 means QW_EDIVERGE)                     */
     double out_norm;    /* out (monitor): ||psi_out||                             */
     int otf_mask;       /* out: bit o set if the passes of orientation o rebuild
-                           the diagonal from (h, J) instead of reading it         */
+                           the diagonal from (h, J) instead of reading it (of
+                           the orientations that `passes` counts)                 */
 } qw_info;
 
 /* ------------------------------------------------------------------------
@@ -215,10 +222,10 @@ qw_status qw_spectral_bound_f64(int n, const double *diag, const double *h, cons
  *             generate them from h, J (host arrays as in qw_spectral_bound_*).
  *             With diag == NULL the fused passes of the two end orientations
  *             rebuild the diagonal inside every Clenshaw term from per-tile
- *             tables and no pass reads a stored one: complex64 from 26 qubits
- *             (n >= 31: it is never stored, and the on-the-fly workspace has no
- *             room for it; 26-30: the workspace still has), complex128 from 26
- *             to 30 qubits.  Otherwise complex128 stores it in the workspace
+ *             tables: complex64 from 26 qubits (n >= 31: it is never stored, and
+ *             the on-the-fly workspace has no room for it; 26-30: the workspace
+ *             still has, and at 26-28 the contiguous passes read it there),
+ *             complex128 from 26 to 30 qubits.  Otherwise complex128 stores it in the workspace
  *             (n = 32: the workspace is 172 GB, with psi 240 GB in all).  A
  *             recomputed value is summed in double and rounded once.
  *   psi_in  : device, N complex values; psi_out: device, N complex values; they
@@ -301,7 +308,7 @@ typedef struct {
     signed char tile_class[23]; /* per n (index n), multi-pass instances: 0 = 2^13-
                                    amplitude tiles, 1024 threads; 1 = 2^12, 1024
                                    threads (13 <= n <= 20); 2 = 2^13, 512 threads;
-                                   -1 = default (1 for n = 13, else 0)             */
+                                   -1 = default (1 up to n = 20, else 0)           */
 } qw_batch_sched;
 
 typedef struct {
@@ -313,7 +320,7 @@ typedef struct {
     float loop_ms;         /* (timing) the recurrence launches (graph replay)     */
     int onchip_nmax, concurrent;   /* the schedule used                           */
     int graph_cached;      /* 1: the instantiated graph of an earlier call with the
-                              same launch sequence and workspace was replayed     */
+                              same launches and workspace places was replayed     */
     float graph_ms;        /* host time to capture and instantiate the graph (0
                               when cached); not part of setup_ms or loop_ms       */
     int class_count[3];    /* multi-pass instances per tile class                 */
@@ -328,7 +335,7 @@ size_t qw_batched_workspace_bytes_c64(const qw_batch_item *items, int count, con
  * (degree chosen for its own tol).  Instances with n <= 13 (or 12) run in one
  * persistent on-chip launch; larger ones in grouped two-pass launches (one per
  * tile class and step) captured into a HIP graph (eager launches when stream
- * is NULL), which later calls with the same launch sequence and workspace
+ * is NULL), which later calls with the same launches and workspace places
  * replay without capturing again (four graphs are kept per process; a call
  * that evicts the oldest waits for its device to finish all work first).  The
  * schedule comes from the tune file tune_cache (may be NULL: the default).
@@ -394,7 +401,11 @@ size_t qw_anneal_workspace_bytes_c64(int n, const double *h, const double *J, in
  *                bit-identical for every ckpt_every.
  *   E, dgamma (S), dt (S), dh (n), dJ (n(n-1)/2): host outputs.
  *   psiT_out   : device complex64, receives psi_S (may be NULL).
- * 1 <= n <= 28.  Synchronises the stream once per segment. */
+ * 1 <= n <= 28.  From 8 to 20 qubits each sweep is one cooperative launch and the
+ * stream is synchronised a few times per call; in passes, once per segment: other
+ * sizes, a segment of degree 0, a device without cooperative launches, or a
+ * workspace smaller than asked for that still has the vectors (the results are
+ * the same up to the order of the double sums in dgamma and dt). */
 qw_status qw_anneal_energy_grad_c64(int n, const double *h, const double *J, int S, const double *gamma,
                                     const double *t, const void *psi0, double tol, int ckpt_every,
                                     double *E, double *dgamma, double *dt, double *dh, double *dJ,

@@ -10,15 +10,16 @@
 // amplitudes (bit j of the index = qubit j); the normalised diagonal
 // d = (E - c)/r is a real vector of N, or recomputed per tile in the fused
 // passes of both end orientations: complex64 from 26 qubits (from 31 never
-// stored, where it would crowd the 288 GB), complex128 from 26 to 30 qubits.
+// stored, where it would crowd the 288 GB; at 26-28 stored for the contiguous
+// passes alone), complex128 from 26 to 30 qubits.
 //
-// Per Clenshaw term the state is streamed in P passes (P = 1 for n <= 13 in
-// complex64): the first pass loads a contiguous tile of 2^13 amplitudes of
-// b_{k+1} into LDS, sums the flips of its low 13 bits, and fuses the diagonal,
-// the coefficient axpy and the three-term update; each further pass loads a
-// tile spanning a group of high bits (plus contiguous "passenger" bits for
-// coalescing) and adds that group's flips.  Small instances (n <= 13) run the
-// whole recurrence inside one workgroup with the vector resident in LDS.
+// Per Clenshaw term the state is streamed in P passes: one loads contiguous tiles
+// of b_{k+1} into LDS, sums the flips of their bits, and fuses the diagonal, the
+// coefficient axpy and the three-term update; the others load tiles spanning a
+// group of high bits (plus contiguous "passenger" bits for coalescing) and add
+// that group's flips, at 25-28 qubits (complex128: 22-27) also those of bits above
+// the group, from other tiles.  Up to 20 qubits (complex128: 19) the whole
+// recurrence is one launch that keeps the vectors in registers (qw_resident.h).
 #include "qw_kernels.h"
 #include "qw_prepared.h"
 #include "qw_resident.h"
@@ -1187,7 +1188,7 @@ qw_status qw_expm_action_c64_noalloc(int n, const float *diag, const double *h, 
 
 
 const char *qw_last_error(void) { return g_err.c_str(); }
-const char *qw_version(void) { return "qwexp 0.15 (gfx950, fused passes, per-orientation launch plans from 25 qubits, contiguous middle orientation, diagonal rebuilt in the end orientations in complex64 and complex128, complex64 flips of a thread's own vectors from registers)"; }
+const char *qw_version(void) { return "qwexp 0.16 (gfx950, one-launch recurrences and gradient sweeps to 20 qubits, fused passes of two orientations to 28 qubits with flips taken across tiles, three above, diagonal rebuilt in the strided orientations)"; }
 
 size_t qw_workspace_bytes(int n, int precision, int on_the_fly)
 {

@@ -1,6 +1,6 @@
 // Shared device kernels and host helpers of libqwexp (included by every HIP
-// translation unit): tile configuration, the Clenshaw pass body, the on-chip
-// whole-recurrence kernel, and small host utilities.
+// translation unit): tile configuration, energies, the Clenshaw pass body, the
+// pass plans, and small host utilities.
 #pragma once
 
 #include "qw_device.h"
