@@ -5,7 +5,7 @@
 // its own shift, bound and coefficients, and sizes may differ:
 //
 //  * instances with n <= 13 run their whole recurrence inside one workgroup
-//    (vector resident in LDS): one persistent launch drains them in
+//    (vectors in registers): one persistent launch drains them in
 //    descending order of cost N*K;
 //  * instances with 14 <= n <= 22 run the fused two-orientation schedule of the
 //    single-instance path (one pass per Clenshaw term), grouped: instances are
