@@ -1049,6 +1049,10 @@ qw_status scaled_chain(int n, const EnergyTables &T, double emin, double emax, c
         double c = it.alpha * 0.5 * (emax + emin);
         double r = std::fabs(it.alpha) * 0.5 * (emax - emin) + n * std::fabs(it.beta);
         if (!(r > 0.0)) continue;   // H' = c I, here c = 0 as well: the identity
+        if (!finite(c) || !finite(r) || !finite(it.beta) || !finite(it.t)) {
+            set_error("an exponential's shift and bound are not finite");
+            return QW_EINVAL;
+        }
         double g = it.beta / r;
         if (sizeof(R) == 4 && it.beta != 0.0) {
             float gf = (float)g;

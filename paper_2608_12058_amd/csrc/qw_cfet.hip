@@ -130,6 +130,12 @@ qw_status cfet_impl(int n, const double *h, const double *J, const double *A_coe
     if (!(tol > 0.0) || !std::isfinite(tol)) { set_error("tol must be positive and finite"); return QW_EINVAL; }
     if (steps < 0 || steps > MAX_STEPS) { set_error("steps must be in 0..2^20"); return QW_EINVAL; }
     if (!psi_in || !psi_out) { set_error("psi_in and psi_out are required"); return QW_EINVAL; }
+    // for every size: exponentials that share a launch pass no check of their own
+    if ((reinterpret_cast<uintptr_t>(psi_in) & 15) != 0 || (reinterpret_cast<uintptr_t>(psi_out) & 15) != 0) {
+        set_error("state vectors must be 16-byte aligned");
+        return QW_EINVAL;
+    }
+    if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) { set_error("workspace must be 256-byte aligned"); return QW_EINVAL; }
     Schedule S;
     qw_status st = read_schedule(A_coef, A_deg, B_coef, B_deg, T, &S);
     if (st != QW_OK) return st;
