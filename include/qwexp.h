@@ -32,7 +32,9 @@
  *     start together (the device shared with many waiting kernels) make one of
  *     them run it alone, slowly, with results that differ by rounding.  The two
  *     largest sizes in each precision are launched cooperatively, and in passes
- *     where a stream is being captured.
+ *     where a stream is being captured.  Where the workgroups have no room side by
+ *     side (a partitioned device, a stream with masked compute units, a refused
+ *     cooperative launch) every such size runs in passes.
  *   - Errors: every call returns a qw_status; nothing is thrown across the ABI.
  *     qw_last_error() returns a thread-local message for the last failure.
  *   - Calls on distinct workspaces may run concurrently from different threads.
@@ -447,6 +449,13 @@ int qw_debug_schedule(int K, int P, int *out, int cap);
  * thread from now on; negative: the default, some 0.1 s).  The results differ
  * only by rounding.  Returns the value before. */
 int qw_debug_start_patience(int looks);
+
+/* For tests: refuse one-launch recurrences and sweeps of several workgroups (calls
+ * of this host thread from now on): 1 as on a stream with masked compute units,
+ * before anything is launched (plans whose tiles wait for one another are left out
+ * as well), 2 at the launch itself, 3 at that of a backward sweep; 0 none.
+ * Returns the value before. */
+int qw_debug_refuse_groups(int how);
 
 /* Library version string. */
 const char *qw_version(void);

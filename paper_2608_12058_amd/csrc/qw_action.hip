@@ -36,8 +36,41 @@
 namespace qw {
 
 static thread_local int t_patience = RES_PATIENCE;   // qw_debug_start_patience
+static thread_local int t_refuse = 0;                // qw_debug_refuse_groups
 static thread_local std::string g_err;
 void set_error(const std::string &msg) { g_err = msg; }
+
+static constexpr int MAX_DEVICES = 64;
+
+// The mask is asked for in every call (0.3 us); the device's count once.
+int stream_cus(hipStream_t s)
+{
+    static std::atomic<int> all[MAX_DEVICES] = {};
+    if (t_refuse == 1) return 0;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    int cus = all[dev].load(std::memory_order_relaxed);
+    if (cus == 0) {
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+            (void)hipGetLastError();
+            return 0;
+        }
+        all[dev].store(cus, std::memory_order_relaxed);
+    }
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    int open = 0;
+    for (uint32_t w : mask) open += __builtin_popcount(w);
+    return open >= cus ? cus : 0;
+}
+
+bool launch_refused(bool back) { return t_refuse == (back ? 3 : 2); }
 
 // ---------------------------------------------------------------------------
 
@@ -577,9 +610,11 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     double c = 0.0, r = 0.0;
     if (poly && info && info->monitor) { set_error("the norm monitor applies to exp(-itH) only"); return QW_EINVAL; }
     const bool monitor = !poly && ((info && info->monitor) || (given_cr && !prep));
-    // one launch for the whole recurrence (unless the degree turns out too large
-    // for the coefficients' place); a cooperative launch is not recorded into graphs
-    bool resident = !monitor && n <= resident_nmax<R>();
+    // one launch for the whole recurrence (unless its workgroups have no room on
+    // the stream's compute units or the degree turns out too large for the
+    // coefficients' place); a cooperative launch is not recorded into graphs
+    const int cus = resident_cus<R>(n, s);
+    bool resident = !monitor && resident_fits<R>(n, cus);
     if (resident && resident_coop<R>(n)) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         QW_HIP(hipStreamIsCapturing(s, &cap));
@@ -662,7 +697,9 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     // where the plan says so, and the stored one is formed only if a pass reads it
     const std::vector<OrientSpec> general = action_plan<R>(n, diag == nullptr);
     std::vector<OrientSpec> pair;
-    if (!monitor) pair = pair_plan<R>(n, diag == nullptr);
+    // (on a stream with masked compute units a cluster's tiles could wait for
+    // partners that have no place beside them)
+    if (!monitor && cus > 0) pair = pair_plan<R>(n, diag == nullptr);
     const std::vector<OrientSpec> &plan = pair.empty() ? general : pair;
     bool any_otf = false;
     for (const OrientSpec &o : plan) any_otf = any_otf || o.otf;
@@ -760,8 +797,8 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
             if (st != QW_OK) return st;
         }
         timer.mark(1);
-        QW_HIP(launch_resident<R>(ra, s, carry ? &blob : nullptr));
-        return timer.finish(info);
+        if (launch_resident<R>(n, &ra, s, carry ? &blob : nullptr, cus) == hipSuccess) return timer.finish(info);
+        (void)hipGetLastError();   // refused after all: passes
     }
 
     if (later && (st = upload_couplings(n, h, J, ws, L, s, &T)) != QW_OK) return st;
@@ -1008,7 +1045,7 @@ qw_status prepare_energy(int n, const double *h, const double *J, void *workspac
     }
     char *ws = static_cast<char *>(workspace);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    *have_q = n > resident_nmax<R>();
+    *have_q = !resident_fits<R>(n, resident_cus<R>(n, s));
     return energy_range<R>(n, (const R *)nullptr, h, J, !*have_q, ws, L, s, T, emin, emax);
 }
 
@@ -1035,15 +1072,17 @@ qw_status scaled_action(int n, const double *h, const double *J, const EnergyTab
 template <typename R>
 qw_status scaled_chain(int n, const EnergyTables &T, double emin, double emax, const std::vector<ChainItem> &items,
                        const void *psi_in, void *psi_out, void *workspace, size_t ws_bytes, void *stream,
-                       long long *terms)
+                       long long *terms, bool *refused)
 {
+    *refused = false;
     using C = typename Cplx<R>::T;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
     const WsLayout L = ws_layout(n, prec_of<R>(), false);
-    if (!chain_fits<R>(n) || ws_bytes < L.total) { set_error("internal: chain of exponentials"); return QW_EINVAL; }
+    if (n < 1 || n > resident_nmax<R>() || ws_bytes < L.total) { set_error("internal: chain of exponentials"); return QW_EINVAL; }
     std::vector<ResStep<R>> steps;
     std::vector<C> coef;
+    long long sum_k = 0;
     for (const ChainItem &it : items) {
         // as scaled_action and action_impl
         double c = it.alpha * 0.5 * (emax + emin);
@@ -1072,7 +1111,7 @@ qw_status scaled_chain(int n, const EnergyTables &T, double emin, double emax, c
             coef_of(alpha, k, cr, ci);
             coef.push_back(C{(R)cr, (R)ci});
         }
-        *terms += K;
+        sum_k += K;
     }
     if (steps.empty()) {
         if (psi_out != psi_in)
@@ -1106,21 +1145,29 @@ qw_status scaled_chain(int n, const EnergyTables &T, double emin, double emax, c
                              coef.data(), coef.size() * sizeof(C) / sizeof(uint64_t), dcoef, ra.flags, RES_MAXFLAGS,
                              ra.start);
     if (st != QW_OK) return st;
-    QW_HIP(launch_resident<R>(ra, s, nullptr));
+    if (launch_resident<R>(n, &ra, s, nullptr, resident_cus<R>(n, s)) != hipSuccess) {
+        (void)hipGetLastError();
+        *refused = true;
+        return QW_OK;
+    }
+    *terms += sum_k;
     return QW_OK;
 }
 
-template <typename R> bool chain_fits(int n) { return n >= 1 && n <= resident_nmax<R>(); }
+template <typename R> bool chain_fits(int n, void *stream)
+{
+    return n >= 1 && resident_fits<R>(n, resident_cus<R>(n, reinterpret_cast<hipStream_t>(stream)));
+}
 template <typename R> bool chain_captures(int n) { return !resident_coop<R>(n); }
 
-template bool chain_fits<float>(int);
-template bool chain_fits<double>(int);
+template bool chain_fits<float>(int, void *);
+template bool chain_fits<double>(int, void *);
 template bool chain_captures<float>(int);
 template bool chain_captures<double>(int);
 template qw_status scaled_chain<float>(int, const EnergyTables &, double, double, const std::vector<ChainItem> &,
-                                       const void *, void *, void *, size_t, void *, long long *);
+                                       const void *, void *, void *, size_t, void *, long long *, bool *);
 template qw_status scaled_chain<double>(int, const EnergyTables &, double, double, const std::vector<ChainItem> &,
-                                        const void *, void *, void *, size_t, void *, long long *);
+                                        const void *, void *, void *, size_t, void *, long long *, bool *);
 template qw_status prepare_energy<float>(int, const double *, const double *, void *, size_t, void *, EnergyTables *,
                                          bool *, double *, double *);
 template qw_status prepare_energy<double>(int, const double *, const double *, void *, size_t, void *, EnergyTables *,
@@ -1144,7 +1191,6 @@ static constexpr int NOALLOC_NMAX = 20;
 static constexpr size_t NOALLOC_BYTES = size_t(22) << 20;   // >= ws_layout(20, 64, false).total
 static __device__ __align__(256) char scratch[NOALLOC_BYTES];
 
-static constexpr int MAX_DEVICES = 64;
 static std::mutex g_scratch_mu;
 static void *g_scratch_ptr[MAX_DEVICES] = {};
 
@@ -1372,6 +1418,13 @@ int qw_debug_start_patience(int looks)
 {
     const int old = t_patience;
     t_patience = looks < 0 ? RES_PATIENCE : looks;
+    return old;
+}
+
+int qw_debug_refuse_groups(int how)
+{
+    const int old = t_refuse;
+    t_refuse = how;
     return old;
 }
 

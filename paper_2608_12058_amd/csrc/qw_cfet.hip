@@ -179,16 +179,30 @@ qw_status cfet_impl(int n, const double *h, const double *J, const double *A_coe
     const void *src = psi_in;
     // sizes whose recurrence is one launch apply several exponentials per launch:
     // the host prepares the next launch while one runs
-    bool chain = chain_fits<R>(n);
+    bool chain = chain_fits<R>(n, stream);
     if (chain && !chain_captures<R>(n)) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         chain = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
     }
+    auto apply = [&](double al, double be, double hs, double tol_exp) -> qw_status {
+        qw_info ai{};
+        const qw_status as = scaled_action<R>(n, h, J, Tb, have_q, al, emin, emax, be, hs, src, psi_out, tol_exp,
+                                              workspace, ws_bytes, stream, &ai);
+        src = psi_out;
+        terms += ai.K;
+        return as;
+    };
     std::vector<ChainItem> items;
     size_t batch = 4;   // a short first launch, so that the device starts early
     auto flush = [&]() -> qw_status {
         if (items.empty()) return QW_OK;
-        const qw_status fs = scaled_chain<R>(n, Tb, emin, emax, items, src, psi_out, workspace, ws_bytes, stream, &terms);
+        bool refused = false;
+        qw_status fs = scaled_chain<R>(n, Tb, emin, emax, items, src, psi_out, workspace, ws_bytes, stream, &terms, &refused);
+        if (refused) {
+            chain = false;
+            for (const ChainItem &it : items)
+                if (fs == QW_OK) fs = apply(it.alpha, it.beta, it.t, it.tol);
+        }
         src = psi_out;
         items.clear();
         batch = CHAIN_ITEMS;
@@ -224,18 +238,14 @@ qw_status cfet_impl(int n, const double *h, const double *J, const double *A_coe
                 const bool large = hs * r > 512.0;
                 if (large || items.size() >= batch) st = flush();
                 if (st != QW_OK) { cleanup(); return st; }
-                if (!large) {
+                if (!large && chain) {
                     items.push_back({al[e], be[e], hs, tol_exp});
                     ++nexp;
                     continue;
                 }
             }
-            qw_info ai{};
-            st = scaled_action<R>(n, h, J, Tb, have_q, al[e], emin, emax, be[e], hs, src, psi_out, tol_exp, workspace,
-                                  ws_bytes, stream, &ai);
+            st = apply(al[e], be[e], hs, tol_exp);
             if (st != QW_OK) { cleanup(); return st; }
-            src = psi_out;
-            terms += ai.K;
             ++nexp;
         }
         if (step_sizes && nsteps < step_cap) step_sizes[nsteps] = hs;

@@ -883,8 +883,21 @@ __global__ void __launch_bounds__(64) k_grad_sums(const double *part, int W, dou
     if (threadIdx.x == 0) sums[blockIdx.x] = s;
 }
 
-template <int T, int NT, int HC, int STRIDE> static hipError_t grad_res_launch(GradRes a, bool back, hipStream_t s)
+// Launches a sweep, or with a == NULL only tells whether both sweeps would be
+// launched (hipSuccess) or have no room on `cus` compute units.
+template <int T, int NT, int HC, int STRIDE>
+static hipError_t grad_res_launch(const GradRes *ask, bool back, hipStream_t s, int cus)
 {
+    static std::atomic<int> per_cu[2];
+    if constexpr (HC > 0) {
+        const void *f[2] = {reinterpret_cast<const void *>(&k_grad_resident<T, NT, HC, false>),
+                            reinterpret_cast<const void *>(&k_grad_resident<T, NT, HC, true>)};
+        for (int i = 0; i < 2; ++i)
+            if (!groups_fit(f[i], NT, STRIDE << HC, cus, per_cu[i])) return hipErrorCooperativeLaunchTooLarge;
+        if (ask && launch_refused(back)) return hipErrorCooperativeLaunchTooLarge;
+    }
+    if (!ask) return hipSuccess;
+    GradRes a = *ask;
     static std::atomic<unsigned> turn{0};   // launches take turns over the XCDs
     a.stride = STRIDE;
     a.sel = (STRIDE > 1) ? (int)(turn.fetch_add(1, std::memory_order_relaxed) % STRIDE) : 0;
@@ -905,22 +918,22 @@ template <int T, int NT, int HC, int STRIDE> static hipError_t grad_res_launch(G
 // 18, 16 segments of 35 terms at 20; windows of 1 to 8, none at 10 and 18), what
 // the passes took in parentheses.  One CU holds one workgroup at 19 and 20 qubits,
 // so like the smaller sizes they are launched cooperatively.
-static hipError_t launch_grad_resident(int n, const GradRes &a, bool back, hipStream_t s)
+static hipError_t launch_grad_resident(int n, const GradRes *a, bool back, hipStream_t s, int cus)
 {
     switch (n) {
-    case 8: return grad_res_launch<8, 128, 0, 1>(a, back, s);   // 0.25 (0.85)
-    case 9: return grad_res_launch<9, 256, 0, 1>(a, back, s);   // 0.35 (1.4)
-    case 10: return grad_res_launch<10, 512, 0, 1>(a, back, s);   // 0.28 (0.81)
-    case 11: return grad_res_launch<11, 512, 0, 1>(a, back, s);   // 0.46 (1.4)
-    case 12: return grad_res_launch<8, 128, 4, 8>(a, back, s);   // 0.60 (2.0)
-    case 13: return grad_res_launch<8, 128, 5, 8>(a, back, s);   // 0.79 (3.3)
-    case 14: return grad_res_launch<9, 256, 5, 8>(a, back, s);   // 0.90 (2.9)
-    case 15: return grad_res_launch<10, 256, 5, 8>(a, back, s);   // 0.93 (2.8)
-    case 16: return grad_res_launch<9, 256, 7, 1>(a, back, s);   // 1.30 (3.7)
-    case 17: return grad_res_launch<9, 256, 8, 1>(a, back, s);   // 1.18 (3.1)
-    case 18: return grad_res_launch<10, 256, 8, 1>(a, back, s);   // 1.49 (3.9)
-    case 19: return grad_res_launch<11, 512, 8, 1>(a, back, s);   // 1.93 (4.3)
-    default: return grad_res_launch<12, 512, 8, 1>(a, back, s);  // 12.1 (24.4)
+    case 8: return grad_res_launch<8, 128, 0, 1>(a, back, s, cus);   // 0.25 (0.85)
+    case 9: return grad_res_launch<9, 256, 0, 1>(a, back, s, cus);   // 0.35 (1.4)
+    case 10: return grad_res_launch<10, 512, 0, 1>(a, back, s, cus);   // 0.28 (0.81)
+    case 11: return grad_res_launch<11, 512, 0, 1>(a, back, s, cus);   // 0.46 (1.4)
+    case 12: return grad_res_launch<8, 128, 4, 8>(a, back, s, cus);   // 0.60 (2.0)
+    case 13: return grad_res_launch<8, 128, 5, 8>(a, back, s, cus);   // 0.79 (3.3)
+    case 14: return grad_res_launch<9, 256, 5, 8>(a, back, s, cus);   // 0.90 (2.9)
+    case 15: return grad_res_launch<10, 256, 5, 8>(a, back, s, cus);   // 0.93 (2.8)
+    case 16: return grad_res_launch<9, 256, 7, 1>(a, back, s, cus);   // 1.30 (3.7)
+    case 17: return grad_res_launch<9, 256, 8, 1>(a, back, s, cus);   // 1.18 (3.1)
+    case 18: return grad_res_launch<10, 256, 8, 1>(a, back, s, cus);   // 1.49 (3.9)
+    case 19: return grad_res_launch<11, 512, 8, 1>(a, back, s, cus);   // 1.93 (4.3)
+    default: return grad_res_launch<12, 512, 8, 1>(a, back, s, cus);  // 12.1 (24.4)
     }
 }
 
@@ -1135,7 +1148,7 @@ static std::vector<int> grad_bounds(int n, const double *h, const double *J, int
 static qw_status grad_impl(int n, const double *h, const double *J, int S, const double *gamma, const double *t,
                            const void *psi0, double tol, int ckpt_every, double *E_out, double *dgamma,
                            double *dt, double *dh, double *dJ, void *workspace, size_t ws_bytes, hipStream_t s,
-                           void *psiT_out, qw_grad_info *info)
+                           void *psiT_out, qw_grad_info *info, bool one_launch)
 {
     qw_status st = grad_validate(n, h, J, S, gamma, t, tol);
     if (st != QW_OK) return st;
@@ -1272,8 +1285,10 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
     for (int q = 0; q < S; ++q) amp_terms += (long long)seg[q].K << n;
     GradRes ra{};
     std::vector<char> tables;
-    bool resident = grad_resident(n) && ws_bytes >= L.total_res && plan[0].h == std::min(n, n > GTB ? TB_NARROW : GTB);
+    bool resident = one_launch && grad_resident(n) && ws_bytes >= L.total_res && plan[0].h == std::min(n, n > GTB ? TB_NARROW : GTB);
     for (const SegPlan &sp : seg) resident = resident && sp.K >= 1;
+    const int cus = resident ? stream_cus(s) : 0;
+    resident = resident && launch_grad_resident(n, nullptr, false, s, cus) == hipSuccess;
     auto clear_sync = [&]() {
         hipLaunchKernelGGL(k_zero_f64, dim3(64), dim3(256), 0, s, reinterpret_cast<double *>(ws + L.sync),
                            (int)(sizeof(int) * RES_LINE * (2 + RES_MAXFLAGS) / sizeof(double)));
@@ -1299,8 +1314,8 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
         ra.c = c;
         ra.nseg = S;
         clear_sync();
-        resident = launch_grad_resident(n, ra, false, s) == hipSuccess;
-        if (!resident) (void)hipGetLastError();   // no cooperative launch here
+        resident = launch_grad_resident(n, &ra, false, s, cus) == hipSuccess;
+        if (!resident) (void)hipGetLastError();   // refused after all: passes
     }
 
     // forward sweep
@@ -1383,9 +1398,6 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
         }
         QW_HIP(hipGetLastError());
     }
-    if (psiT_out)
-        QW_HIP(hipMemcpyAsync(psiT_out, states + (size_t)S * N, N * sizeof(C), hipMemcpyDeviceToDevice, s));
-
     // seed: ybar = 2 H_P psi_S, G = |psi_S|^2, energy
     hipLaunchKernelGGL(k_zero_f64, dim3(64), dim3(256), 0, s, partm, 2 * L.ntiles_lo);
     {
@@ -1404,7 +1416,12 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
     QW_HIP(hipMemcpyAsync(hp.data(), partm, 2 * ntw * sizeof(double), hipMemcpyDeviceToHost, s));
     if (resident) {
         clear_sync();
-        QW_HIP(launch_grad_resident(n, ra, true, s));
+        if (launch_grad_resident(n, &ra, true, s, cus) != hipSuccess) {
+            (void)hipGetLastError();
+            QW_HIP(hipStreamSynchronize(s));   // hp
+            return grad_impl(n, h, J, S, gamma, t, psi0, tol, ckpt_every, E_out, dgamma, dt, dh, dJ, workspace, ws_bytes,
+                             s, psiT_out, info, false);
+        }
         hipLaunchKernelGGL(k_grad_sums, dim3(3 * S), dim3(64), 0, s, (const double *)ra.part, grad_resident_groups(n),
                            reinterpret_cast<double *>(ws + L.sums));
         QW_HIP(hipGetLastError());
@@ -1421,6 +1438,9 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
     double energy = 0.0;
     for (int i = 0; i < ntw; ++i) energy += hp[2 * i];
     *E_out = energy;
+    // (which may be psi0: after the last point from which the call starts again)
+    if (psiT_out)
+        QW_HIP(hipMemcpyAsync(psiT_out, states + (size_t)S * N, N * sizeof(C), hipMemcpyDeviceToDevice, s));
 
     // backward sweep
     for (int q = S - 1; q >= 0 && !resident; --q) {
@@ -1659,7 +1679,7 @@ qw_status qw_anneal_energy_grad_c64(int n, const double *h, const double *J, int
         info->timing = tm;
     }
     return grad_impl(n, h, J, S, gamma, t, psi0, tol, ckpt_every, E, dgamma, dt, dh, dJ, workspace, ws_bytes,
-                     reinterpret_cast<hipStream_t>(stream), psiT_out, info);
+                     reinterpret_cast<hipStream_t>(stream), psiT_out, info, true);
 }
 
 }  // extern "C"

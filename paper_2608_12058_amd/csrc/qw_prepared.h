@@ -33,14 +33,14 @@ qw_status scaled_action(int n, const double *h, const double *J, const EnergyTab
                         double emin, double emax, double beta, double t, const void *psi_in, void *psi_out, double tol,
                         void *workspace, size_t ws_bytes, void *stream, qw_info *info);
 
-// Whether exponentials of n qubits can be applied several to a launch, and
-// whether such a launch can be recorded into a graph.
-template <typename R> bool chain_fits(int n);
+// Whether exponentials of n qubits can be applied several to a launch on this
+// stream, and whether such a launch can be recorded into a graph.
+template <typename R> bool chain_fits(int n, void *stream);
 template <typename R> bool chain_captures(int n);
 
 // Up to CHAIN_ITEMS exponentials exp(-i t (alpha H_P + beta sum_j X_j)), the
 // first first, in one launch (psi_out may be psi_in); adds their degrees to
-// *terms.
+// *terms.  *refused: the launch was refused, nothing has been applied.
 struct ChainItem {
     double alpha, beta, t, tol;
 };
@@ -48,6 +48,6 @@ static constexpr int CHAIN_ITEMS = 32;
 template <typename R>
 qw_status scaled_chain(int n, const EnergyTables &T, double emin, double emax, const std::vector<ChainItem> &items,
                        const void *psi_in, void *psi_out, void *workspace, size_t ws_bytes, void *stream,
-                       long long *terms);
+                       long long *terms, bool *refused);
 
 }  // namespace qw

@@ -499,9 +499,44 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
 // (41 us per term with the spills, 17 in passes); complex128 20 likewise.
 template <typename R> constexpr int resident_nmax() { return sizeof(R) == 4 ? 20 : 19; }
 
-template <typename R, int T, int NT, int HC, int STRIDE, int WPE, bool COOP>
-static hipError_t res_launch(ResArgs<R> a, hipStream_t s, const PutBlob *blob)
+// Compute units on which stream s may run; 0 if some of its device's are masked
+// off, so that nothing is known of how many an XCD has left (qw_action.hip).
+int stream_cus(hipStream_t s);
+// For tests: whether a launch of several workgroups is to be refused (qw_action.hip);
+// `back`: the backward one of two sweeps.
+bool launch_refused(bool back = false);
+
+// Whether `groups` workgroups of a kernel find room side by side on `cus` compute
+// units: the whole device has 256, a partition of it as few as 32.  Where they do
+// not, a cooperative launch would be refused, and a plain one would wait in vain
+// for its common start.  per_cu: the kernel's, asked for once.
+inline bool groups_fit(const void *kernel, int threads, int groups, int cus, std::atomic<int> &per_cu)
 {
+    int m = per_cu.load(std::memory_order_relaxed);
+    if (m == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, kernel, threads, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        per_cu.store(m, std::memory_order_relaxed);
+    }
+    return (int64_t)m * cus >= groups;
+}
+
+// Launches the recurrence, or with a == NULL only tells whether it would be
+// launched (hipSuccess) or has no room on `cus` compute units.
+template <typename R, int T, int NT, int HC, int STRIDE, int WPE, bool COOP>
+static hipError_t res_launch(const ResArgs<R> *ask, hipStream_t s, const PutBlob *blob, int cus)
+{
+    static std::atomic<int> per_cu{0};
+    if constexpr (HC > 0) {
+        const int groups = (COOP ? STRIDE : 1) << HC;
+        if (!groups_fit(reinterpret_cast<const void *>(&k_resident<R, T, NT, HC, WPE>), NT, groups, cus, per_cu) ||
+            (ask && launch_refused()))
+            return hipErrorCooperativeLaunchTooLarge;
+    }
+    if (!ask) return hipSuccess;
+    ResArgs<R> a = *ask;
     // launches take turns over the XCDs, so that calls on several streams do not
     // crowd one
     static std::atomic<unsigned> turn{0};
@@ -546,43 +581,54 @@ template <typename R> constexpr bool resident_single(int n) { return n <= (sizeo
 // where it takes 2.0 us and more, since 32 CUs would spend longer on a term
 // (17 qubits: 5.2 us).
 template <typename R>
-static hipError_t launch_resident(const ResArgs<R> &a, hipStream_t s, const PutBlob *blob)
+static hipError_t launch_resident(int n, const ResArgs<R> *a, hipStream_t s, const PutBlob *blob, int cus)
 {
     if constexpr (sizeof(R) == 4) {
-        switch (a.n) {
-        case 8: return res_launch<R, 8, 128, 0, 1, 1, false>(a, s, blob);       // 0.31 (1.2)
-        case 9: return res_launch<R, 9, 256, 0, 1, 1, false>(a, s, blob);       // 0.36 (1.2)
-        case 10: return res_launch<R, 10, 512, 0, 1, 1, false>(a, s, blob);     // 0.45 (1.3)
-        case 11: return res_launch<R, 11, 1024, 0, 1, 1, false>(a, s, blob);    // 0.78 (1.9)
-        case 12: return res_launch<R, 8, 128, 4, 8, 1, false>(a, s, blob);      // 0.91 (3.1)
-        case 13: return res_launch<R, 8, 128, 5, 8, 1, false>(a, s, blob);      // 1.03 (5.6)
-        case 14: return res_launch<R, 9, 256, 5, 8, 1, false>(a, s, blob);      // 1.25 (5.8)
-        case 15: return res_launch<R, 10, 256, 5, 8, 4, false>(a, s, blob);     // 1.57 (5.8)
-        case 16: return res_launch<R, 9, 256, 7, 1, 4, false>(a, s, blob);      // 2.12 (6.3)
-        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s, blob);      // 2.60 (6.6)
-        case 18: return res_launch<R, 10, 256, 8, 1, 4, false>(a, s, blob);     // 3.78 (7.6)
-        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob);      // 5.56 (9.7)
-        case 20: return res_launch<R, 12, 512, 8, 1, 1, true>(a, s, blob);      // 6.40 (9.6)
-        default: return res_launch<R, 7, 64, 0, 1, 1, false>(a, s, blob);       // 0.29 (1.2)
+        switch (n) {
+        case 8: return res_launch<R, 8, 128, 0, 1, 1, false>(a, s, blob, cus);       // 0.31 (1.2)
+        case 9: return res_launch<R, 9, 256, 0, 1, 1, false>(a, s, blob, cus);       // 0.36 (1.2)
+        case 10: return res_launch<R, 10, 512, 0, 1, 1, false>(a, s, blob, cus);     // 0.45 (1.3)
+        case 11: return res_launch<R, 11, 1024, 0, 1, 1, false>(a, s, blob, cus);    // 0.78 (1.9)
+        case 12: return res_launch<R, 8, 128, 4, 8, 1, false>(a, s, blob, cus);      // 0.91 (3.1)
+        case 13: return res_launch<R, 8, 128, 5, 8, 1, false>(a, s, blob, cus);      // 1.03 (5.6)
+        case 14: return res_launch<R, 9, 256, 5, 8, 1, false>(a, s, blob, cus);      // 1.25 (5.8)
+        case 15: return res_launch<R, 10, 256, 5, 8, 4, false>(a, s, blob, cus);     // 1.57 (5.8)
+        case 16: return res_launch<R, 9, 256, 7, 1, 4, false>(a, s, blob, cus);      // 2.12 (6.3)
+        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s, blob, cus);      // 2.60 (6.6)
+        case 18: return res_launch<R, 10, 256, 8, 1, 4, false>(a, s, blob, cus);     // 3.78 (7.6)
+        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob, cus);      // 5.56 (9.7)
+        case 20: return res_launch<R, 12, 512, 8, 1, 1, true>(a, s, blob, cus);      // 6.40 (9.6)
+        default: return res_launch<R, 7, 64, 0, 1, 1, false>(a, s, blob, cus);       // 0.29 (1.2)
         }
     } else {
-        switch (a.n) {
-        case 7: return res_launch<R, 7, 128, 0, 1, 1, false>(a, s, blob);       // 0.31 (1.1)
-        case 8: return res_launch<R, 8, 256, 0, 1, 1, false>(a, s, blob);       // 0.31 (1.1)
-        case 9: return res_launch<R, 9, 512, 0, 1, 1, false>(a, s, blob);       // 0.44 (1.2)
-        case 10: return res_launch<R, 10, 1024, 0, 1, 1, false>(a, s, blob);    // 0.70 (1.3)
-        case 11: return res_launch<R, 8, 256, 3, 8, 1, false>(a, s, blob);      // 0.79 (2.0)
-        case 12: return res_launch<R, 7, 128, 5, 8, 1, false>(a, s, blob);      // 0.90 (3.4)
-        case 13: return res_launch<R, 8, 256, 5, 8, 1, false>(a, s, blob);      // 1.11 (7.8)
-        case 14: return res_launch<R, 9, 256, 5, 8, 4, false>(a, s, blob);      // 1.42 (8.1)
-        case 15: return res_launch<R, 8, 256, 7, 1, 4, false>(a, s, blob);      // 2.01 (8.6)
-        case 16: return res_launch<R, 8, 256, 8, 1, 4, false>(a, s, blob);      // 2.52 (9.1)
-        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s, blob);      // 3.60 (10.3)
-        case 18: return res_launch<R, 10, 1024, 8, 1, 1, true>(a, s, blob);     // 5.43 (12.3)
-        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob);      // 6.35 (13.0)
-        default: return res_launch<R, 6, 64, 0, 1, 1, false>(a, s, blob);       // 0.25 (1.1)
+        switch (n) {
+        case 7: return res_launch<R, 7, 128, 0, 1, 1, false>(a, s, blob, cus);       // 0.31 (1.1)
+        case 8: return res_launch<R, 8, 256, 0, 1, 1, false>(a, s, blob, cus);       // 0.31 (1.1)
+        case 9: return res_launch<R, 9, 512, 0, 1, 1, false>(a, s, blob, cus);       // 0.44 (1.2)
+        case 10: return res_launch<R, 10, 1024, 0, 1, 1, false>(a, s, blob, cus);    // 0.70 (1.3)
+        case 11: return res_launch<R, 8, 256, 3, 8, 1, false>(a, s, blob, cus);      // 0.79 (2.0)
+        case 12: return res_launch<R, 7, 128, 5, 8, 1, false>(a, s, blob, cus);      // 0.90 (3.4)
+        case 13: return res_launch<R, 8, 256, 5, 8, 1, false>(a, s, blob, cus);      // 1.11 (7.8)
+        case 14: return res_launch<R, 9, 256, 5, 8, 4, false>(a, s, blob, cus);      // 1.42 (8.1)
+        case 15: return res_launch<R, 8, 256, 7, 1, 4, false>(a, s, blob, cus);      // 2.01 (8.6)
+        case 16: return res_launch<R, 8, 256, 8, 1, 4, false>(a, s, blob, cus);      // 2.52 (9.1)
+        case 17: return res_launch<R, 9, 256, 8, 1, 4, false>(a, s, blob, cus);      // 3.60 (10.3)
+        case 18: return res_launch<R, 10, 1024, 8, 1, 1, true>(a, s, blob, cus);     // 5.43 (12.3)
+        case 19: return res_launch<R, 11, 512, 8, 1, 1, true>(a, s, blob, cus);      // 6.35 (13.0)
+        default: return res_launch<R, 6, 64, 0, 1, 1, false>(a, s, blob, cus);       // 0.25 (1.1)
         }
     }
+}
+
+// What launch_resident asks of the stream: its compute units, if the size takes
+// more than one workgroup.
+template <typename R> static int resident_cus(int n, hipStream_t s) { return resident_single<R>(n) ? 1 : stream_cus(s); }
+
+// Whether a call of n qubits can run in one launch on `cus` compute units.
+template <typename R> static bool resident_fits(int n, int cus)
+{
+    return n <= resident_nmax<R>() &&
+           (resident_single<R>(n) || launch_resident<R>(n, nullptr, nullptr, nullptr, cus) == hipSuccess);
 }
 
 }  // namespace qw
