@@ -34,7 +34,11 @@
  *     largest sizes in each precision are launched cooperatively, and in passes
  *     where a stream is being captured.  Where the workgroups have no room side by
  *     side (a partitioned device, a stream with masked compute units, a refused
- *     cooperative launch) every such size runs in passes.
+ *     cooperative launch) every such size runs in passes.  A workgroup that waits
+ *     for another for seconds (a device that stopped running it) gives up: the
+ *     amplitudes that depend on the other are then NaN, the rest are right, and
+ *     the call, which does not wait for its recurrence, has returned QW_OK.  The
+ *     gradient looks for such values and starts again in passes.
  *   - Errors: every call returns a qw_status; nothing is thrown across the ABI.
  *     qw_last_error() returns a thread-local message for the last failure.
  *   - Calls on distinct workspaces may run concurrently from different threads.
@@ -449,6 +453,11 @@ int qw_debug_schedule(int K, int P, int *out, int cap);
  * thread from now on; negative: the default, some 0.1 s).  The results differ
  * only by rounding.  Returns the value before. */
 int qw_debug_start_patience(int looks);
+
+/* For tests: how often a wave of a one-launch recurrence or sweep looks at a
+ * partner's flag before it gives up (calls of this host thread from now on;
+ * negative: the default, seconds).  Returns the value before. */
+int qw_debug_wait_limit(int looks);
 
 /* For tests: refuse one-launch recurrences and sweeps of several workgroups (calls
  * of this host thread from now on): 1 as on a stream with masked compute units,

@@ -36,6 +36,7 @@
 namespace qw {
 
 static thread_local int t_patience = RES_PATIENCE;   // qw_debug_start_patience
+static thread_local int t_polls = RES_POLLS;         // qw_debug_wait_limit
 static thread_local int t_refuse = 0;                // qw_debug_refuse_groups
 static thread_local std::string g_err;
 void set_error(const std::string &msg) { g_err = msg; }
@@ -70,6 +71,7 @@ int stream_cus(hipStream_t s)
     return open >= cus ? cus : 0;
 }
 
+int wait_polls() { return t_polls; }
 bool launch_refused(bool back) { return t_refuse == (back ? 3 : 2); }
 
 // ---------------------------------------------------------------------------
@@ -780,6 +782,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         ra.sub = horner ? R(0) : R(1);
         ra.n = n;
         ra.patience = t_patience;
+        ra.polls = t_polls;
         C *dcoef = reinterpret_cast<C *>(ws + (own_coef ? L.coef : L.qt));
         ra.coef = dcoef;
         const std::vector<double> hj = later ? packed_couplings(n, h, J) : std::vector<double>();
@@ -1141,6 +1144,7 @@ qw_status scaled_chain(int n, const EnergyTables &T, double emin, double emax, c
     ra.sub = R(1);
     ra.n = n;
     ra.patience = t_patience;
+    ra.polls = t_polls;
     const qw_status st = put(steps.data() + 1, (steps.size() - 1) * sizeof(ResStep<R>) / sizeof(uint64_t), ws + L.q, s,
                              coef.data(), coef.size() * sizeof(C) / sizeof(uint64_t), dcoef, ra.flags, RES_MAXFLAGS,
                              ra.start);
@@ -1418,6 +1422,13 @@ int qw_debug_start_patience(int looks)
 {
     const int old = t_patience;
     t_patience = looks < 0 ? RES_PATIENCE : looks;
+    return old;
+}
+
+int qw_debug_wait_limit(int looks)
+{
+    const int old = t_polls;
+    t_polls = looks < 0 ? RES_POLLS : looks;
     return old;
 }
 

@@ -450,6 +450,7 @@ struct GradRes {
     double c;
     int nseg;
     int stride, sel;           // workgroups with blockIdx.x % stride == sel take part
+    int polls;                 // looks at a flag before giving up on a partner
 };
 
 // One sweep over all segments by W = 2^HC workgroups that hold one tile of 2^T
@@ -558,6 +559,7 @@ template <int T, int NT, int HC, bool BACK> __global__ void __launch_bounds__(NT
             s.v[v].y += y.v[v].y;
         }
     };
+    GradSeg sg{};
     // Flips of the published x, whose other tiles are at p, handed to elem(q, the
     // first group's sum, the second's).  The partners' vectors of QG of a thread's
     // own are under way at a time: with two or four instead of one of its four, 20
@@ -581,10 +583,11 @@ template <int T, int NT, int HC, bool BACK> __global__ void __launch_bounds__(NT
         }
         if constexpr (HC > 0) {
             if (!lost) {
-                int left = RES_POLLS;
+                int left = a.polls;
                 while (__any(lane < HC && __hip_atomic_load(peer, __ATOMIC_RELAXED, QW_AGENT) < t))
-                    if (--left == 0) { lost = true; break; }
+                    if (--left <= 0) { lost = true; break; }
             }
+            if (lost) sg.g = NAN;   // as in k_resident: no finite number is a wrong one
             asm volatile("" ::: "memory");
         }
         const auto rs = rsrc(p);
@@ -629,7 +632,6 @@ template <int T, int NT, int HC, bool BACK> __global__ void __launch_bounds__(NT
 #pragma unroll
         for (int v = 0; v < VE; ++v) er[q][v] = a.erel[at(q) + v];
 
-    GradSeg sg{};
     C ck{0.f, 0.f};           // lane l: c_{64 i + l}
     double dx = 0.0, dy = 0.0;
     uint64_t pl = 0;
@@ -1313,6 +1315,7 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
         ra.flags = ra.start + 2 * RES_LINE;
         ra.c = c;
         ra.nseg = S;
+        ra.polls = wait_polls();
         clear_sync();
         resident = launch_grad_resident(n, &ra, false, s, cus) == hipSuccess;
         if (!resident) (void)hipGetLastError();   // refused after all: passes
@@ -1428,6 +1431,13 @@ static qw_status grad_impl(int n, const double *h, const double *J, int S, const
         std::vector<double> sums(3 * (size_t)S);
         QW_HIP(hipMemcpyAsync(sums.data(), ws + L.sums, sums.size() * sizeof(double), hipMemcpyDeviceToHost, s));
         QW_HIP(hipStreamSynchronize(s));
+        // NaN: a wait was given up (or the state held one): again in passes
+        bool whole = true;
+        for (int i = 0; i < ntw; ++i) whole = whole && finite(hp[2 * i]);
+        for (double x : sums) whole = whole && finite(x);
+        if (!whole)
+            return grad_impl(n, h, J, S, gamma, t, psi0, tol, ckpt_every, E_out, dgamma, dt, dh, dJ, workspace, ws_bytes,
+                             s, psiT_out, info, false);
         for (int q = 0; q < S; ++q) {
             dt[q] = sums[3 * q] + sums[3 * q + 2];
             dgamma[q] = sums[3 * q + 1] / seg[q].r;

@@ -22,6 +22,7 @@ static constexpr int RES_LINE = 32;            // 4-byte words per line
 static constexpr int RES_MAXFLAGS = 4096;
 static constexpr int RES_PATIENCE = 1 << 17;   // looks at the start word, some 0.1 s
 static constexpr int RES_POLLS = 1 << 24;      // looks at a flag, seconds
+int wait_polls();                              // the same, or what a test has set (qw_action.hip)
 
 // Small host arrays travel as kernel arguments (a launch keeps its own copy, so
 // nothing on the host has to outlive the call and no copy engine is involved).
@@ -57,6 +58,7 @@ template <typename R> struct ResArgs {
     int n;
     int stride, sel;      // workgroups with blockIdx.x % stride == sel take part
     int patience;         // looks at the start word before giving up on a common start
+    int polls;            // looks at a flag before giving up on a partner
 };
 
 // E(z) from couplings in LDS (h, then J packed), in double.
@@ -241,6 +243,9 @@ template <typename R, int CTRL> __device__ __forceinline__ CVec<R> lane_flip(con
 // A wave overwrites a buffer only after the flags of the next round, which its
 // partners raise after they have read it, so two buffers and one barrier per
 // term (of the workgroup, for its LDS tile) suffice.
+// A wave that gives up on a partner goes on with NaN in all its amplitudes.  It may
+// then overwrite a buffer that a late partner still reads, which finds there what it
+// came for or NaN, and passes that on: a finite amplitude is a right one.
 // Every exchanged word passes the L1 (sc1 loads); stores go through to memory
 // unless all workgroups sit on one XCD, whose L2 they then share.
 // What bounds it: the latency of that round, not bytes: about 0.3 us for the
@@ -426,9 +431,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
             }
             if constexpr (HC > 0) {
                 if (!lost) {
-                    int left = RES_POLLS;
+                    int left = a.polls;
                     while (__any(lane < HC && __hip_atomic_load(peer, __ATOMIC_RELAXED, QW_AGENT) < t))
-                        if (--left == 0) { lost = true; break; }
+                        if (--left <= 0) {
+                            lost = true;
+                            st.g = R(NAN);
+                            break;
+                        }
                 }
                 asm volatile("" ::: "memory");
 #pragma unroll
@@ -483,9 +492,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         if (!inside(q)) continue;
-#pragma unroll
-        for (int v = 0; v < VE; ++v)
-            if (lost) ps[q].v[v] = C{R(NAN), R(NAN)};   // a wave that all were waiting for is gone
         st_v<R, false>(a.out + base + (uint32_t)(q * NT + tid) * VE, ps[q]);
     }
 }
