@@ -871,7 +871,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         pa.flag = reinterpret_cast<int *>(norms);
         pa.flag_step = (int)std::min<uint64_t>(RES_LINE, half / sizeof(int) / nt);
         pa.late = reinterpret_cast<int *>(reinterpret_cast<char *>(norms) + half);
-        pa.patience = t_patience;
+        pa.patience = std::min(t_patience, CROSS_PATIENCE);
         if (pa.flag_step < 1 || (nt + 1) * sizeof(int) > half) { set_error("internal: room for the flags"); return QW_EINVAL; }
         hipLaunchKernelGGL(k_fill_zero<0>, dim3(64), dim3(256), 0, s, norms, (uint64_t)KMAX_MON);
     }

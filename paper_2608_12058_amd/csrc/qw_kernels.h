@@ -285,7 +285,8 @@ template <typename R> struct PassArgs {
     double *norm_acc = nullptr;   // if set: += sum |b|^2 of the completed vector (atomic, one per block)
     int xcd_order = 0;            // 1: blocks take tiles in XCD-major order (xcd_tile)
     int *flag = nullptr;          // cross bits: one word per tile, flag[tile * flag_step]
-    int *late = nullptr;          // cross bits: tiles whose second half is left to k_pass_late
+    int *late = nullptr;          // cross bits: nonzero if a tile of the call has given up; per tile, the
+                                  // round in which its second half was left to k_pass_late
     int flag_step = 0, round = 0; // the word of a tile that has reached this pass's middle: its round number
     int patience = 0;             // looks at a flag before giving up
     int b1_scaled = 0;            // 1: b1 points at psi and b_{k+1} = (b1r + i b1i) psi (the
@@ -392,18 +393,40 @@ __device__ __forceinline__ int cross_word(int round)
     return round * 16 + (int)__builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, 4 bits
 }
 
+// What a partner's word says to a tile whose own is `word`: the partner has stored
+// b_k on this XCD; it has not come so far; it has, but on another XCD, so that the
+// words will never be equal.
+enum { CROSS_MET, CROSS_NOT_YET, CROSS_NEVER };
+__host__ __device__ __forceinline__ int cross_state(int seen, int word)
+{
+    return seen == word ? CROSS_MET : (seen >> 4) == (word >> 4) ? CROSS_NEVER : CROSS_NOT_YET;
+}
+
+// Looks at the partners before a tile gives them up, 0.8 ms: 30 times what a tile
+// takes.
+static constexpr int CROSS_PATIENCE = 1 << 10;
+
 // One wave: true once the words of the XH partners of `tile` (its id with one of
 // the bits shift .. shift + XH - 1 flipped) equal `word`: all of them have
-// stored b_k, on this XCD.
+// stored b_k, on this XCD.  False after `patience` looks, or as soon as one of them
+// cannot come to be equal, or if another tile of the call has given up before
+// (late[0]): then the CUs are crowded.  Tiles of one call hold up to 2^XH - 1 CUs
+// of an XCD while they wait for the last of their cluster, and three calls at once
+// with four cross bits hold all 32 of them.  With 0.1 s of patience for each tile
+// four calls of 28 qubits took 8.4 s instead of 0.27.
 template <int XH>
-__device__ __forceinline__ bool cross_meet(const int *flag, int step, uint64_t tile, int shift, int word, int patience)
+__device__ __forceinline__ bool cross_meet(const int *flag, int step, uint64_t tile, int shift, int word, int patience,
+                                           const int *late)
 {
     const int lane = threadIdx.x & 63;
-    const int *p = flag + (tile ^ (lane < XH ? uint64_t(1) << (shift + lane) : 0)) * step;
-    bool met = false;
-    do {
-        met = !__any(lane < XH && __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != word);
-    } while (!met && --patience > 0);
+    const int *p = lane == XH ? late : flag + (tile ^ (lane < XH ? uint64_t(1) << (shift + lane) : 0)) * step;
+    bool met = false, crowded = false;
+    while (!met && !crowded && patience-- > 0) {
+        const int seen = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int state = lane < XH ? cross_state(seen, word) : CROSS_MET;
+        met = !__any(state != CROSS_MET);
+        crowded = __any(state == CROSS_NEVER || (lane == XH && seen != 0));
+    }
     asm volatile("" ::: "memory");
     return met;
 }
@@ -690,12 +713,13 @@ __device__ __forceinline__ void pass_tile(const PassArgs<R> &a, uint64_t tile, t
         if constexpr (XH > 0 && !LATE) {
             __shared__ int met;
             if (threadIdx.x < 64) {
-                const bool ok = cross_meet<XH>(a.flag, a.flag_step, tile, a.g0 - a.L, cross_word(a.round), a.patience);
+                const bool ok = cross_meet<XH>(a.flag, a.flag_step, tile, a.g0 - a.L, cross_word(a.round), a.patience,
+                                               a.late);
                 if (threadIdx.x == 0) {
                     met = ok;
                     if (!ok) {
                         a.late[1 + tile] = a.round;
-                        (void)__hip_atomic_fetch_add(a.late, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(a.late, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
                 }
             }
@@ -785,12 +809,12 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_
 // launched before it or are the next in line on that XCD, so the wait is short
 // unless other work holds the CUs (without it 26 qubits took 615 us against 616);
 // it ends after `patience` looks in any case, or in vain if a partner ran on
-// another XCD, and then the tile's second half is left to k_pass_late, which
-// follows every FUSED pass and finds nothing to do as a rule.  A tile writes
-// b_{k-1} over b_{k+1} only after its partners, which read it, have passed their
-// middle.  A stale L1 line cannot be met: the vectors of a partner's tile are read
-// only by that tile and, after its flag, by its partners, and a store by the same
-// CU replaces the line.
+// another XCD or the CUs are crowded (cross_meet), and then the tile's second half is
+// left to k_pass_late, which follows every FUSED pass and finds nothing to do as a
+// rule.  A tile writes b_{k-1} over b_{k+1} only after its partners, which read it,
+// have passed their middle.  A stale L1 line cannot be met: the vectors of a
+// partner's tile are read only by that tile and, after its flag, by its partners,
+// and a store by the same CU replaces the line.
 // What bounds it: rows of 128 B and one workgroup per CU, 3.9 TB/s at 25-27
 // qubits (the contiguous 2^14 tiles: 5.5); each cross bit adds 2 % at two bits and
 // 8 % at four, where the partners' vectors outgrow the L2.  Rows of 256 B with one
@@ -820,7 +844,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_
 {
     __shared__ typename Cplx<R>::T lds[1 << TB];
     if (a.late[0] == 0) return;
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    for (int b = blockIdx.x; b < ntiles; b += gridDim.x) {   // clusters side by side on their XCD, as before
+        const int t = (int)cross_tile<XH>((uint32_t)b, (uint32_t)ntiles, a.g0 - a.L);
         if (a.late[1 + t] != a.round) continue;
         __syncthreads();   // lds of the tile before
         pass_tile<R, TB, NT, PM_FUSED, OTF, STREAM, KEEP_PD, XH, true>(a, (uint64_t)t, lds);
@@ -1094,6 +1119,9 @@ template <typename R> inline std::vector<OrientSpec> action_plan(int n, bool dia
 // (810), 26: 1195 (1570), 27: 2705 (3190).  Five cross bits are slower than a third
 // orientation (28 qubits on 2^13 tiles: 3053); at 24 qubits complex64 keeps its two
 // orientations of 2^14 tiles (140; contiguous 2^12 tiles and two cross bits 153).
+// Several calls at once share the L2 that the partners' vectors come from: 28 qubits,
+// 25 terms, two at once 143 ms (three orientations 143), three 259 (218), four 403
+// (298); complex128 27 four 343 (304); with three cross bits 27 qubits four 163 (179).
 // Complex128 at 22 qubits needs no cross bit with rows of 64 B, as at 21
 // (cached_plan): 61.4 (94.1; rows of 128 B 63.9).  The
 // strided orientation rebuilds the diagonal from 26 qubits; the contiguous one
