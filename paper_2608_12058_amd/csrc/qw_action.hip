@@ -695,19 +695,6 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     const double norm_c = (es != 0.0) ? c / es : 0.0, norm_inv_r = es * inv_r;
     R *dn = otf ? nullptr : reinterpret_cast<R *>(ws + L.d);
     double *qt = reinterpret_cast<double *>(ws + L.qt);
-    // orientations and launch shapes; the end orientations rebuild the diagonal
-    // where the plan says so, and the stored one is formed only if a pass reads it
-    const std::vector<OrientSpec> general = action_plan<R>(n, diag == nullptr);
-    std::vector<OrientSpec> pair;
-    // (on a stream with masked compute units a cluster's tiles could wait for
-    // partners that have no place beside them)
-    if (!monitor && cus > 0) pair = pair_plan<R>(n, diag == nullptr);
-    const std::vector<OrientSpec> &plan = pair.empty() ? general : pair;
-    bool any_otf = false;
-    for (const OrientSpec &o : plan) any_otf = any_otf || o.otf;
-    if (any_otf && !(L.ft != size_t(-1))) { set_error("internal: no per-tile field table for this size"); return QW_EINVAL; }
-    double *ft = any_otf ? reinterpret_cast<double *>(ws + L.ft) : nullptr;
-    const uint64_t ft_stride = (N >> TB_NARROW) * TILE_FIELDS;   // doubles per orientation
     // coefficients (host, double): c_k = (-i)^k alpha_k, or the caller's
     const double a = poly ? 0.0 : t * r;
     std::vector<double> alpha;
@@ -728,6 +715,19 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
             coef_of(alpha, k, cre[k], cim[k]);
         }
     }
+    // orientations and launch shapes; the end orientations rebuild the diagonal
+    // where the plan says so, and the stored one is formed only if a pass reads it
+    const std::vector<OrientSpec> general = action_plan<R>(n, diag == nullptr);
+    std::vector<OrientSpec> pair;
+    // (on a stream with masked compute units a cluster's tiles could wait for
+    // partners that have no place beside them)
+    if (!monitor && cus > 0) pair = pair_plan<R>(n, diag == nullptr, K);
+    const std::vector<OrientSpec> &plan = pair.empty() ? general : pair;
+    bool any_otf = false;
+    for (const OrientSpec &o : plan) any_otf = any_otf || o.otf;
+    if (any_otf && !(L.ft != size_t(-1))) { set_error("internal: no per-tile field table for this size"); return QW_EINVAL; }
+    double *ft = any_otf ? reinterpret_cast<double *>(ws + L.ft) : nullptr;
+    const uint64_t ft_stride = (N >> TB_NARROW) * TILE_FIELDS;   // doubles per orientation
     const bool horner = poly && poly->horner;
     if (info) {
         info->K = K;
@@ -759,6 +759,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         if (n <= Cfg<R>::TB) { set_error("degree too large for the on-chip path"); return QW_ENOMEM; }
         resident = false;
     }
+    if (diag && K < resident_kmin<R>(n)) resident = false;
     if (resident && !own_coef && (size_t)(K + 1) * sizeof(C) > 4 * (size_t(1) << TB_WIDE) * sizeof(double)) resident = false;
     if (resident) {
         std::vector<C> ch(K + 1);
@@ -1012,7 +1013,7 @@ static int check_orientations(const std::vector<OrientSpec> &spec, int n)
 
 int check_plan(int n, int prec)
 {
-    const std::vector<OrientSpec> pair = (prec == 64) ? pair_plan<float>(n, true) : pair_plan<double>(n, true);
+    const std::vector<OrientSpec> pair = (prec == 64) ? pair_plan<float>(n, true, 2) : pair_plan<double>(n, true, 2);
     if (!pair.empty()) {
         const int rc = check_orientations(pair, n);
         if (rc < 0) return rc;

@@ -1127,7 +1127,11 @@ template <typename R> inline std::vector<OrientSpec> action_plan(int n, bool dia
 // strided orientation rebuilds the diagonal from 26 qubits; the contiguous one
 // does in complex128, while in complex64 its 4 of 44 bytes are cheaper read (28
 // qubits: 2006 us per pass against 2131).
-template <typename R> inline std::vector<OrientSpec> pair_plan(int n, bool diag_from_tables)
+// K: the degree.  A single term with four cross bits is a start pass whose partners'
+// psi come from memory and one add pass: complex64 28 qubits 3.80 ms against 3.60 in
+// three orientations (from two terms on, 6.53 against 6.66; complex128 27 with one
+// term 2.84 against 3.72).
+template <typename R> inline std::vector<OrientSpec> pair_plan(int n, bool diag_from_tables, int K)
 {
     std::vector<OrientSpec> S;
     const bool st = stream_for<R>(n);
@@ -1142,6 +1146,7 @@ template <typename R> inline std::vector<OrientSpec> pair_plan(int n, bool diag_
         S.push_back({{TB_LOW_D - 9, TB, 9}, low, low, false, 1, 0});
         return S;
     }
+    if (sizeof(R) == 4 && xh == 4 && K < 2) return S;
     const TileCfg wide{TB, NT_WIDE, st, 0, kp};
     const int h = n - TB - xh;
     const bool otf = diag_from_tables && n >= OTF_TOP_NMIN;

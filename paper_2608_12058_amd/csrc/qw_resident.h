@@ -575,6 +575,19 @@ static hipError_t res_launch(const ResArgs<R> *ask, hipStream_t s, const PutBlob
 // starts.)  A cooperative launch costs 8 us more than a plain one.
 template <typename R> constexpr bool resident_coop(int n) { return n >= (sizeof(R) == 4 ? 19 : 18); }
 
+// Smallest degree that takes the one launch with the caller's diagonal.  A
+// cooperative launch of 256 workgroups costs 18-27 us more than a pass and a term
+// 3-6 us less, so the passes are faster below (in us, passes against one launch):
+// complex64 19 qubits 6 terms 64.4 / 64.5, 8: 83.6 / 75.5; 20: 8: 83.8 / 87.0, 10:
+// 102.7 / 99.4; complex128 18: 3: 41.6 / 49.1, 4: 54.2 / 52.4; 19: 4: 57.3 / 57.8, 5:
+// 72.9 / 67.9.  With (h, J) the passes have 60 us of tables to build besides, and one
+// launch is faster from the first term (20 qubits 86.5 / 53.6).
+template <typename R> constexpr int resident_kmin(int n)
+{
+    if (!resident_coop<R>(n)) return 1;
+    return sizeof(R) == 4 ? (n == 19 ? 7 : 9) : (n == 18 ? 4 : 5);
+}
+
 // Sizes of one workgroup, whose launch can carry coefficients and couplings.
 template <typename R> constexpr bool resident_single(int n) { return n <= (sizeof(R) == 4 ? 11 : 10); }
 
