@@ -599,36 +599,52 @@ static qw_status side_stream(hipStream_t *out)
     return QW_OK;
 }
 
-// Enqueues the launches on s (captured or not).  The one-workgroup launch goes
-// first; with `side` it runs on the side stream between a fork and a join
-// event, so it overlaps the passes.
-static qw_status replay(const std::vector<BLaunch> &Ls, const BatchDesc *dD, const OnchipItem *ditems,
-                        const int *dorder, int nsmall, hipStream_t s, hipStream_t side, hipEvent_t fork,
-                        hipEvent_t join)
+static void launch_small(unsigned grid, const OnchipItem *ditems, const int *dorder, int nsmall, hipStream_t s)
 {
-    bool joined = true;
+    hipLaunchKernelGGL(k_onchip, dim3(grid), dim3(ONCHIP_NT), 0, s, ditems, dorder, nsmall);
+}
+
+// Enqueues the launches on s (captured or not).
+static qw_status replay(const std::vector<BLaunch> &Ls, const BatchDesc *dD, const OnchipItem *ditems,
+                        const int *dorder, int nsmall, hipStream_t s)
+{
     for (const BLaunch &L : Ls) {
-        if (L.onchip) {
-            hipStream_t os = s;
-            if (side) {
-                QW_HIP(hipEventRecord(fork, s));
-                QW_HIP(hipStreamWaitEvent(side, fork, 0));
-                os = side;
-                joined = false;
-            }
-            hipLaunchKernelGGL(k_onchip, dim3(L.grid), dim3(ONCHIP_NT), 0, os,
-                               ditems, dorder, nsmall);
-            if (side) QW_HIP(hipEventRecord(join, side));
-            continue;
-        }
-        if (L.cls == BC_NARROW) launch_class<BC_NARROW>(L, dD, s);
+        if (L.onchip) launch_small(L.grid, ditems, dorder, nsmall, s);
+        else if (L.cls == BC_NARROW) launch_class<BC_NARROW>(L, dD, s);
         else if (L.cls == BC_WIDE_T) launch_class<BC_WIDE_T>(L, dD, s);
         else launch_class<BC_MID>(L, dD, s);
     }
-    if (!joined) QW_HIP(hipStreamWaitEvent(s, join, 0));
     QW_HIP(hipGetLastError());
     return QW_OK;
 }
+
+// The one-workgroup launch on the side stream, from what s has done so far (fork)
+// until what it does next (join).  It is never part of a graph: the side stream is
+// shared by the threads of the process, and while one of them captured it, the
+// launches of another went into that graph.
+struct Beside {
+    hipStream_t s, side;
+    hipEvent_t fork, join;
+    bool open = false;
+    qw_status start(unsigned grid, const OnchipItem *ditems, const int *dorder, int nsmall)
+    {
+        QW_HIP(hipEventRecord(fork, s));
+        QW_HIP(hipStreamWaitEvent(side, fork, 0));
+        launch_small(grid, ditems, dorder, nsmall, side);
+        QW_HIP(hipGetLastError());
+        QW_HIP(hipEventRecord(join, side));
+        open = true;
+        return QW_OK;
+    }
+    qw_status finish()
+    {
+        if (!open) return QW_OK;
+        open = false;
+        QW_HIP(hipStreamWaitEvent(s, join, 0));
+        return QW_OK;
+    }
+    ~Beside() { (void)finish(); }
+};
 
 // Instantiated graphs of recent calls, keyed by the device and the exact launch
 // sequence with every kernel argument (the places of the descriptors, items, order
@@ -645,10 +661,10 @@ static std::mutex g_graph_mu;
 static std::vector<GraphEntry> g_graphs;
 
 static std::string launch_key(const std::vector<BLaunch> &Ls, const void *desc, const void *items, const void *order,
-                              size_t nsmall, int conc)
+                              size_t nsmall)
 {
     std::ostringstream os;
-    os << desc << ',' << items << ',' << order << ',' << nsmall << ':' << conc;
+    os << desc << ',' << items << ',' << order << ',' << nsmall;
     for (const BLaunch &L : Ls)
         os << ';' << L.onchip << ',' << L.cls << ',' << L.mode << ',' << L.high << ',' << L.stream_hint << ','
            << L.grid << ',' << static_cast<const void *>(L.tiles) << ',' << L.step;
@@ -846,8 +862,9 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
     tiles.reserve(P.n_tiles);
     int2 *dT = reinterpret_cast<int2 *>(ws + P.off_tiles);
     std::vector<BLaunch> Ls;
-    if (!run.small.empty())
-        Ls.push_back({1, 0, 0, 0, 0, (unsigned)std::min<int>((int)run.small.size(), 512), nullptr, 0});
+    const bool conc = sch.concurrent && !run.small.empty() && !Lg.empty();
+    const unsigned small_grid = (unsigned)std::min<int>((int)run.small.size(), 512);
+    if (!run.small.empty() && !conc) Ls.push_back({1, 0, 0, 0, 0, small_grid, nullptr, 0});
     for (auto &w : waves) {
         double wave_vec_bytes = 0.0;   // b1, b2, psi, out (8 B each) and the diagonal per amplitude
         for (int i : w) wave_vec_bytes += std::ldexp(36.0, items[i].n);
@@ -904,14 +921,18 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
         QW_HIP(hipMemcpyAsync(dT, tiles.data(), tiles.size() * sizeof(int2), hipMemcpyHostToDevice, s));
     QW_HIP(hipStreamSynchronize(s));   // host staging buffers go out of scope below
 
-    hipStream_t side = nullptr;
-    const bool conc = sch.concurrent && !run.small.empty() && !Lg.empty();
+    Beside beside{s, nullptr, nullptr, nullptr};
     if (conc) {
-        st = side_stream(&side);
+        st = side_stream(&beside.side);
         if (st != QW_OK) return st;
         QW_HIP(hipEventCreateWithFlags(&ev[3], hipEventDisableTiming));
         QW_HIP(hipEventCreateWithFlags(&ev[4], hipEventDisableTiming));
+        beside.fork = ev[3];
+        beside.join = ev[4];
     }
+    auto start_beside = [&]() -> qw_status {
+        return conc ? beside.start(small_grid, ditems, dorder, (int)run.small.size()) : QW_OK;
+    };
     if (s == nullptr) use_graph = false;   // the null stream cannot be captured
     int graph_cached = 0;
     float graph_ms = 0.f;
@@ -919,7 +940,7 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
     if (use_graph && !Ls.empty()) {
         int dev = 0;
         QW_HIP(hipGetDevice(&dev));
-        const std::string key = launch_key(Ls, dD, ditems, dorder, run.small.size(), conc ? 1 : 0);
+        const std::string key = launch_key(Ls, dD, ditems, dorder, run.small.size());
         std::lock_guard<std::mutex> lock(g_graph_mu);
         for (const GraphEntry &e : g_graphs)
             if (e.dev == dev && e.key == key) exec = e.exec;
@@ -929,7 +950,7 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
             const auto h0 = std::chrono::steady_clock::now();
             hipGraph_t graph = nullptr;
             QW_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            const qw_status rs = replay(Ls, dD, ditems, dorder, (int)run.small.size(), s, side, ev[3], ev[4]);
+            const qw_status rs = replay(Ls, dD, ditems, dorder, (int)run.small.size(), s);
             hipError_t e1 = hipStreamEndCapture(s, &graph);
             if (rs != QW_OK) {
                 if (graph) (void)hipGraphDestroy(graph);
@@ -955,13 +976,16 @@ static qw_status batched_impl(const qw_batch_item *items, int count, const doubl
             graph_ms = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - h0).count();
         }
         if (timing) QW_HIP(hipEventRecord(ev[1], s));
+        if ((st = start_beside()) != QW_OK) return st;
         QW_HIP(hipGraphLaunch(exec, s));
     } else {
         if (timing) QW_HIP(hipEventRecord(ev[1], s));
-        st = replay(Ls, dD, ditems, dorder, (int)run.small.size(), s, side, ev[3], ev[4]);
+        if ((st = start_beside()) != QW_OK) return st;
+        st = replay(Ls, dD, ditems, dorder, (int)run.small.size(), s);
         if (st != QW_OK) return st;
     }
-    run.launches = (int)Ls.size();
+    if ((st = beside.finish()) != QW_OK) return st;
+    run.launches = (int)Ls.size() + (conc ? 1 : 0);
     if (timing) QW_HIP(hipEventRecord(ev[2], s));
     QW_HIP(hipStreamSynchronize(s));
     if (info) {
