@@ -314,7 +314,8 @@ typedef struct {
     signed char tile_class[23]; /* per n (index n), multi-pass instances: 0 = 2^13-
                                    amplitude tiles, 1024 threads; 1 = 2^12, 1024
                                    threads (13 <= n <= 20); 2 = 2^13, 512 threads;
-                                   -1 = default (1 up to n = 20, else 0)           */
+                                   -1 = default (1 up to n = 20, else 0; 0 at 19
+                                   and 20 if the batch has 2^24 amplitudes there)  */
 } qw_batch_sched;
 
 typedef struct {

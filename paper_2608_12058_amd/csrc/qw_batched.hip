@@ -384,6 +384,7 @@ struct BatchSched {
     int onchip_nmax = Cfg<float>::TB;
     int concurrent = 0;
     signed char cls[BATCH_MAXN + 1];
+    bool full = false;   // the batch fills the device with 19 and 20 qubits alone (class_for)
     BatchSched() { std::memset(cls, -1, sizeof(cls)); }
 };
 
@@ -392,12 +393,24 @@ struct BatchSched {
 // below 128 B (21) or a third orientation (22).  The smaller tiles give twice the
 // workgroups, which counts at the steps that only a few instances still take: 48
 // instances of 12 to 20 qubits 42.8 ms against 45.0 with MID, 9 of 14 to 19 7.8
-// against 9.1, 34 of 11 to 17 5.8 against 6.9.
+// against 9.1, 34 of 11 to 17 5.8 against 6.9.  From 2^24 amplitudes of 19 and 20
+// qubits every step fills the device and outgrows the memory-side cache, where those
+// two sizes are faster in the longer rows of MID (64 instances of 19 qubits 15.2
+// against 14.7 ms, 16 of 20 7.75 against 7.53; 16 of 19 3.30 against 3.43, 64 of 18
+// 6.24 against 6.56).
 static int class_for(const BatchSched &S, int n)
 {
     const int c = S.cls[n];
     if (c >= 0) return c;
-    return (n <= 20) ? (int)BC_NARROW : (int)BC_MID;
+    return (n <= 18 || (n <= 20 && !S.full)) ? (int)BC_NARROW : (int)BC_MID;
+}
+
+static bool fills_device(const qw_batch_item *items, int count)
+{
+    long long amps = 0;
+    for (int i = 0; i < count; ++i)
+        if (items[i].n == 19 || items[i].n == 20) amps += 1ll << items[i].n;
+    return amps >= 1ll << 24;
 }
 
 static qw_status validate_sched(const BatchSched &S)
@@ -681,13 +694,14 @@ struct BatchRun {
 };
 
 static qw_status batched_impl(const qw_batch_item *items, int count, const double *hJ, const void *psi_pool,
-                              void *out_pool, int method, void *workspace, size_t ws_bytes, const BatchSched &sch,
+                              void *out_pool, int method, void *workspace, size_t ws_bytes, BatchSched sch,
                               bool use_graph, hipStream_t s, qw_batch_info *info)
 {
     qw_status st = validate_batch(items, count, hJ);
     if (st != QW_OK) return st;
     st = validate_sched(sch);
     if (st != QW_OK) return st;
+    sch.full = fills_device(items, count);
     if (method != QW_CHEB && method != QW_CF) { set_error("unknown method"); return QW_EINVAL; }
     if (!psi_pool || !out_pool || !workspace) { set_error("pools and workspace are required"); return QW_EINVAL; }
     if ((reinterpret_cast<uintptr_t>(workspace) & 255) || (reinterpret_cast<uintptr_t>(psi_pool) & 15) ||
@@ -1098,6 +1112,7 @@ qw_status qw_batched_tune_c64(const qw_batch_item *items, int count, const doubl
     int present[BATCH_MAXN + 1] = {0};
     for (int i = 0; i < count; ++i) present[items[i].n] = 1;
     BatchSched best;
+    best.full = fills_device(items, count);
     float best_ms = 0.f;
     qw_status st = time_of(best, &best_ms);
     if (st != QW_OK) return st;
