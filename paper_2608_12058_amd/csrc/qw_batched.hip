@@ -1071,7 +1071,8 @@ qw_status qw_expm_action_batched_c64(const qw_batch_item *items, int count, cons
                                      size_t ws_bytes, const char *tune_cache, void *stream, qw_batch_info *info)
 {
     clear_info(info);
-    if (!items || count < 1) { set_error("items and count >= 1 are required"); return QW_EINVAL; }
+    const qw_status st = validate_batch(items, count, hJ_pool);   // before the sizes are counted
+    if (st != QW_OK) return st;
     BatchSched S;
     (void)read_tuned_sched(tune_cache, batch_signature(items, count), &S);
     return batched_impl(items, count, hJ_pool, psi_pool, out_pool, (int)method, workspace, ws_bytes, S, true,
@@ -1096,7 +1097,8 @@ qw_status qw_batched_tune_c64(const qw_batch_item *items, int count, const doubl
                               void *out_pool, void *workspace, size_t ws_bytes, const char *tune_cache,
                               void *stream, qw_batch_sched *best_out)
 {
-    if (!items || count < 1) { set_error("items and count >= 1 are required"); return QW_EINVAL; }
+    qw_status st = validate_batch(items, count, hJ_pool);   // before the sizes are counted
+    if (st != QW_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     auto time_of = [&](const BatchSched &S, float *ms) -> qw_status {
         qw_batch_info bi{};
@@ -1114,7 +1116,7 @@ qw_status qw_batched_tune_c64(const qw_batch_item *items, int count, const doubl
     BatchSched best;
     best.full = fills_device(items, count);
     float best_ms = 0.f;
-    qw_status st = time_of(best, &best_ms);
+    st = time_of(best, &best_ms);
     if (st != QW_OK) return st;
     auto consider = [&](const BatchSched &S) -> qw_status {
         if (validate_sched(S) != QW_OK) return QW_OK;   // not a valid candidate for these sizes
