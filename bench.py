@@ -408,7 +408,8 @@ def main():
     t1 = time.perf_counter()
     ms_step = (t1 - t0) * 1e3 / args.steps
     K = infos[0]["K"]
-    P = infos[0]["passes"]
+    plan = qw.call_plan(n, 64, K)
+    P = len(plan)
     loop_ms = float(np.median([i["loop_ms"] for i in infos]))
     setup_ms = float(np.median([i["setup_ms"] for i in infos]))
     value = N * K / (ms_step * 1e-3)
@@ -416,32 +417,21 @@ def main():
     # per-pass live durations (one extra untimed call with an event after every pass)
     pinfo = step(timing=2)
     pass_ms = pinfo["pass_ms"][:P]
-    # without the norm monitor 28 qubits run two orientations: rows of 128 B that
-    # rebuild the diagonal (40 B/amp), contiguous tiles that read it (44 B/amp)
-    two = P == 3 and pass_ms[2] == 0
-    ran = 2 if two else P
     terms = K  # K-1 recurrence terms + the final step, each P passes
     term_ms = loop_ms / terms
-    # the passes that would read a stored diagonal (START / FUSED, on the end
-    # orientations) all rebuild it: the algorithmic figure is then 32 B
-    ends = {0, P - 1}
-    otf_all = all((pinfo["otf_mask"] >> p) & 1 for p in ends)
-    alg_per_amp = BYTES_PER_AMP_TERM_OTF if otf_all else BYTES_PER_AMP_TERM[64]
+    # where a fused pass rebuilds the diagonal no stored one is needed: 32 B
+    alg_per_amp = BYTES_PER_AMP_TERM_OTF if any(o["rebuilds"] for o in plan) else BYTES_PER_AMP_TERM[64]
     alg_bytes_term = alg_per_amp * N
     achieved = (BYTES_INIT[64] * N + alg_bytes_term * terms) / (loop_ms * 1e-3) / 1e9
     achieved_36 = 36 * N * terms / (loop_ms * 1e-3) / 1e9
     # bytes each orientation moves per term under the fused schedule: the two
     # end orientations alternate a fused pass every other term (44 B/amp, 40
-    # where the pass rebuilds the diagonal: bit o of otf_mask), the middle ones
-    # add (24 B/amp) every term
-    mask = pinfo.get("otf_mask", 0)
-    fused = [(40 if (mask >> p) & 1 else 44) * N for p in range(P)]
-    per_term = ([fused[p] / 2 if p in (0, P - 1) else 24 * N for p in range(P)] if P > 1 else [36 * N])
-    if two:
-        mask, per_term = 1, [20 * N, 22 * N]
-    passes = [{"orientation": p, "rebuilds_diagonal": bool((mask >> p) & 1),
+    # where the pass rebuilds the diagonal), the middle ones add (24 B/amp) every term
+    fused = [(40 if o["rebuilds"] else 44) * N for o in plan]
+    per_term = ([fused[p] / 2 if p in (0, P - 1) else 24 * N for p in range(P)] if P > 1 else [36 * N] * P)
+    passes = [{"orientation": p, "rebuilds_diagonal": plan[p]["rebuilds"],
                "avg_us_per_term": pass_ms[p] / terms * 1e3, "moved_bytes_per_term": per_term[p],
-               "moved_GBps": per_term[p] / (pass_ms[p] / terms * 1e-3) / 1e9} for p in range(ran)]
+               "moved_GBps": per_term[p] / (pass_ms[p] / terms * 1e-3) / 1e9} for p in range(P)]
 
     traffic = None
     if os.path.exists(args.traffic_json):
@@ -459,7 +449,7 @@ def main():
         "vs_baseline": None, "dtype": "fp32", "data": "synthetic",
         "config": {"workload": f"SK spin glass n={n} (seed 0, J~N(0,1/n), h~N(0,1)), gamma=1, t=5, "
                                f"tol=2^-23, psi0=|+>, complex64 state, fp32 diagonal rebuilt per tile from (h, J) in the strided passes",
-                   "n": n, "K": K, "passes_per_term": ran, "radius_r": infos[0]["radius_r"],
+                   "n": n, "K": K, "passes_per_term": P, "radius_r": infos[0]["radius_r"],
                    "a": infos[0]["a"]},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                      "frac": achieved / PEAK_HBM_GBPS, "traffic": traffic,
@@ -488,8 +478,8 @@ def main():
         i128 = qw.expm_action(psi128, gamma, t, h=h, J=J, tol=1e-12, out=out128, workspace=ws128, timing=1)[1]
         tb = time.perf_counter()
         # 64 B/amp per term when both end orientations rebuild the diagonal
-        P128 = i128["passes"]
-        alg128 = 64 if all((i128["otf_mask"] >> p) & 1 for p in {0, P128 - 1}) else BYTES_PER_AMP_TERM[128]
+        plan128 = qw.call_plan(n, 128, i128["K"])
+        alg128 = 64 if plan128 and plan128[0]["rebuilds"] and plan128[-1]["rebuilds"] else BYTES_PER_AMP_TERM[128]
         result["c128_plain"] = {"tol": 1e-12, "K": i128["K"], "ms_per_call": (tb - ta) * 1e3,
                                 "loop_ms": i128["loop_ms"], "ms_per_term": i128["loop_ms"] / i128["K"],
                                 "value": N * i128["K"] / (tb - ta), "alg_bytes_per_amp_term": alg128,

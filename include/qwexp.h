@@ -72,7 +72,7 @@ typedef struct {
     int passes;         /* global passes per Clenshaw term with the norm monitor
                            (without it, complex64 25-28 and complex128 22-27
                            qubits take two where this says three, and sizes of
-                           one launch none)                                       */
+                           one launch none: qw_call_plan)                         */
     int method;         /* qw_method actually used                                */
     double shift_c;     /* spectral shift c = (max E + min E)/2                   */
     double radius_r;    /* bound r on the spectral radius of H - cI               */
@@ -93,7 +93,8 @@ typedef struct {
     double out_norm;    /* out (monitor): ||psi_out||                             */
     int otf_mask;       /* out: bit o set if the passes of orientation o rebuild
                            the diagonal from (h, J) instead of reading it (of
-                           the orientations that `passes` counts)                 */
+                           the orientations that `passes` counts; those that
+                           ran: qw_call_plan)                                     */
 } qw_info;
 
 /* ------------------------------------------------------------------------
@@ -442,6 +443,16 @@ const char *qw_last_error(void);
  * Returns the number of passes per term, or a negative code on a violation.
  * Launches nothing. */
 int qw_debug_check_plan(int n, int precision);
+
+/* Host-only: what an action or polynomial call of n qubits and degree K >= 1 runs on
+ * a whole device, outside graph capture (precision 64 or 128; from_tables: the
+ * diagonal comes from (h, J); monitor: with the norm monitor, as the `bounded` calls
+ * have it).  Returns the number of its orientations, that is of its passes per
+ * Clenshaw term, or 0 for one launch, or -1 for bad arguments, and writes for each
+ * (pass_ms counts them in this order): first flipped bit, flipped bits of a tile,
+ * bits above them that are taken from other tiles, and whether its fused passes
+ * rebuild the diagonal (4*cap ints; nothing is written when there are more). */
+int qw_call_plan(int n, int precision, int from_tables, int monitor, int K, int *out, int cap);
 
 /* Host-only: the sequence of Clenshaw passes for degree K >= 1 over P
  * orientations, as quadruples (mode 0 START / 1 ADD / 2 FUSED, orientation,

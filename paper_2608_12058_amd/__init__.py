@@ -78,6 +78,8 @@ def _declare(lib):
         f.argtypes = [_i, _dp, _dp, _dp, _i, _dp, _i, _d, _i, _d, _vp, _vp, _dp, _i, _vp, _sz, _vp,
                       ctypes.POINTER(CfetInfo)]
     lib.qw_cfet4_step_bound.argtypes = [_i, _dp, _dp, _dp, _i, _dp, _i, _d, _d, _d, _d, _dp]
+    lib.qw_call_plan.argtypes = [_i, _i, _i, _i, _i, ctypes.POINTER(_i), _i]
+    lib.qw_call_plan.restype = _i
     lib.qw_debug_check_plan.argtypes = [_i, _i]
     lib.qw_debug_check_plan.restype = _i
     return lib
@@ -395,6 +397,18 @@ def cfet4_step_bound(n: int, h, J, A, B, T: float, emin: float, emax: float, t: 
                                      int(b.size - 1), float(T), float(emin), float(emax), float(t),
                                      ctypes.byref(out)))
     return float(out.value)
+
+
+def call_plan(n: int, precision: int, K: int, *, from_tables: bool = True, monitor: bool = False) -> list:
+    """The orientations of an action or polynomial call of degree K >= 1, in the order
+    of info["pass_ms"] (empty: one launch): dicts with the first flipped bit g0, the
+    flipped bits h of a tile, the bits `cross` above them taken from other tiles, and
+    `rebuilds`, whether the fused passes rebuild the diagonal.  Host only."""
+    out = (_i * 16)()
+    P = int(lib().qw_call_plan(int(n), int(precision), int(from_tables), int(monitor), int(K), out, 4))
+    if P < 0:
+        raise QwError(QW_EINVAL, lib().qw_last_error().decode())
+    return [dict(g0=out[4 * o], h=out[4 * o + 1], cross=out[4 * o + 2], rebuilds=bool(out[4 * o + 3])) for o in range(P)]
 
 
 def debug_check_plan(n: int, precision: int) -> int:

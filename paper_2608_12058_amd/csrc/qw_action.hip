@@ -586,6 +586,16 @@ struct PolyIn {
     int horner;
 };
 
+// The orientations of a call's passes (where it runs in passes).
+template <typename R> static std::vector<OrientSpec> run_plan(int n, bool tables, bool monitor, int cus, int K)
+{
+    // (on a stream with masked compute units a cluster's tiles could wait for
+    // partners that have no place beside them)
+    std::vector<OrientSpec> S;
+    if (!monitor && cus > 0) S = pair_plan<R>(n, tables, K);
+    return S.empty() ? action_plan<R>(n, tables) : S;
+}
+
 template <typename R>
 static qw_status action_impl(int n, const R *diag, const double *h, const double *J, double gamma, double t,
                              const void *psi_in, void *psi_out, double tol, int method, void *workspace,
@@ -717,12 +727,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
     }
     // orientations and launch shapes; the end orientations rebuild the diagonal
     // where the plan says so, and the stored one is formed only if a pass reads it
-    const std::vector<OrientSpec> general = action_plan<R>(n, diag == nullptr);
-    std::vector<OrientSpec> pair;
-    // (on a stream with masked compute units a cluster's tiles could wait for
-    // partners that have no place beside them)
-    if (!monitor && cus > 0) pair = pair_plan<R>(n, diag == nullptr, K);
-    const std::vector<OrientSpec> &plan = pair.empty() ? general : pair;
+    const std::vector<OrientSpec> plan = run_plan<R>(n, diag == nullptr, monitor, cus, K);
     bool any_otf = false;
     for (const OrientSpec &o : plan) any_otf = any_otf || o.otf;
     if (any_otf && !(L.ft != size_t(-1))) { set_error("internal: no per-tile field table for this size"); return QW_EINVAL; }
@@ -733,6 +738,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         info->K = K;
         info->a = a;
         info->trunc_bound = err;
+        const std::vector<OrientSpec> general = action_plan<R>(n, diag == nullptr);
         info->passes = (int)general.size();
         for (size_t o = 0; o < general.size(); ++o)
             if (general[o].otf) info->otf_mask |= 1 << o;
@@ -1438,6 +1444,31 @@ int qw_debug_refuse_groups(int how)
     const int old = t_refuse;
     t_refuse = how;
     return old;
+}
+
+}  // extern "C"
+
+template <typename R> static int call_plan(int n, bool tables, bool monitor, int K, int *out, int cap)
+{
+    if (!monitor && n <= resident_nmax<R>() && (tables || K >= resident_kmin<R>(n))) return 0;
+    const std::vector<OrientSpec> S = run_plan<R>(n, tables, monitor, 256, K);
+    if ((int)S.size() <= cap && out)
+        for (size_t o = 0; o < S.size(); ++o) {
+            out[4 * o] = S[o].pl.g0;
+            out[4 * o + 1] = S[o].pl.h;
+            out[4 * o + 2] = S[o].xh;
+            out[4 * o + 3] = S[o].otf ? 1 : 0;
+        }
+    return (int)S.size();
+}
+
+extern "C" {
+
+int qw_call_plan(int n, int precision, int from_tables, int monitor, int K, int *out, int cap)
+{
+    if (n < 1 || n > 32 || K < 1 || (precision != 64 && precision != 128)) { set_error("bad arguments"); return -1; }
+    return precision == 64 ? call_plan<float>(n, from_tables != 0, monitor != 0, K, out, cap)
+                           : call_plan<double>(n, from_tables != 0, monitor != 0, K, out, cap);
 }
 
 // Host-only self check of the pass index maps; returns the number of passes or
