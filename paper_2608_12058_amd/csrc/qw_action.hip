@@ -381,7 +381,7 @@ static void launch_shape(const PassArgs<R> &a, int mode, bool otf, uint64_t ntil
             return;
         }
     }
-    if constexpr (WITH_OTF) {
+    if constexpr (WITH_OTF && STREAM) {   // sizes that rebuild the diagonal are streamed
         if (otf && mode == PM_START) { hipLaunchKernelGGL((k_pass<R, TB, NT, PM_START, true, STREAM>), grid, block, 0, s, a); return; }
         if (otf && mode == PM_FUSED) { hipLaunchKernelGGL((k_pass<R, TB, NT, PM_FUSED, true, STREAM>), grid, block, 0, s, a); return; }
     }
@@ -844,7 +844,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         const bool shape_ok = (sizeof(R) == 4 && pc.tb == TB_WIDE && pc.nt == NT_WIDE) ||
                               (sizeof(R) == 8 && pc.tb == TB_WIDE_D && pc.nt == NT_WIDE) ||
                               (pc.tb == Cfg<R>::TB && pc.nt == Cfg<R>::NT);
-        if (pl.L + pl.h != pc.tb || !shape_ok || pc.tb - log_nt > QS_MAX_R) {
+        if (pl.L + pl.h != pc.tb || !shape_ok || !pc.stream || pc.tb - log_nt > QS_MAX_R) {
             set_error("internal: on-the-fly tile shape");
             return QW_EINVAL;
         }
