@@ -1,5 +1,6 @@
-"""The words by which tiles of a cluster meet: a partner that ran this round on another
-XCD is never waited for (host code of qw_kernels.h, CPU only)."""
+"""The words by which tiles of a cluster meet (a partner that ran this round on another
+XCD is never waited for), and the maps of the two-orientation plans of 22 to 28 qubits
+(host code of qw_kernels.h, CPU only)."""
 import os
 import shutil
 import subprocess
@@ -10,7 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2608_12058_amd", "csrc")
 
 
-def test_words_of_a_cluster(tmp_path):
+def test_words_and_maps(tmp_path):
     hipcc = next((c for c in ("/opt/rocm/bin/hipcc", shutil.which("hipcc")) if c and os.path.exists(c)), None)
     if hipcc is None:
         pytest.skip("hipcc not available")
