@@ -28,10 +28,11 @@
  *     recurrence is enqueued; that runs asynchronously.  Host arrays may be
  *     freed when a call returns.
  *   - The recurrence of n <= 20 qubits (complex128: 19) without norm monitor is
- *     one launch whose workgroups exchange data; workgroups that cannot all
- *     start together (the device shared with many waiting kernels) make one of
- *     them run it alone, slowly, with results that differ by rounding.  The two
- *     largest sizes in each precision are launched cooperatively, and in passes
+ *     one launch whose workgroups exchange data; where they cannot all start
+ *     together (the device shared with other kernels that hold compute units), those
+ *     that have started run it together after 0.4 ms, several times slower and with
+ *     results that differ by rounding.  The two largest sizes in each precision are
+ *     launched cooperatively, wait 0.1 s for their start, and run in passes
  *     where a stream is being captured.  Where the workgroups have no room side by
  *     side (a partitioned device, a stream with masked compute units, a refused
  *     cooperative launch) every such size runs in passes.  A workgroup that waits
@@ -461,9 +462,9 @@ int qw_call_plan(int n, int precision, int from_tables, int monitor, int K, int 
 int qw_debug_schedule(int K, int P, int *out, int cap);
 
 /* For tests: how often the workgroups of a one-launch recurrence look at their
- * common start before one of them runs the recurrence alone (calls of this host
- * thread from now on; negative: the default, some 0.1 s).  The results differ
- * only by rounding.  Returns the value before. */
+ * common start before those that have started run it together (calls of this host
+ * thread from now on; negative: the default, 0.4 ms or 0.1 s), and tiles at their
+ * partners' flags.  The results differ only by rounding.  Returns the value before. */
 int qw_debug_start_patience(int looks);
 
 /* For tests: how often a wave of a one-launch recurrence or sweep looks at a

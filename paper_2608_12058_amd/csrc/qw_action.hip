@@ -35,7 +35,7 @@
 
 namespace qw {
 
-static thread_local int t_patience = RES_PATIENCE;   // qw_debug_start_patience
+static thread_local int t_patience = -1;             // qw_debug_start_patience; -1: the defaults
 static thread_local int t_polls = RES_POLLS;         // qw_debug_wait_limit
 static thread_local int t_refuse = 0;                // qw_debug_refuse_groups
 static thread_local std::string g_err;
@@ -151,7 +151,7 @@ static WsLayout ws_layout(int n, int prec, bool otf)
 
 
 // Copies count words to dst and count2 words to dst2, and clears the first word
-// of nlines lines and of the two lines at `two`.
+// of nlines lines and the words in use of the two lines at `two`.
 template <int D = 0>
 __global__ void __launch_bounds__(256) k_put(PutBlob b, int count, uint64_t *dst, int count2, uint64_t *dst2,
                                              int *lines, int nlines, int *two)
@@ -161,7 +161,8 @@ __global__ void __launch_bounds__(256) k_put(PutBlob b, int count, uint64_t *dst
         else dst2[i - count] = b.v[i];
     }
     for (int i = threadIdx.x; i < nlines; i += 256) lines[i * RES_LINE] = 0;
-    if (nlines > 0 && threadIdx.x < 2) two[threadIdx.x * RES_LINE] = 0;
+    if (nlines > 0 && threadIdx.x <= RES_MET) two[threadIdx.x] = 0;
+    if (nlines > 0 && threadIdx.x == 0) two[RES_LINE] = 0;
 }
 
 // The same from host arrays, in as many launches as it takes.
@@ -878,7 +879,7 @@ static qw_status action_impl(int n, const R *diag, const double *h, const double
         pa.flag = reinterpret_cast<int *>(norms);
         pa.flag_step = (int)std::min<uint64_t>(RES_LINE, half / sizeof(int) / nt);
         pa.late = reinterpret_cast<int *>(reinterpret_cast<char *>(norms) + half);
-        pa.patience = std::min(t_patience, CROSS_PATIENCE);
+        pa.patience = t_patience < 0 ? CROSS_PATIENCE : std::min(t_patience, CROSS_PATIENCE);
         if (pa.flag_step < 1 || (nt + 1) * sizeof(int) > half) { set_error("internal: room for the flags"); return QW_EINVAL; }
         hipLaunchKernelGGL(k_fill_zero<0>, dim3(64), dim3(256), 0, s, norms, (uint64_t)KMAX_MON);
     }
@@ -1428,7 +1429,7 @@ int qw_debug_schedule(int K, int P, int *out, int cap)
 int qw_debug_start_patience(int looks)
 {
     const int old = t_patience;
-    t_patience = looks < 0 ? RES_PATIENCE : looks;
+    t_patience = looks < 0 ? -1 : looks;
     return old;
 }
 

@@ -508,7 +508,8 @@ template <int T, int NT, int HC, bool BACK> __global__ void __launch_bounds__(NT
             const int xcc = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, 4 bits
             (void)__hip_atomic_fetch_or(a.start + RES_LINE, 1 << xcc, __ATOMIC_RELAXED, QW_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            const bool ok = res_join(a.start, W, RES_POLLS);
+            int id;
+            const bool ok = res_join(a.start, W, RES_POLLS, &id) == 1;
             const int m = __hip_atomic_load(a.start + RES_LINE, __ATOMIC_RELAXED, QW_AGENT);
             go = !ok ? 0 : (m & (m - 1)) == 0 ? 2 : 1;
         }

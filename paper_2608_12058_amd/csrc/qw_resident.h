@@ -20,7 +20,10 @@ static constexpr int RES_XCDS = 8;
 // mask of XCDs on two more lines.
 static constexpr int RES_LINE = 32;            // 4-byte words per line
 static constexpr int RES_MAXFLAGS = 4096;
-static constexpr int RES_PATIENCE = 1 << 17;   // looks at the start word, some 0.1 s
+// Looks at the start word, 0.4 ms and 0.1 s.  Only a cooperative launch, of which a
+// process runs one at a time, waits long: it needs every CU, so a plain one that
+// holds some and waits for more has to go on without them (k_resident's start).
+static constexpr int RES_PATIENCE = 1 << 9, RES_PATIENCE_COOP = 1 << 17;
 static constexpr int RES_POLLS = 1 << 24;      // looks at a flag, seconds
 int wait_polls();                              // the same, or what a test has set (qw_action.hip)
 
@@ -53,11 +56,11 @@ template <typename R> struct ResArgs {
     const C *coef;        // device: coefficients of all steps
     C *X0, *X1;           // exchange buffers of 2^n
     R *d;                 // 2^n, used only when the workgroups cannot all start
-    int *start, *flags;   // 2 and RES_MAXFLAGS lines, cleared before the launch
+    int *start, *flags;   // 2 and RES_MAXFLAGS lines, their words in use cleared before the launch
     R two, sub;           // Clenshaw 2 and 1, Horner's rule 1 and 0
     int n;
     int stride, sel;      // workgroups with blockIdx.x % stride == sel take part
-    int patience;         // looks at the start word before giving up on a common start
+    int patience;         // looks at the start word before giving up on a common start (< 0: the default)
     int polls;            // looks at a flag before giving up on a partner
 };
 
@@ -145,39 +148,71 @@ template <int T> struct TileEnergy {
 };
 
 #define QW_AGENT __HIP_MEMORY_SCOPE_AGENT
-enum : int { RES_CNT = 0xfff, RES_EXIT = 1 << 12, RES_TRY = 1 << 28, RES_ABORT = 1 << 29, RES_GO = 1 << 30 };
+enum : int { RES_CNT = 0xfff, RES_TRY = 1 << 28, RES_ABORT = 1 << 29, RES_GO = 1 << 30 };
+// words of the first line: joined and decided, size of a team, its barrier's count
+enum : int { RES_STATE, RES_TEAM, RES_MET };
 
-// Common start of W workgroups (one thread of each): true once all of them run.
+// Common start of W workgroups (one thread of each): 1 once all of them run.
 // From then on every wait between them ends, since none has to be placed any
 // more.  After `patience` looks the first one to lose patience decides for all,
-// by what the count was when it did.
-__device__ inline bool res_join(int *state, int W, int patience)
+// by how many had joined when it did: if some had not, those that had are a team
+// (0; *id: number of this one), and who comes later leaves (-1).
+__device__ inline int res_join(int *state, int W, int patience, int *id)
 {
-    int s = __hip_atomic_fetch_add(state, 1, __ATOMIC_RELAXED, QW_AGENT) + 1;
-    for (;;) {
-        if (s & RES_ABORT) return false;
-        if (s & RES_GO) return true;
-        if (!(s & RES_TRY)) {
-            if ((s & RES_CNT) == W) return true;
-            if (patience-- <= 0) {
-                const int old = __hip_atomic_fetch_or(state, (int)RES_TRY, __ATOMIC_RELAXED, QW_AGENT);
-                if (!(old & RES_TRY)) {
-                    const bool full = (old & RES_CNT) == W;
-                    (void)__hip_atomic_fetch_or(state, (int)(full ? RES_GO : RES_ABORT), __ATOMIC_RELAXED, QW_AGENT);
-                    return full;
-                }
+    const int before = __hip_atomic_fetch_add(state, 1, __ATOMIC_RELAXED, QW_AGENT);
+    *id = before & RES_CNT;
+    if (before & RES_TRY) return -1;   // without this one the count cannot have been W
+    for (int s = before + 1;; s = __hip_atomic_load(state, __ATOMIC_RELAXED, QW_AGENT)) {
+        if (s & RES_ABORT) return 0;
+        if (s & RES_GO) return 1;
+        if (s & RES_TRY) continue;
+        if ((s & RES_CNT) == W) return 1;
+        if (patience-- <= 0) {
+            const int old = __hip_atomic_fetch_or(state, (int)RES_TRY, __ATOMIC_RELAXED, QW_AGENT);
+            if (old & RES_TRY) continue;
+            const int m = old & RES_CNT;
+            if (m != W) {
+                __hip_atomic_store(state + RES_TEAM, m, __ATOMIC_RELAXED, QW_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
+            (void)__hip_atomic_fetch_or(state, (int)(m == W ? RES_GO : RES_ABORT), __ATOMIC_RELAXED, QW_AGENT);
+            return m == W;
         }
-        s = __hip_atomic_load(state, __ATOMIC_RELAXED, QW_AGENT);
     }
 }
 
-// The recurrence by one workgroup alone, from global memory: what the last
-// workgroup to leave does when the common start failed.
-template <typename R, int NT> __device__ __forceinline__ void res_alone(const ResArgs<R> &a, const double *hJ)
+// The recurrence by the workgroups that had started when the common start failed,
+// from global memory with a barrier per term.  All of them run, so the barrier's
+// waits end.  Bounded by the barrier's round trips (17 us) and, at the largest
+// sizes, by the reads of n flips: 17 qubits 21 us per term by 254 workgroups, 25 by
+// 24; 20 qubits 37 by 248, 75 by 49.  One workgroup alone, which ran it before after
+// 0.1 s, took a second for a call of 20 qubits: eight streams of mixed sizes needed
+// 5.7 s for what takes 0.14 one after another and 0.12 now.
+template <typename R, int NT>
+__device__ __forceinline__ void res_team(const ResArgs<R> &a, const double *hJ, int id, int m)
 {
     using C = typename Cplx<R>::T;
-    const uint32_t N = 1u << a.n;
+    using V = CVec<R>;
+    constexpr int VE = V::N, B0 = VE - 1;   // lowest bit whose flip is another vector
+    const uint32_t nvec = (1u << a.n) / VE, first = id * NT + threadIdx.x, step = m * NT;
+    __shared__ int gone;
+    int met = 0;
+    bool lost = false;
+    auto meet = [&]() {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the wave's stores have reached the L2
+        __syncthreads();
+        met += m;
+        if (threadIdx.x == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            (void)__hip_atomic_fetch_add(a.start + RES_MET, 1, __ATOMIC_RELAXED, QW_AGENT);
+            int left = lost ? 0 : a.polls;
+            while (left > 0 && __hip_atomic_load(a.start + RES_MET, __ATOMIC_RELAXED, QW_AGENT) < met) --left;
+            gone = left <= 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the L1 is the workgroup's
+        }
+        __syncthreads();
+        lost = gone != 0;
+    };
 #pragma unroll 1
     for (int i = 0; i < a.nsteps; ++i) {
         const ResStep<R> st = i == 0 ? a.first : a.more[i - 1];
@@ -185,40 +220,68 @@ template <typename R, int NT> __device__ __forceinline__ void res_alone(const Re
         C *b1 = a.X0, *b2 = a.X1;
         const C cK = coef[st.K];
 #pragma unroll 1
-        for (uint32_t z = threadIdx.x; z < N; z += NT) {
-            const double E = a.diag ? (double)a.diag[z] : energy_direct(hJ, a.n, z);
-            a.d[z] = (R)((E - st.c) * st.inv_r);
-            const C p = psi[z];
-            b1[z] = C{fmad(cK.x, p.x, -(cK.y * p.y)), fmad(cK.x, p.y, cK.y * p.x)};
-            b2[z] = C{R(0), R(0)};
-            if (st.K == 0) a.out[z] = C{fmad(st.pr, b1[z].x, -(st.pi * b1[z].y)), fmad(st.pr, b1[z].y, st.pi * b1[z].x)};
+        for (uint32_t q = first; q < nvec; q += step) {
+            const uint32_t z = q * VE;
+            const V p = ld_v<R, false>(psi + z);
+            V x, y;
+#pragma unroll
+            for (int v = 0; v < VE; ++v) {
+                const double E = a.diag ? (double)a.diag[z + v] : energy_direct(hJ, a.n, z + v);
+                a.d[z + v] = (R)((E - st.c) * st.inv_r);
+                x.v[v] = C{fmad(cK.x, p.v[v].x, -(cK.y * p.v[v].y)), fmad(cK.x, p.v[v].y, cK.y * p.v[v].x)};
+                y.v[v] = C{fmad(st.pr, x.v[v].x, -(st.pi * x.v[v].y)), fmad(st.pr, x.v[v].y, st.pi * x.v[v].x)};
+            }
+            st_v<R, false>(b1 + z, x);
+            if (st.K == 0) st_v<R, false>(a.out + z, y);
         }
-        __syncthreads();
 #pragma unroll 1
         for (int k = st.K - 1; k >= 0; --k) {
+            meet();
             const C ck = coef[k];
-            const R scale = (k == 0) ? R(1) : a.two;
+            const R scale = (k == 0) ? R(1) : a.two, g = lost ? R(NAN) : st.g;
 #pragma unroll 1
-            for (uint32_t z = threadIdx.x; z < N; z += NT) {
-                R sr = R(0), si = R(0);
-#pragma unroll 1
-                for (int j = 0; j < a.n; ++j) {
-                    const C x = b1[z ^ (1u << j)];
-                    sr += x.x;
-                    si += x.y;
+            for (uint32_t q = first; q < nvec; q += step) {
+                const uint32_t z = q * VE;
+                const V b = ld_v<R, false>(b1 + z);
+                V f, s, o;
+#pragma unroll
+                for (int v = 0; v < VE; ++v) {
+                    f.v[v] = (VE == 2) ? b.v[VE - 1 - v] : C{R(0), R(0)};
+                    s.v[v] = C{R(0), R(0)};
                 }
-                const C b = b1[z], s = b2[z], p = psi[z];
-                const R hr = fmad(a.d[z], b.x, st.g * sr), hi = fmad(a.d[z], b.y, st.g * si);
-                const R tr = fmad(scale, hr, -(a.sub * s.x)), ti = fmad(scale, hi, -(a.sub * s.y));
-                const C o{tr + fmad(ck.x, p.x, -(ck.y * p.y)), ti + fmad(ck.x, p.y, ck.y * p.x)};
-                if (k > 0) b2[z] = o;
-                else a.out[z] = C{fmad(st.pr, o.x, -(st.pi * o.y)), fmad(st.pr, o.y, st.pi * o.x)};
+                if (k < st.K - 1) s = ld_v<R, false>(b2 + z);
+                const V p = ld_v<R, false>(psi + z);
+#pragma unroll 1
+                for (int j = B0; j < a.n; j += 4) {
+                    V x[4];
+#pragma unroll
+                    for (int l = 0; l < 4; ++l)
+                        if (j + l < a.n) x[l] = ld_v<R, false>(b1 + (z ^ (1u << (j + l))));
+#pragma unroll
+                    for (int l = 0; l < 4; ++l)
+                        if (j + l < a.n)
+#pragma unroll
+                            for (int v = 0; v < VE; ++v) {
+                                f.v[v].x += x[l].v[v].x;
+                                f.v[v].y += x[l].v[v].y;
+                            }
+                }
+#pragma unroll
+                for (int v = 0; v < VE; ++v) {
+                    const R d = a.d[z + v];
+                    const R hr = fmad(d, b.v[v].x, g * f.v[v].x), hi = fmad(d, b.v[v].y, g * f.v[v].y);
+                    const R tr = fmad(scale, hr, -(a.sub * s.v[v].x)), ti = fmad(scale, hi, -(a.sub * s.v[v].y));
+                    const C w{tr + fmad(ck.x, p.v[v].x, -(ck.y * p.v[v].y)), ti + fmad(ck.x, p.v[v].y, ck.y * p.v[v].x)};
+                    o.v[v] = k > 0 ? w : C{fmad(st.pr, w.x, -(st.pi * w.y)), fmad(st.pr, w.y, st.pi * w.x)};
+                }
+                st_v<R, false>((k > 0 ? b2 : a.out) + z, o);
             }
-            __syncthreads();
             C *t = b1;
             b1 = b2;
             b2 = t;
         }
+        // the next step starts over b1, which the others may still be reading
+        if (i + 1 < a.nsteps) meet();
     }
 }
 
@@ -270,7 +333,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
     constexpr bool GUARD = (HC == 0 && NT == 64);        // the smallest shape also takes n < T
     __shared__ V lds[2][PER * NT];
     __shared__ TileEnergy<T> en;
-    __shared__ int go;
+    __shared__ int go, team[2];
 
     int w = 0;
     if constexpr (HC > 0) {
@@ -297,20 +360,21 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
             const int xcc = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, 4 bits
             (void)__hip_atomic_fetch_or(a.start + RES_LINE, 1 << xcc, __ATOMIC_RELAXED, QW_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            int ok = res_join(a.start, W, a.patience) ? 1 : 0;
-            if (ok) {
+            int id, ok = res_join(a.start, W, a.patience, &id);
+            if (ok == 1) {
                 const int m = __hip_atomic_load(a.start + RES_LINE, __ATOMIC_RELAXED, QW_AGENT);
                 if ((m & (m - 1)) == 0) ok = 2;
-            } else {
-                const int old = __hip_atomic_fetch_add(a.start, (int)RES_EXIT, __ATOMIC_RELAXED, QW_AGENT);
-                if (((old >> 12) & RES_CNT) + 1 == W) ok = -1;   // the last one out
+            } else if (ok == 0) {
+                team[0] = id;
+                team[1] = __hip_atomic_load(a.start + RES_TEAM, __ATOMIC_RELAXED, QW_AGENT);
             }
             go = ok;
         }
         __syncthreads();
         const int ok = __builtin_amdgcn_readfirstlane(go);
         if (ok <= 0) {
-            if (ok < 0) res_alone<R, NT>(a, en.hJ);
+            if (ok == 0)
+                res_team<R, NT>(a, en.hJ, __builtin_amdgcn_readfirstlane(team[0]), __builtin_amdgcn_readfirstlane(team[1]));
             return;
         }
         near = (ok == 2);
@@ -548,6 +612,7 @@ static hipError_t res_launch(const ResArgs<R> *ask, hipStream_t s, const PutBlob
     static std::atomic<unsigned> turn{0};
     a.stride = STRIDE;
     a.sel = (STRIDE > 1) ? (int)(turn.fetch_add(1, std::memory_order_relaxed) % STRIDE) : 0;
+    if (a.patience < 0) a.patience = COOP ? RES_PATIENCE_COOP : RES_PATIENCE;
     const dim3 grid((1u << HC) * STRIDE), block(NT);
     if constexpr (HC == 0) {
         if (blob) {
