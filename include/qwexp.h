@@ -32,7 +32,7 @@
  *     together (the device shared with other kernels that hold compute units), those
  *     that have started run it together after 0.4 ms, several times slower and with
  *     results that differ by rounding.  The two largest sizes in each precision are
- *     launched cooperatively, wait 0.1 s for their start, and run in passes
+ *     launched cooperatively, wait 6 ms for their start, and run in passes
  *     where a stream is being captured.  Where the workgroups have no room side by
  *     side (a partitioned device, a stream with masked compute units, a refused
  *     cooperative launch) every such size runs in passes.  A workgroup that waits
@@ -463,7 +463,7 @@ int qw_debug_schedule(int K, int P, int *out, int cap);
 
 /* For tests: how often the workgroups of a one-launch recurrence look at their
  * common start before those that have started run it together (calls of this host
- * thread from now on; negative: the default, 0.4 ms or 0.1 s), and tiles at their
+ * thread from now on; negative: the default, 0.4 or 6 ms), and tiles at their
  * partners' flags.  The results differ only by rounding.  Returns the value before. */
 int qw_debug_start_patience(int looks);
 

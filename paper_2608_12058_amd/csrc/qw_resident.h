@@ -20,10 +20,10 @@ static constexpr int RES_XCDS = 8;
 // mask of XCDs on two more lines.
 static constexpr int RES_LINE = 32;            // 4-byte words per line
 static constexpr int RES_MAXFLAGS = 4096;
-// Looks at the start word, 0.4 ms and 0.1 s.  Only a cooperative launch, of which a
+// Looks at the start word, 0.4 and 6 ms.  Only a cooperative launch, of which a
 // process runs one at a time, waits long: it needs every CU, so a plain one that
 // holds some and waits for more has to go on without them (k_resident's start).
-static constexpr int RES_PATIENCE = 1 << 9, RES_PATIENCE_COOP = 1 << 17;
+static constexpr int RES_PATIENCE = 1 << 9, RES_PATIENCE_COOP = 1 << 13;
 static constexpr int RES_POLLS = 1 << 24;      // looks at a flag, seconds
 int wait_polls();                              // the same, or what a test has set (qw_action.hip)
 
