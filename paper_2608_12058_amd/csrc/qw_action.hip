@@ -1250,7 +1250,7 @@ qw_status qw_expm_action_c64_noalloc(int n, const float *diag, const double *h, 
 
 
 const char *qw_last_error(void) { return g_err.c_str(); }
-const char *qw_version(void) { return "qwexp 0.16 (gfx950, one-launch recurrences and gradient sweeps to 20 qubits, fused passes of two orientations to 28 qubits with flips taken across tiles, three above, diagonal rebuilt in the strided orientations)"; }
+const char *qw_version(void) { return "qwexp 0.17 (gfx950, one-launch recurrences and gradient sweeps to 20 qubits, fused passes of two orientations to 28 qubits with flips taken across tiles, three above, diagonal rebuilt in the strided orientations)"; }
 
 size_t qw_workspace_bytes(int n, int precision, int on_the_fly)
 {
