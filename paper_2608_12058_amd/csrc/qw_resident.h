@@ -344,7 +344,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
     const int n = a.n;
     constexpr bool INLINE = std::is_same<BLOB, PutBlob>::value;
     static_assert(!INLINE || HC == 0, "one workgroup");
-    __shared__ uint64_t words[INLINE ? PutBlob::WORDS : 1];
+    __shared__ alignas(16) uint64_t words[INLINE ? PutBlob::WORDS : 1];
     const C *coef = a.coef;
     const double *hJ = a.hJ;
     if constexpr (INLINE) {
